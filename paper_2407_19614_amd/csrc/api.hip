@@ -99,11 +99,27 @@ SlabWS carve_slab(Arena& a, int N, int n_aux, int prec, bool comp) {
     return w;
 }
 
-// X^T = (B^P C)^T for all P; from resident packed B, or (B == nullptr) slab by
+ri::XSparse carve_sparse(Arena& a, int N, int n_aux, int64_t n_pairs) {
+    ri::XSparse w;
+    w.ldp = ri::xs_ldp(n_aux);
+    w.lmax = ri::xs_lmax(N);
+    w.map = a.take<int32_t>((int64_t)N * N);
+    w.list = a.take<int2>((int64_t)N * w.lmax);
+    w.cnt = a.take<int>(N);
+    w.n_pairs = n_pairs;
+    w.BcT = a.take<double>((n_pairs + 1) * w.ldp);
+    w.gpart = a.take<double>(ri::xs_gpart(n_aux, n_pairs));
+    return w;
+}
+
+// X^T = (B^P C)^T for all P; over the partner lists where xs holds them
+// (already prepared); else from resident packed B, or (B == nullptr) slab by
 // slab from B_c: unpack RI_COMPRESSED_SLAB auxiliaries into packed tiles, then
 // transform them into their rows of X^T.
 hipError_t x_any(const void* B, int prec, int N, int n_aux, int n_occ, const double* C, double* Cp, void* Xt,
-                 const double* Bc, const int32_t* pairs, int64_t n_pairs, const SlabWS& sw, hipStream_t st) {
+                 const double* Bc, const int32_t* pairs, int64_t n_pairs, const SlabWS& sw, const ri::XSparse& xs,
+                 hipStream_t st) {
+    if (xs.BcT && prec == RI_FP64) return ri::xs_transform(xs, N, n_aux, n_occ, C, Cp, (double*)Xt, st);
     if (B) return ri::x_transform(B, prec, N, n_aux, n_occ, C, Cp, Xt, st);
     if (!sw.Bs) return hipErrorInvalidValue;
     RI_TRY(ri::pair_map(pairs, n_pairs, N, sw.map, st));
@@ -116,10 +132,13 @@ hipError_t x_any(const void* B, int prec, int N, int n_aux, int n_occ, const dou
     return hipSuccess;
 }
 
-struct FockWS { void* Xt; double* part; double* dpair; double* jpart; double* gamma; double* Cp; int ks, js; SlabWS sw; };
-FockWS carve_fock(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, bool comp = false) {
+struct FockWS { void* Xt; double* part; double* dpair; double* jpart; double* gamma; double* Cp; int ks, js; SlabWS sw; ri::XSparse xs; };
+// pairs_x: the exchange may run over the partner lists (not for FP32-stored B in the FP64 layout)
+FockWS carve_fock(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, bool comp = false,
+                  bool pairs_x = true) {
     FockWS w;
-    w.sw = carve_slab(a, N, n_aux, prec, comp);
+    if (prec == RI_FP64 && pairs_x && ri::xs_wanted(N, n_aux, n_occ, n_pairs)) w.xs = carve_sparse(a, N, n_aux, n_pairs);
+    else w.sw = carve_slab(a, N, n_aux, prec, comp);
     const int Npad = ri::xt_ld(N);
     w.js = ri::j_split_count(n_aux);
     if (is_bf16(prec)) {
@@ -182,7 +201,7 @@ struct EnergyWS {
     DensityWS dens;
 };
 EnergyWS carve_energy(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, int diis_n,
-                      bool comp = false, bool fin_slab = false) {
+                      bool comp = false, bool fin_slab = false, bool pairs_x = true) {
     EnergyWS w;
     const int64_t n2 = (int64_t)N * N;
     double** mats[] = {&w.S, &w.H, &w.Ls, &w.LinvS, &w.J, &w.K, &w.F, &w.D, &w.T1, &w.T2, &w.E, &w.Fx, &w.X, &w.X2};
@@ -207,7 +226,7 @@ EnergyWS carve_energy(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, in
     w.tpart = a.take<double>(4 * (int64_t)ri::tc2f_tiles(N));   // purification partial sums, two parities
     w.bad = a.take<int>(2);
     w.tst = a.take<int>(16);                                    // purification state, two parities
-    w.fock = carve_fock(a, N, n_aux, n_occ, n_pairs, prec, comp);
+    w.fock = carve_fock(a, N, n_aux, n_occ, n_pairs, prec, comp, pairs_x);
     w.fin = fin_slab ? carve_fock(a, N, n_aux, n_occ, n_pairs, RI_FP64, true) : FockWS{};
     w.dens = carve_density(a, N, n_aux, n_pairs);
     return w;
@@ -220,11 +239,12 @@ EnergyWS carve_energy(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, in
 int energy_layout(const Prec& p) { return p.fin && !is_bf16(p.base) ? RI_FP64 : p.base; }
 bool energy_fin_slab(const Prec& p) { return p.fin && is_bf16(p.base); }
 
-struct GradWS { double *D, *W, *T1, *dpair, *gamma, *c, *Bij, *Xi, *Zx, *part, *Cp, *WY; void* Xt; float* Xt32; SlabWS sw; };
+struct GradWS { double *D, *W, *T1, *dpair, *gamma, *c, *Bij, *Xi, *Zx, *part, *Cp, *WY; void* Xt; float* Xt32; SlabWS sw; ri::XSparse xs; };
 GradWS carve_grad(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int n_centres, int prec,
                   bool comp = false) {
     GradWS w;
-    w.sw = carve_slab(a, N, n_aux, prec, comp);
+    if (prec == RI_FP64 && ri::xs_wanted(N, n_aux, n_occ, n_pairs)) w.xs = carve_sparse(a, N, n_aux, n_pairs);
+    else w.sw = carve_slab(a, N, n_aux, prec, comp);
     const int Npad = ri::xt_ld(N);
     const int64_t n2 = (int64_t)N * N, o2 = (int64_t)n_occ * n_occ;
     w.D = a.take<double>(n2);
@@ -301,10 +321,11 @@ struct Fork {
 // on `st` after X, ev[3] on `st` after the SYRK and the join (for the
 // split-BF16 forms the side stream forks after X).
 // With side == false everything runs on `st` (no side stream, no events): the
-// same kernels and sums, so the same results bit for bit.
+// same kernels and sums, so the same results bit for bit.  prepared: the
+// partner lists and the transposed fitted tensor of w.xs are there already.
 int32_t fock_impl(int N, int n_aux, int n_occ, const void* B, int prec, const double* Bc, const int32_t* pairs,
                   int64_t n_pairs, const double* C, double* J, double* K, double* gamma, const FockWS& w,
-                  hipStream_t st, hipEvent_t* ev = nullptr, bool side = true) {
+                  hipStream_t st, hipEvent_t* ev = nullptr, bool side = true, bool prepared = false) {
     double* g = gamma ? gamma : w.gamma;
     if (ev) HIPC(hipEventRecord(ev[0], st));
     Fork fk;
@@ -317,23 +338,31 @@ int32_t fock_impl(int N, int n_aux, int n_occ, const void* B, int prec, const do
         HIPC(ri::x_transform_bf16(B, prec, N, n_aux, n_occ, C, w.Cp, w.Xt, st));
         if (ev) HIPC(hipEventRecord(ev[2], st));
     }
+    const bool by_pairs = w.xs.BcT && prec == RI_FP64;
+    if (by_pairs && !prepared) HIPC(ri::xs_prepare(w.xs, Bc, pairs, n_pairs, N, n_aux, st));
     const bool overlap = side && fk.open(st);
     if (ev && !overlap) {
         ri::set_hip_error("side stream or its events could not be created");
         return RI_E_HIP;
     }
-    // beside a large FP64 or FP32 exchange, gamma and J run on a capped grid so
+    hipStream_t ss = overlap ? fk.side : st;
+    // beside a large dense FP64 or FP32 exchange, gamma and J run on a capped grid so
     // that the X kernel's workgroups are not held back behind thousands of
     // theirs; beside the split-BF16 SYRK, which is shorter than capped gamma/J
     // would be, they keep the full grid
     const bool capped = overlap && !bf && (int64_t)n_aux * n_pairs >= ri::GJ_SIDE_MIN;
-    HIPC(ri::gamma_j(Bc, pairs, n_pairs, N, n_aux, n_occ, C, w.dpair, g, w.jpart, w.js, J, overlap ? fk.side : st,
-                     capped ? ri::GJ_SIDE_CAP : 0));
+    if (by_pairs) {
+        HIPC(ri::dpair_orbitals(pairs, n_pairs, n_occ, C, w.dpair, ss));
+        HIPC(ri::xs_gamma_j(w.xs, N, n_aux, w.dpair, pairs, g, J, ss));
+    } else {
+        HIPC(ri::gamma_j(Bc, pairs, n_pairs, N, n_aux, n_occ, C, w.dpair, g, w.jpart, w.js, J, ss,
+                         capped ? ri::GJ_SIDE_CAP : 0));
+    }
     if (ev) HIPC(hipEventRecord(ev[1], fk.side));
     if (bf) {
         HIPC(ri::k_syrk_bf16(w.Xt, prec, N, n_aux, n_occ, w.part, w.ks, K, st));
     } else {
-        HIPC(x_any(B, prec, N, n_aux, n_occ, C, w.Cp, w.Xt, Bc, pairs, n_pairs, w.sw, st));
+        HIPC(x_any(B, prec, N, n_aux, n_occ, C, w.Cp, w.Xt, Bc, pairs, n_pairs, w.sw, w.xs, st));
         if (ev) HIPC(hipEventRecord(ev[2], st));
         HIPC(ri::k_syrk(w.Xt, prec, N, n_aux, n_occ, w.part, w.ks, K, st));
     }
@@ -459,7 +488,8 @@ size_t ri_workspace_bytes(int32_t op, int32_t N, int32_t n_aux, int32_t n_occ, i
         case RI_OP_METRIC: carve_metric(a, N, n_aux, n_pairs); break;
         case RI_OP_FOCK: carve_fock(a, N, n_aux, n_occ, n_pairs, prec, pp.comp); break;
         case RI_OP_ENERGY:
-            carve_energy(a, N, n_aux, n_occ, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp));
+            carve_energy(a, N, n_aux, n_occ, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp),
+                         pp.base == RI_FP64);
             break;
         case RI_OP_GRADIENT:
             carve_grad(a, N, n_aux, n_occ, n_pairs, 2048, is_bf16(prec) ? RI_FP64 : prec, pp.comp || is_bf16(prec));
@@ -672,7 +702,8 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
     const int N = sys->n_fn, na = sys->n_aux, no = sys->n_occ, dn = opts->diis_n;
     const int64_t n2 = (int64_t)N * N;
     Arena a{(char*)ws, ws_bytes, 0, false};
-    EnergyWS w = carve_energy(a, N, na, no, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp));
+    EnergyWS w = carve_energy(a, N, na, no, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp),
+                         pp.base == RI_FP64);
     if (!a.ok()) return RI_E_WORKSPACE;
     std::memset(res, 0, sizeof(*res));
 
@@ -708,6 +739,7 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
         HIPC(ri::gemm_f64(true, false, N, no, N, 1.0, w.Ls, N, 0, C_occ, no, 0, 0.0, w.Cp, no, 0, 1, 2, 0, st));
     }
 
+    if (w.fock.xs.BcT) HIPC(ri::xs_prepare(w.fock.xs, Bc, pairs, n_pairs, N, na, st));
     std::vector<int> slots;
     HIPC(ri::fill(w.Bfull, 0.0, 64, st));   // DIIS inner products <e_i, e_j>, indexed by ring slot
     int pushes = 0;
@@ -715,7 +747,8 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
     bool converged = false;
     int it = 0;
     for (it = 1; it <= opts->max_iter; ++it) {
-        rc = fock_impl(N, na, no, B, prec, Bc, pairs, n_pairs, C_occ, w.J, w.K, nullptr, w.fock, st);
+        rc = fock_impl(N, na, no, B, prec, Bc, pairs, n_pairs, C_occ, w.J, w.K, nullptr, w.fock, st, nullptr, true,
+                       true);
         if (rc) return rc;
         HIPC(ri::fock_assemble(w.H, w.J, w.K, w.F, n2, st));
         HIPC(ri::gemm_f64(false, true, N, N, no, 2.0, C_occ, no, 0, C_occ, no, 0, 0.0, w.D, N, 0, 1, 0, 0, st));
@@ -773,7 +806,8 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
         // hold B only to 2^-17 or 2^-25) from the FP64 B_c unpacked slab by
         // slab; the energy from the same D, h and J
         if (is_bf16(prec)) {
-            HIPC(x_any(nullptr, RI_FP64, N, na, no, C_occ, w.fin.Cp, w.fin.Xt, Bc, pairs, n_pairs, w.fin.sw, st));
+            if (w.fin.xs.BcT) HIPC(ri::xs_prepare(w.fin.xs, Bc, pairs, n_pairs, N, na, st));
+            HIPC(x_any(nullptr, RI_FP64, N, na, no, C_occ, w.fin.Cp, w.fin.Xt, Bc, pairs, n_pairs, w.fin.sw, w.fin.xs, st));
             HIPC(ri::k_syrk(w.fin.Xt, RI_FP64, N, na, no, w.fin.part, w.fin.ks, w.K, st));
         } else {
             HIPC(ri::x_transform(B, ri::X_F64_B32, N, na, no, C_occ, w.fock.Cp, w.fock.Xt, st));
@@ -831,10 +865,11 @@ int32_t ri_gradient(const ri_system* sys, const int32_t* pairs, int64_t n_pairs,
     HIPC(ri::grad_one_electron(sys, w.D, w.W, w.part, ss));
     // B_ij^P = (C^T B^P C)_ij from X^P = B^P C
     if (prec == RI_FP32) {
-        HIPC(x_any(B, prec, N, na, no, C, w.Cp, w.Xt32, Bc, pairs, n_pairs, w.sw, st));
+        HIPC(x_any(B, prec, N, na, no, C, w.Cp, w.Xt32, Bc, pairs, n_pairs, w.sw, w.xs, st));
         HIPC(ri::widen(w.Xt32, (double*)w.Xt, (int64_t)na * no * Npad, st));
     } else {
-        HIPC(x_any(B, prec, N, na, no, C, w.Cp, w.Xt, Bc, pairs, n_pairs, w.sw, st));
+        if (w.xs.BcT) HIPC(ri::xs_prepare(w.xs, Bc, pairs, n_pairs, N, na, st));
+        HIPC(x_any(B, prec, N, na, no, C, w.Cp, w.Xt, Bc, pairs, n_pairs, w.sw, w.xs, st));
     }
     // one GEMM over all (P, i) rows: the rows of X^T are stacked P-major, as B_ij's
     HIPC(ri::gemm_f64(false, false, na * no, no, N, 1.0, (const double*)w.Xt, Npad, 0, C, no, 0, 0.0, w.Bij, no, 0,

@@ -776,6 +776,12 @@ int cpad_ld(int n_occ) { return (n_occ + 127) / 128 * 128; }
 int64_t cpad_elems(int N, int n_occ) { return (int64_t)n_tiles_1d(N) * 64 * cpad_ld(n_occ); }
 
 
+hipError_t cpad(const double* C, int N, int n_occ, double* Cp, hipStream_t st) {
+    const int cld = cpad_ld(n_occ), rows = n_tiles_1d(N) * 64;
+    cpad_kernel<<<(unsigned)(((int64_t)rows * cld + 255) / 256), 256, 0, st>>>(C, N, n_occ, rows, cld, Cp);
+    return hipGetLastError();
+}
+
 // The FP64 X launch for shape code 4 * (16-row tiles) + (4-row quads); B
 // stored as TB (double, or float widened on load).
 template <typename TB>
@@ -829,8 +835,7 @@ hipError_t x_transform(const void* B, int prec, int N, int n_aux, int n_occ, con
     // buffer-resource offsets are 32-bit: one auxiliary index's packed tiles
     // and the padded C must each stay under 2 GiB (N below about 22,000)
     if (ntl * 4096 * 8 > INT32_MAX || (int64_t)rows * cld * 8 > INT32_MAX) return hipErrorInvalidValue;
-    cpad_kernel<<<(unsigned)(((int64_t)rows * cld + 255) / 256), 256, 0, st>>>(C, N, n_occ, rows, cld, Cp);
-    RI_TRY(hipGetLastError());
+    RI_TRY(cpad(C, N, n_occ, Cp, st));
     if (prec == X_F64_B32) return x_f64_launch((const float*)B, grid, mf * 4 + tq, nt, ntl, Cp, cld, N, n_occ, n_aux, x, Npad, st);
     return x_f64_launch((const double*)B, grid, mf * 4 + tq, nt, ntl, Cp, cld, N, n_occ, n_aux, x, Npad, st);
 }
@@ -881,13 +886,17 @@ hipError_t k_syrk(const void* Xt, int prec, int N, int n_aux, int n_occ, double*
 
 int j_split_count(int n_aux) { return n_aux >= 512 ? 16 : 1; }
 
+hipError_t dpair_orbitals(const int32_t* pairs, int64_t n_pairs, int n_occ, const double* C, double* dpair,
+                          hipStream_t st) {
+    if (n_pairs == 0) return hipSuccess;
+    dpair_kernel<<<(unsigned)((n_pairs + 255) / 256), 256, 0, st>>>(pairs, n_pairs, C, n_occ, dpair);
+    return hipGetLastError();
+}
+
 hipError_t gamma_j(const double* Bc, const int32_t* pairs, int64_t n_pairs, int N, int n_aux, int n_occ,
                    const double* C, double* dpair, double* gamma, double* jpart, int n_jsplit, double* J,
                    hipStream_t st, int cap) {
-    if (n_pairs > 0) {
-        dpair_kernel<<<(unsigned)((n_pairs + 255) / 256), 256, 0, st>>>(pairs, n_pairs, C, n_occ, dpair);
-        RI_TRY(hipGetLastError());
-    }
+    RI_TRY(dpair_orbitals(pairs, n_pairs, n_occ, C, dpair, st));
     return gamma_j_pairs(Bc, pairs, n_pairs, N, n_aux, dpair, gamma, jpart, n_jsplit, J, st, cap);
 }
 

@@ -44,6 +44,41 @@ int cpad_ld(int n_occ);
 int64_t cpad_elems(int N, int n_occ);
 hipError_t x_transform(const void* B, int prec, int N, int n_aux, int n_occ, const double* C,
                        double* Cp, void* Xt, hipStream_t st);
+// Cp = C zero-padded to [64 * tiles][cpad_ld(n_occ)]
+hipError_t cpad(const double* C, int N, int n_occ, double* Cp, hipStream_t st);
+// The same X^T from the fitted tensor over each row's significant partners
+// (FP64 arithmetic; B is not read).  xs_prepare lays out, from B_c and the pairs,
+// the partner lists [N][lmax] with their counts, and the transposed fitted
+// tensor [ldp / 64][n_pairs + 1][64]; the other calls may then run any number
+// of times.
+struct XSparse {
+    int32_t* map = nullptr;   // [N][N] pair index or -1
+    int2* list = nullptr;
+    int* cnt = nullptr;
+    double* BcT = nullptr;    // nullptr: the dense form is used
+    double* gpart = nullptr;  // xs_gpart(n_aux, n_pairs) doubles
+    int64_t n_pairs = 0;
+    int ldp = 0, lmax = 0;
+};
+// Whether a size takes this form: the pairs fill at most 60 % of the matrix
+// (its multiplications are those of the pairs; above, the dense kernel's whole
+// tiles cost no more than the gathers) and X^T is over 64 MiB (builds that fit
+// the static scratch of ri_fock_jk_noalloc keep the dense form and its
+// workspace, which need no partner lists or transposed copy).
+bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs);
+int xs_ldp(int n_aux);
+int xs_lmax(int N);
+int64_t xs_gpart(int n_aux, int64_t n_pairs);
+hipError_t xs_prepare(const XSparse& w, const double* Bc, const int32_t* pairs, int64_t n_pairs, int N, int n_aux,
+                      hipStream_t st);
+hipError_t xs_transform(const XSparse& w, int N, int n_aux, int n_occ, const double* C, double* Cp, double* Xt,
+                        hipStream_t st);
+// gamma and (J != nullptr) J from the pair weights dpair
+hipError_t xs_gamma_j(const XSparse& w, int N, int n_aux, const double* dpair, const int32_t* pairs, double* gamma,
+                      double* J, hipStream_t st);
+// pair weights of D = 2 C C^T
+hipError_t dpair_orbitals(const int32_t* pairs, int64_t n_pairs, int n_occ, const double* C, double* dpair,
+                          hipStream_t st);
 // K = sum_P X^P X^P^T from Xt; part = workspace of n_split * Npad^2 doubles.
 hipError_t k_syrk(const void* Xt, int prec, int N, int n_aux, int n_occ, double* part, int n_split,
                   double* K, hipStream_t st);
