@@ -138,7 +138,7 @@ FockWS carve_fock(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int pr
                   bool pairs_x = true) {
     FockWS w;
     if (prec == RI_FP64 && pairs_x && ri::xs_wanted(N, n_aux, n_occ, n_pairs)) w.xs = carve_sparse(a, N, n_aux, n_pairs);
-    else w.sw = carve_slab(a, N, n_aux, prec, comp);
+    w.sw = carve_slab(a, N, n_aux, prec, comp);   // the compressed form's size contract holds for either form of X
     const int Npad = ri::xt_ld(N);
     w.js = ri::j_split_count(n_aux);
     if (is_bf16(prec)) {
@@ -244,7 +244,7 @@ GradWS carve_grad(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int n_
                   bool comp = false) {
     GradWS w;
     if (prec == RI_FP64 && ri::xs_wanted(N, n_aux, n_occ, n_pairs)) w.xs = carve_sparse(a, N, n_aux, n_pairs);
-    else w.sw = carve_slab(a, N, n_aux, prec, comp);
+    w.sw = carve_slab(a, N, n_aux, prec, comp);   // the compressed form's size contract holds for either form of X
     const int Npad = ri::xt_ld(N);
     const int64_t n2 = (int64_t)N * N, o2 = (int64_t)n_occ * n_occ;
     w.D = a.take<double>(n2);
