@@ -920,8 +920,7 @@ int32_t ri_mlp_train_step(const ri_mlp* net, float* m, float* v, int32_t step, f
     if (off + 256 > ws_bytes) return RI_E_WORKSPACE;
     off = 0;
     ri::MlpWS w = ri::carve_mlp((char*)ws, ws_bytes, off, n);
-    HIPC(ri::mlp_train_step(net, m, v, step, lr, feat, target, n, loss, w, st));
-    if (grad) HIPC(hipMemcpyAsync(grad, w.grad, sizeof(float) * RI_MLP_NPARAM, hipMemcpyDeviceToDevice, st));
+    HIPC(ri::mlp_train_step(net, m, v, step, lr, feat, target, n, loss, grad, w, st));
     return RI_OK;
 }
 

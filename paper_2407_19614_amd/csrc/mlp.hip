@@ -25,8 +25,37 @@ __device__ __forceinline__ f4_t mfma_f32x4(float a, float b, f4_t c) {
 // f0 |A-B|, f1 ln max(a,b), f2 ln min(a,b), f3 same centre, f4 exp(-(ab/(a+b))|A-B|^2),
 // f5/f6 max/min coordination sum_{C != X} exp(-|R_X - R_C|^2 / 8),
 // f7 sum_C exp(-|P - R_C|^2 / 4) at the Gaussian product centre P.
-__global__ void features_kernel(const double* xyz, int nc, const int32_t* fc, const double* fe,
-                                const int32_t* pairs, int64_t n_pairs, float* feat) {
+// Bound by the exponentials.  The coordination depends on the centre only, so
+// each workgroup forms it once for all centres (8 partial sums each, in
+// dynamic LDS: 9 nc doubles) where COORD is set; the pair then needs one
+// exponential per centre instead of three.
+template <bool COORD>
+__global__ __launch_bounds__(256) void features_kernel(const double* __restrict__ xyz, int nc,
+                                                       const int32_t* __restrict__ fc,
+                                                       const double* __restrict__ fe,
+                                                       const int32_t* __restrict__ pairs, int64_t n_pairs,
+                                                       float* __restrict__ feat) {
+    extern __shared__ double cs[];   // [nc] coordination, then [nc][8] partial sums
+    if (COORD) {
+        for (int e = threadIdx.x; e < 8 * nc; e += 256) {
+            const int X = e >> 3;
+            const double x = xyz[3 * X], y = xyz[3 * X + 1], z = xyz[3 * X + 2];
+            double v = 0.0;
+            for (int c = e & 7; c < nc; c += 8) {
+                const double dx = x - xyz[3 * c], dy = y - xyz[3 * c + 1], dz = z - xyz[3 * c + 2];
+                if (c != X) v += exp(-(dx * dx + dy * dy + dz * dz) / 8.0);
+            }
+            cs[nc + e] = v;
+        }
+        __syncthreads();
+        for (int X = threadIdx.x; X < nc; X += 256) {
+            double v = 0.0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v += cs[nc + 8 * X + k];
+            cs[X] = v;
+        }
+        __syncthreads();
+    }
     int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (q >= n_pairs) return;
     int mu = pairs[2 * q], nu = pairs[2 * q + 1];
@@ -38,15 +67,17 @@ __global__ void features_kernel(const double* xyz, int nc, const int32_t* fc, co
     double r2 = dx * dx + dy * dy + dz * dz;
     double Px = (a * A[0] + b * B[0]) / (a + b), Py = (a * A[1] + b * B[1]) / (a + b),
            Pz = (a * A[2] + b * B[2]) / (a + b);
-    double cA = 0.0, cB = 0.0, md = 0.0;
+    double cA = COORD ? cs[ca] : 0.0, cB = COORD ? cs[cb] : 0.0, md = 0.0;
     for (int c = 0; c < nc; ++c) {
         const double* C = xyz + 3 * c;
-        double ax = A[0] - C[0], ay = A[1] - C[1], az = A[2] - C[2];
-        double bx = B[0] - C[0], by = B[1] - C[1], bz = B[2] - C[2];
         double px = Px - C[0], py = Py - C[1], pz = Pz - C[2];
-        if (c != ca) cA += exp(-(ax * ax + ay * ay + az * az) / 8.0);
-        if (c != cb) cB += exp(-(bx * bx + by * by + bz * bz) / 8.0);
         md += exp(-(px * px + py * py + pz * pz) / 4.0);
+        if (!COORD) {
+            double ax = A[0] - C[0], ay = A[1] - C[1], az = A[2] - C[2];
+            double bx = B[0] - C[0], by = B[1] - C[1], bz = B[2] - C[2];
+            if (c != ca) cA += exp(-(ax * ax + ay * ay + az * az) / 8.0);
+            if (c != cb) cB += exp(-(bx * bx + by * by + bz * bz) / 8.0);
+        }
     }
     float* f = feat + q * NF;
     f[0] = (float)sqrt(r2);
@@ -59,120 +90,379 @@ __global__ void features_kernel(const double* xyz, int nc, const int32_t* fc, co
     f[7] = (float)md;
 }
 
-// layer 1: z1 = ((f - mu) / sigma) W1 + b1 (keeps x-hat for the backward), h1 = silu(z1)
-__global__ void layer1_kernel(const float* feat, int64_t n, const float* mu, const float* sg, const float* W1,
-                              const float* b1, float* xh, float* z1, float* h1) {
-    int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= n * W) return;
-    int64_t r = e / W;
-    int c = e % W;
-    float s = b1[c];
-#pragma unroll
-    for (int k = 0; k < NF; ++k) {
-        float x = (feat[r * NF + k] - mu[k]) / sg[k];
-        s += x * W1[k * W + c];
-        if (c == 0) xh[r * NF + k] = x;
-    }
-    z1[e] = s;
-    h1[e] = silu(s);
-}
+// Layout of one block's partial sums in a training step (columns of `part`)
+constexpr int PW1 = 0, PB1 = PW1 + NF * W, PB2 = PB1 + W, PW3 = PB2 + W, PB3 = PW3 + W, PLOSS = PB3 + 1, PCOLS = PLOSS + 1;
 
-// C[M][N] = op(A) op(B) (+ bias[N]) with optional silu epilogue, FP32 MFMA,
-// 64 x 64 tiles staged through LDS.  A: TA ? [K][M] : [M][K]; B: TB ? [N][K] : [K][N].
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
-                                                       int lda, const float* __restrict__ B, int ldb,
-                                                       float* __restrict__ C, int ldc, const float* bias,
-                                                       float* Cact) {
-    __shared__ float As[16][65];
-    __shared__ float Bs[16][65];
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+// The network on 32 MT rows, all three layers in one launch, and with TRAIN
+// the loss and the backward pass of the same rows down to the partial sums of
+// every gradient but W2's, so that the activations never leave the chip
+// except for h1 and dz2, the operands of that one product.
+// The 256 x 256 layer runs on MFMA: 8 waves, each 16 MT rows x 64 columns
+// (MT x 4 tiles); its A operand comes from the block's activations in LDS
+// (rows padded by 4 floats or 8 bfloat16: conflict-free), its B operand
+// straight from W2 in 16-byte loads, since 256 KB of weights do not fit beside
+// them and are shared by every block through L2.
+//   forward FP32: columns 4 li + t of tile t, one load for four tiles;
+//   forward BF16: columns 16 t + li from W2^T in bfloat16, 32-deep MFMAs;
+//   backward: output columns 16 t + li are rows of W2, one load for four
+//   k-steps (k = 16 u + 4 g + h on both operands).
+// Bound by MFMA throughput (the FP32 step's 4.3 GFLOP of this kernel take 27
+// us at peak) and the latency of the weight loads.  Before, each layer,
+// elementwise step and column sum was a launch of its own over the activations
+// in memory.  Measured, training step of 16384 rows: 5171 -> 98 us (this kernel
+// 73, g_W2 25, the update 11; g_W2 and g_W1 alone took 4761 on 20 workgroups);
+// BF16 inference with the features of 22,000 pairs: 99 -> 36 us.
+template <bool BF16, bool TRAIN, int MT>
+__global__ __launch_bounds__(512, 2) void mlp_kernel(const float* __restrict__ feat, int64_t n,
+                                                     const float* __restrict__ mu, const float* __restrict__ sg,
+                                                     const float* __restrict__ P, const __bf16* __restrict__ W2t,
+                                                     float* __restrict__ y_out, const float* __restrict__ target,
+                                                     float* __restrict__ h1g, float* __restrict__ dz2g,
+                                                     float* __restrict__ part) {
+    constexpr int RB = 32 * MT;
+    constexpr int LDF = W + 4, LDB = W + 8;
+    __shared__ __align__(16) float H[BF16 ? RB * LDB / 2 : RB * LDF];   // h1, then dz2
+    __shared__ float X[RB][NF];
+    __shared__ float ys[4][RB], dyv[RB];
+    const float* W1 = P + RI_MLP_OFF_W1;
+    const float* W2 = P + RI_MLP_OFF_W2;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    f4_t acc[2][2];
+    const int64_t r0 = (int64_t)blockIdx.x * RB;
+    for (int e = tid; e < RB * NF; e += 512) {
+        const int r = e / NF, k = e % NF;
+        X[r][k] = r0 + r < n ? (feat[(r0 + r) * NF + k] - mu[k]) / sg[k] : 0.0f;
+    }
+    __syncthreads();
+    {
+        const int c = tid & (W - 1);
+        float w[NF];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int k = 0; k < NF; ++k) w[k] = W1[k * W + c];
+        const float b = P[RI_MLP_OFF_B1 + c];
+        for (int r = tid >> 8; r < RB; r += 2) {
+            float z = b;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f4_t{0, 0, 0, 0};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            int m, k;
-            if (!TA) { k = tid & 15; m = (tid >> 4) + 16 * r; }
-            else     { m = tid & 63; k = (tid >> 6) + 4 * r; }
-            int gm = m0 + m, gk = k0 + k;
-            As[k][m] = (gm < M && gk < K) ? (TA ? A[(int64_t)gk * lda + gm] : A[(int64_t)gm * lda + gk]) : 0.0f;
-            int n, kb;
-            if (!TB) { n = tid & 63; kb = (tid >> 6) + 4 * r; }
-            else     { kb = tid & 15; n = (tid >> 4) + 16 * r; }
-            int gn = n0 + n, gkb = k0 + kb;
-            Bs[kb][n] = (gn < N && gkb < K) ? (TB ? B[(int64_t)gn * ldb + gkb] : B[(int64_t)gkb * ldb + gn]) : 0.0f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; kk += 4) {
-            float a0 = As[kk + lk][wm + li], a1 = As[kk + lk][wm + 16 + li];
-            float b0 = Bs[kk + lk][wn + li], b1 = Bs[kk + lk][wn + 16 + li];
-            acc[0][0] = mfma_f32x4(a0, b0, acc[0][0]);
-            acc[0][1] = mfma_f32x4(a0, b1, acc[0][1]);
-            acc[1][0] = mfma_f32x4(a1, b0, acc[1][0]);
-            acc[1][1] = mfma_f32x4(a1, b1, acc[1][1]);
+            for (int k = 0; k < NF; ++k) z += X[r][k] * w[k];
+            const float h = silu(z);
+            if constexpr (BF16) ((__bf16*)H)[r * LDB + c] = (__bf16)h;
+            else H[r * LDF + c] = h;
+            if (TRAIN) h1g[(r0 + r) * W + c] = h;
         }
     }
+    __syncthreads();
+    const int wr = (wave >> 2) * 16 * MT, cq = (wave & 3) * 64;
+    auto col = [&](int t) { return cq + (BF16 ? 16 * t + li : 4 * li + t); };
+    f4_t acc[MT][4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int t = 0; t < 4; ++t) acc[i][t] = f4_t{0, 0, 0, 0};
+    if constexpr (BF16) {
+        const __bf16* Hb = (const __bf16*)H;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                int gm = m0 + wm + 16 * i + 4 * lk + r, gn = n0 + wn + 16 * j + li;
-                if (gm < M && gn < N) {
-                    float v = acc[i][j][r] + (bias ? bias[gn] : 0.0f);
-                    C[(int64_t)gm * ldc + gn] = v;
-                    if (Cact) Cact[(int64_t)gm * ldc + gn] = silu(v);
-                }
+        for (int k0 = 0; k0 < W; k0 += 32) {
+            bf16x8_t b[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) b[t] = *(const bf16x8_t*)(W2t + (int64_t)(cq + 16 * t + li) * W + k0 + 8 * lk);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const bf16x8_t a = *(const bf16x8_t*)(Hb + (wr + 16 * i + li) * LDB + k0 + 8 * lk);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[t], acc[i][t], 0, 0, 0);
             }
+        }
+    } else {
+        const float* bp = W2 + lk * W + cq + 4 * li;
+        constexpr int D = 8;                       // k-steps of weights in flight
+        f4_t b[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) b[d] = *(const f4_t*)(bp + 4 * d * W);
+        for (int s0 = 0; s0 < W / 4; s0 += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const int s = s0 + d;
+                float a[MT];
+#pragma unroll
+                for (int i = 0; i < MT; ++i) a[i] = H[(wr + 16 * i + li) * LDF + 4 * s + lk];
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) acc[i][t] = mfma_f32x4(a[i], b[d][t], acc[i][t]);
+                b[d] = *(const f4_t*)(bp + 4 * min(s + D, W / 4 - 1) * W);
+            }
+        }
+    }
+    // element q of lane (li, lk) in tile (i, t): row wr + 16 i + 4 lk + q, column col(t)
+    float w3[4], b2[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        w3[t] = P[RI_MLP_OFF_W3 + col(t)];
+        b2[t] = P[RI_MLP_OFF_B2 + col(t)];
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float v = 0.0f;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                acc[i][t][q] += b2[t];             // z2
+                v += silu(acc[i][t][q]) * w3[t];
+            }
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
+            if (li == 0) ys[wave & 3][wr + 16 * i + 4 * lk + q] = v;
+        }
+    __syncthreads();                               // also: every wave has read h1
+    if (tid < RB) {
+        const float y = ys[0][tid] + ys[1][tid] + ys[2][tid] + ys[3][tid] + P[RI_MLP_OFF_B3];
+        const bool in = r0 + tid < n;
+        if (!TRAIN && in) y_out[r0 + tid] = y;
+        if (TRAIN) {
+            const float r = in ? y - target[r0 + tid] : 0.0f;
+            dyv[tid] = 2.0f * r / (float)n;
+            ys[0][tid] = r * r;
+        }
+    }
+    if constexpr (TRAIN) {
+        static_assert(!BF16, "training is FP32");
+        __syncthreads();
+        float* pp = part + (int64_t)blockIdx.x * PCOLS;
+        if (tid == 0) {
+            float l = 0.0f, d = 0.0f;
+            for (int r = 0; r < RB; ++r) {
+                l += ys[0][r];
+                d += dyv[r];
+            }
+            pp[PLOSS] = l;
+            pp[PB3] = d;
+        }
+        float g3[4], gb[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) g3[t] = gb[t] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int row = wr + 16 * i + 4 * lk + q;
+                const float dy = dyv[row];
+                f4_t o;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float z = acc[i][t][q];
+                    g3[t] += silu(z) * dy;
+                    o[t] = dy * w3[t] * dsilu(z);
+                    gb[t] += o[t];
+                }
+                *(f4_t*)(H + row * LDF + cq + 4 * li) = o;
+                *(f4_t*)(dz2g + (r0 + row) * W + cq + 4 * li) = o;
+            }
+        __shared__ float red[PB3];                 // the upper rows' share of the column sums
+        auto colsum = [&](float v, int at, bool low) {
+            v += __shfl_xor(v, 16);
+            v += __shfl_xor(v, 32);
+            if (lk == 0) {
+                if (low) pp[at] = v + red[at];
+                else red[at] = v;
+            }
+        };
+        const bool low = wave < 4;
+        if (!low)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                colsum(g3[t], PW3 + col(t), false);
+                colsum(gb[t], PB2 + col(t), false);
+            }
+        __syncthreads();
+        if (low)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                colsum(g3[t], PW3 + col(t), true);
+                colsum(gb[t], PB2 + col(t), true);
+            }
+        // dh1 = dz2 W2^T
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[i][t] = f4_t{0, 0, 0, 0};
+        f4_t b[2][4];
+        const float* bp = W2 + (int64_t)(cq + li) * W + 4 * lk;
+#pragma unroll
+        for (int d = 0; d < 2; ++d)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) b[d][t] = *(const f4_t*)(bp + 16 * t * W + 16 * d);
+        for (int u0 = 0; u0 < W / 16; u0 += 2) {
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                const int u = u0 + d;
+                f4_t a[MT];
+#pragma unroll
+                for (int i = 0; i < MT; ++i) a[i] = *(const f4_t*)(H + (wr + 16 * i + li) * LDF + 16 * u + 4 * lk);
+#pragma unroll
+                for (int h = 0; h < 4; ++h)
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) acc[i][t] = mfma_f32x4(a[i][h], b[d][t][h], acc[i][t]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) b[d][t] = *(const f4_t*)(bp + 16 * t * W + 16 * min(u + 2, W / 16 - 1));
+            }
+        }
+        // dz1 = dh1 silu'(z1) with z1 formed again, and its sums; columns 16 t + li
+        float hold[4][NF + 1];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int c = cq + 16 * t + li;
+            float w[NF], g[NF], s = 0.0f;
+#pragma unroll
+            for (int k = 0; k < NF; ++k) {
+                w[k] = W1[k * W + c];
+                g[k] = 0.0f;
+            }
+            const float b1 = P[RI_MLP_OFF_B1 + c];
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float* x = X[wr + 16 * i + 4 * lk + q];
+                    float z = b1;
+#pragma unroll
+                    for (int k = 0; k < NF; ++k) z += x[k] * w[k];
+                    const float d = acc[i][t][q] * dsilu(z);
+                    s += d;
+#pragma unroll
+                    for (int k = 0; k < NF; ++k) g[k] += x[k] * d;
+                }
+            if (!low) {
+                colsum(s, PB1 + c, false);
+#pragma unroll
+                for (int k = 0; k < NF; ++k) colsum(g[k], PW1 + k * W + c, false);
+            } else {
+                hold[t][0] = s;
+#pragma unroll
+                for (int k = 0; k < NF; ++k) hold[t][k + 1] = g[k];
+            }
+        }
+        __syncthreads();
+        if (low)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int c = cq + 16 * t + li;
+                colsum(hold[t][0], PB1 + c, true);
+#pragma unroll
+                for (int k = 0; k < NF; ++k) colsum(hold[t][k + 1], PW1 + k * W + c, true);
+            }
+    }
 }
 
-// z2 = h1 W2 + b2 with BF16 operands (h1 and W2^T converted on the fly) and
-// FP32 accumulation: v_mfma_f32_16x16x32_bf16, lane l supplies rows l%16 and
-// k = 8 (l/16) + 0..7, receives D[4 (l/16) + r][l%16].  One wave per 16 x 64
-// output block, operands read directly from global memory.
-__global__ __launch_bounds__(256) void layer2_bf16_kernel(const float* __restrict__ h1, int64_t n,
-                                                          const __bf16* __restrict__ W2t, const float* b2,
-                                                          float* __restrict__ z2, float* __restrict__ h2) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
-    const int64_t r0 = (blockIdx.x * 4 + wave) * 16;
-    const int c0 = blockIdx.y * 64;
-    if (r0 >= n) return;
-    f4_t acc[4];
+// g_W2 partials: rows r of one split of h1^T dz2 (both [rows][256], rows a
+// multiple of 32).  One 64 x 64 tile per workgroup; each of its 4 waves takes
+// a quarter of the split's rows over the whole tile, its operands straight
+// from memory (16 bytes per lane: rows m = 4 li + i, columns 4 li + j of tile
+// (i, j)), and the four sums meet in LDS.  The product has 16 tiles only, so
+// the reduction over the rows is split to fill the chip; without that it ran
+// on 16 workgroups (2.4 ms for 16384 rows).
+__global__ __launch_bounds__(256, 2) void gw2_kernel(const float* __restrict__ h1, const float* __restrict__ dz2,
+                                                     int64_t rows, int64_t per, float* __restrict__ part) {
+    __shared__ f4_t sh[3][64][17];
+    const int tile = blockIdx.x & 15, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+    const int64_t z = blockIdx.x >> 4;
+    const int m0 = (tile >> 2) * 64, n0 = (tile & 3) * 64;
+    const int64_t a0 = (4 * z + wave) * per, a1 = min(rows, a0 + per);
+    f4_t acc[4][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = f4_t{0, 0, 0, 0};
-    const int64_t row = min(r0 + li, n - 1);
-    for (int k0 = 0; k0 < W; k0 += 32) {
-        bf16x8_t a;
-        const float* hp = h1 + row * W + k0 + 8 * lk;
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int t = 0; t < 8; ++t) a[t] = (__bf16)hp[t];
+        for (int j = 0; j < 4; ++j) acc[i][j] = f4_t{0, 0, 0, 0};
+    const float* ap = h1 + (a0 + lk) * W + m0 + 4 * li;
+    const float* bp = dz2 + (a0 + lk) * W + n0 + 4 * li;
+    const int steps = a1 > a0 ? (int)((a1 - a0) / 4) : 0;
+    constexpr int D = 4;
+    if (steps > 0) {                               // per and rows are multiples of 16: steps of D
+        f4_t a[D], b[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            a[d] = *(const f4_t*)(ap + (int64_t)d * 4 * W);
+            b[d] = *(const f4_t*)(bp + (int64_t)d * 4 * W);
+        }
+        for (int s0 = 0; s0 < steps; s0 += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[i][j] = mfma_f32x4(a[d][i], b[d][j], acc[i][j]);
+                const int64_t nx = (int64_t)min(s0 + d + D, steps - 1) * 4 * W;
+                a[d] = *(const f4_t*)(ap + nx);
+                b[d] = *(const f4_t*)(bp + nx);
+            }
+        }
+    }
+    if (wave > 0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sh[wave - 1][lane][4 * i + j] = acc[i][j];
+    __syncthreads();
+    if (wave > 0) return;
+    float* out = part + z * (W * W);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const bf16x8_t b = *(const bf16x8_t*)(W2t + (int64_t)(c0 + 16 * j + li) * W + k0 + 8 * lk);
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[j], 0, 0, 0);
+#pragma unroll
+            for (int w = 0; w < 3; ++w) acc[i][j] += sh[w][lane][4 * i + j];
         }
+    // element q of tile (i, j): row m0 + 4 (4 lk + q) + i, columns n0 + 4 li + j
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f4_t v = f4_t{acc[i][0][q], acc[i][1][q], acc[i][2][q], acc[i][3][q]};
+            *(f4_t*)(out + (m0 + 4 * (4 * lk + q) + i) * W + n0 + 4 * li) = v;
+        }
+}
+
+// The gradient from its partial sums (W2's splits in pw2, everything else and
+// the loss in pr, one row per block), and the Adam update.  Blocks
+// 0 .. 255 take W2's rows, the others 32 further columns each (8 threads per
+// column over the rows, summed in one fixed order).
+__global__ __launch_bounds__(256) void grad_adam_kernel(const float* __restrict__ pw2, int splits,
+                                                        const float* __restrict__ pr, int nrow, float inv_n,
+                                                        float* __restrict__ p, float* __restrict__ g_out,
+                                                        float* __restrict__ m, float* __restrict__ v,
+                                                        float* __restrict__ loss, float lr, float b1, float b2,
+                                                        float eps, float c1, float c2) {
+    __shared__ float sh[8][33];
+    int i = -1;
+    float gi = 0.0f;
+    if (blockIdx.x < W) {
+        const int e = blockIdx.x * W + threadIdx.x;
+        for (int z = 0; z < splits; ++z) gi += pw2[(int64_t)z * (W * W) + e];
+        i = RI_MLP_OFF_W2 + e;
+    } else {
+        const int c = threadIdx.x & 31, k = threadIdx.x >> 5, e = (blockIdx.x - W) * 32 + c;
+        float s = 0.0f;
+        if (e < PCOLS)
+            for (int r = k; r < nrow; r += 8) s += pr[(int64_t)r * PCOLS + e];
+        sh[k][c] = s;
+        __syncthreads();
+        if (k != 0 || e >= PCOLS) return;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) gi += sh[j][c];
+        if (e == PLOSS) {
+            *loss = gi * inv_n;
+            return;
+        }
+        i = e < PB1 ? RI_MLP_OFF_W1 + e : e < PB2 ? RI_MLP_OFF_B1 + e - PB1 : e < PW3 ? RI_MLP_OFF_B2 + e - PB2
+            : e < PB3 ? RI_MLP_OFF_W3 + e - PW3 : RI_MLP_OFF_B3;
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            int64_t gr = r0 + 4 * lk + r;
-            int gc = c0 + 16 * j + li;
-            if (gr < n) {
-                float v = acc[j][r] + b2[gc];
-                z2[gr * W + gc] = v;
-                h2[gr * W + gc] = silu(v);
-            }
-        }
+    if (g_out) g_out[i] = gi;
+    const float mi = b1 * m[i] + (1.0f - b1) * gi;
+    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
+    m[i] = mi;
+    v[i] = vi;
+    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
 __global__ void transpose_bf16_kernel(const float* W2, __bf16* W2t) {
@@ -180,94 +470,6 @@ __global__ void transpose_bf16_kernel(const float* W2, __bf16* W2t) {
     if (e >= W * W) return;
     int k = e / W, c = e % W;
     W2t[c * W + k] = (__bf16)W2[e];
-}
-
-// y = h2 w3 + b3: one wave per row
-__global__ __launch_bounds__(256) void layer3_kernel(const float* h2, int64_t n, const float* w3, const float* b3,
-                                                     float* y) {
-    const int lane = threadIdx.x & 63;
-    const int64_t r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= n) return;
-    float s = 0.0f;
-    for (int c = lane; c < W; c += 64) s += h2[r * W + c] * w3[c];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
-    if (lane == 0) y[r] = s + b3[0];
-}
-
-// dy = 2 (y - t) / n, partial sums of (y - t)^2 per block
-__global__ __launch_bounds__(256) void mse_kernel(const float* y, const float* t, int64_t n, float* dy,
-                                                  float* part) {
-    int64_t i = blockIdx.x * 256ll + threadIdx.x;
-    float r = 0.0f;
-    if (i < n) {
-        r = y[i] - t[i];
-        dy[i] = 2.0f * r / (float)n;
-    }
-    float s = r * r;
-    __shared__ float sh[4];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
-}
-
-__global__ void sum_kernel(const float* part, int np, float scale, float* out) {
-    if (threadIdx.x != 0) return;
-    float s = 0.0f;
-    for (int i = 0; i < np; ++i) s += part[i];
-    *out = s * scale;
-}
-
-// dz2 = dy (x) w3 * silu'(z2), in place over z2's buffer
-__global__ void dz2_kernel(const float* dy, const float* w3, int64_t n, float* z2) {
-    int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= n * W) return;
-    z2[e] = dy[e / W] * w3[e % W] * dsilu(z2[e]);
-}
-
-// dz1 = dh1 * silu'(z1), in place over dh1
-__global__ void dz1_kernel(const float* z1, int64_t n, float* dh1) {
-    int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= n * W) return;
-    dh1[e] *= dsilu(z1[e]);
-}
-
-// column sums of A [n][cols] over row chunks: part[blk][c]
-__global__ void colsum_partial_kernel(const float* A, int64_t n, int cols, int64_t rows_per, float* part) {
-    int c = threadIdx.x + blockIdx.y * blockDim.x;
-    if (c >= cols) return;
-    int64_t r0 = blockIdx.x * rows_per, r1 = min(n, r0 + rows_per);
-    float s = 0.0f;
-    for (int64_t r = r0; r < r1; ++r) s += A[r * cols + c];
-    part[(int64_t)blockIdx.x * cols + c] = s;
-}
-__global__ void colsum_final_kernel(const float* part, int nblk, int cols, float* out) {
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
-    float s = 0.0f;
-    for (int b = 0; b < nblk; ++b) s += part[(int64_t)b * cols + c];
-    out[c] = s;
-}
-
-// g_w3[c] = sum_r h2[r][c] dy[r] (partials over row chunks)
-__global__ void gw3_partial_kernel(const float* h2, const float* dy, int64_t n, int64_t rows_per, float* part) {
-    int c = threadIdx.x;
-    int64_t r0 = blockIdx.x * rows_per, r1 = min(n, r0 + rows_per);
-    float s = 0.0f;
-    for (int64_t r = r0; r < r1; ++r) s += h2[r * W + c] * dy[r];
-    part[(int64_t)blockIdx.x * W + c] = s;
-}
-
-__global__ void adam_kernel(float* p, const float* g, float* m, float* v, int n, float lr, float b1, float b2,
-                            float eps, float c1, float c2) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float gi = g[i];
-    float mi = b1 * m[i] + (1.0f - b1) * gi;
-    float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
 __global__ void scatter_density_kernel(const int32_t* pairs, int64_t n_pairs, const float* d, int N, double* D) {
@@ -357,15 +559,12 @@ __global__ void density_add_kernel(const int32_t* pairs, int64_t n_pairs, const 
     Dout[(int64_t)nu * N + mu] = v;
 }
 
-inline unsigned g1(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
+// Rows per workgroup: 64, or 32 where 64 would leave most of the 256 CUs idle.
+int block_rows(int64_t n) { return n > 64 * 256 / 2 ? 64 : 32; }
+// Most splits of g_W2's row sum: 16 tiles x 32 = two workgroups per CU.
+constexpr int GW2_SPLITS = 32;
 
-template <bool TA, bool TB>
-hipError_t gemm_f32(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
-                    const float* bias, float* Cact, hipStream_t st) {
-    dim3 grid((N + 63) / 64, (M + 63) / 64);
-    gemm_f32_kernel<TA, TB><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, bias, Cact);
-    return hipGetLastError();
-}
+inline unsigned g1(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
 
@@ -373,7 +572,13 @@ namespace ri {
 
 hipError_t pair_features(const ri_system* s, const int32_t* pairs, int64_t n_pairs, float* feat, hipStream_t st) {
     if (n_pairs == 0) return hipSuccess;
-    features_kernel<<<g1(n_pairs), 256, 0, st>>>(s->xyz, s->n_centres, s->fn_centre, s->fn_exp, pairs, n_pairs, feat);
+    const size_t lds = 9 * sizeof(double) * (size_t)s->n_centres;
+    if (lds <= 32768)   // 455 centres; beyond, the sums no longer leave room for several workgroups per CU
+        features_kernel<true><<<g1(n_pairs), 256, lds, st>>>(s->xyz, s->n_centres, s->fn_centre, s->fn_exp, pairs,
+                                                             n_pairs, feat);
+    else
+        features_kernel<false><<<g1(n_pairs), 256, 0, st>>>(s->xyz, s->n_centres, s->fn_centre, s->fn_exp, pairs,
+                                                            n_pairs, feat);
     return hipGetLastError();
 }
 
@@ -385,15 +590,11 @@ MlpWS carve_mlp(char* base, size_t cap, size_t& off, int64_t n) {
         return base ? (void*)(base + o) : nullptr;
     };
     MlpWS w;
-    w.xh = (float*)take(n * NF, 4);
-    w.z1 = (float*)take(n * W, 4);
-    w.h1 = (float*)take(n * W, 4);
-    w.z2 = (float*)take(n * W, 4);
-    w.h2 = (float*)take(n * W, 4);
-    w.y = (float*)take(n, 4);
-    w.dy = (float*)take(n, 4);
-    w.part = (float*)take((int64_t)std::max<int64_t>(1024, (n + 255) / 256) * W, 4);
-    w.grad = (float*)take(RI_MLP_NPARAM, 4);
+    const int64_t rows = (n + 63) / 64 * 64;
+    w.h1 = (float*)take(rows * W, 4);
+    w.dz2 = (float*)take(rows * W, 4);
+    w.part = (float*)take((rows / 32) * PCOLS, 4);
+    w.pw2 = (float*)take((int64_t)GW2_SPLITS * W * W, 4);
     w.W2t = (__bf16*)take(W * W, 2);
     (void)cap;
     return w;
@@ -402,60 +603,43 @@ MlpWS carve_mlp(char* base, size_t cap, size_t& off, int64_t n) {
 hipError_t mlp_forward(const ri_mlp* net, const float* feat, int64_t n, float* y, int prec, const MlpWS& w,
                        hipStream_t st) {
     const float* P = net->params;
-    layer1_kernel<<<g1(n * W), 256, 0, st>>>(feat, n, net->mu, net->sigma, P + RI_MLP_OFF_W1, P + RI_MLP_OFF_B1,
-                                             w.xh, w.z1, w.h1);
-    RI_TRY(hipGetLastError());
+    const int rb = block_rows(n);
     if (prec == RI_MLP_BF16) {
         transpose_bf16_kernel<<<g1(W * W), 256, 0, st>>>(P + RI_MLP_OFF_W2, w.W2t);
         RI_TRY(hipGetLastError());
-        dim3 grid((unsigned)((n + 63) / 64), W / 64);
-        layer2_bf16_kernel<<<grid, 256, 0, st>>>(w.h1, n, w.W2t, P + RI_MLP_OFF_B2, w.z2, w.h2);
-    } else {
-        RI_TRY((gemm_f32<false, false>((int)n, W, W, w.h1, W, P + RI_MLP_OFF_W2, W, w.z2, W, P + RI_MLP_OFF_B2, w.h2, st)));
     }
-    RI_TRY(hipGetLastError());
-    layer3_kernel<<<g1(n, 4), 256, 0, st>>>(w.h2, n, P + RI_MLP_OFF_W3, P + RI_MLP_OFF_B3, y);
+#define FWD(B, M) mlp_kernel<B, false, M><<<g1(n, rb), 512, 0, st>>>(feat, n, net->mu, net->sigma, P, w.W2t, y, \
+                                                                     nullptr, nullptr, nullptr, nullptr)
+    if (prec == RI_MLP_BF16) {
+        if (rb == 64) FWD(true, 2); else FWD(true, 1);
+    } else {
+        if (rb == 64) FWD(false, 2); else FWD(false, 1);
+    }
+#undef FWD
     return hipGetLastError();
 }
 
 hipError_t mlp_train_step(const ri_mlp* net, float* m, float* v, int step, float lr, const float* feat,
-                          const float* target, int64_t n, float* loss, const MlpWS& w, hipStream_t st) {
+                          const float* target, int64_t n, float* loss, float* grad, const MlpWS& w, hipStream_t st) {
     float* P = net->params;
-    RI_TRY(mlp_forward(net, feat, n, w.y, RI_MLP_FP32, w, st));
-    const int nb = (int)g1(n);
-    mse_kernel<<<nb, 256, 0, st>>>(w.y, target, n, w.dy, w.part);
+    const int rb = block_rows(n), nblk = (int)g1(n, rb);
+    if (rb == 64)
+        mlp_kernel<false, true, 2><<<nblk, 512, 0, st>>>(feat, n, net->mu, net->sigma, P, nullptr, nullptr, target,
+                                                         w.h1, w.dz2, w.part);
+    else
+        mlp_kernel<false, true, 1><<<nblk, 512, 0, st>>>(feat, n, net->mu, net->sigma, P, nullptr, nullptr, target,
+                                                         w.h1, w.dz2, w.part);
     RI_TRY(hipGetLastError());
-    sum_kernel<<<1, 64, 0, st>>>(w.part, nb, 1.0f / (float)n, loss);
-    RI_TRY(hipGetLastError());
-    float* g = w.grad;
-    const int64_t rows_per = 256;
-    const int nchunk = (int)((n + rows_per - 1) / rows_per);
-    // w3, b3
-    gw3_partial_kernel<<<nchunk, W, 0, st>>>(w.h2, w.dy, n, rows_per, w.part);
-    colsum_final_kernel<<<1, W, 0, st>>>(w.part, nchunk, W, g + RI_MLP_OFF_W3);
-    colsum_partial_kernel<<<dim3(nchunk, 1), 1, 0, st>>>(w.dy, n, 1, rows_per, w.part);
-    colsum_final_kernel<<<1, 1, 0, st>>>(w.part, nchunk, 1, g + RI_MLP_OFF_B3);
-    RI_TRY(hipGetLastError());
-    // dz2 (in z2's buffer)
-    dz2_kernel<<<g1(n * W), 256, 0, st>>>(w.dy, P + RI_MLP_OFF_W3, n, w.z2);
-    RI_TRY(hipGetLastError());
-    // g_W2 = h1^T dz2, g_b2 = colsum dz2
-    RI_TRY((gemm_f32<true, false>(W, W, (int)n, w.h1, W, w.z2, W, g + RI_MLP_OFF_W2, W, nullptr, nullptr, st)));
-    colsum_partial_kernel<<<dim3(nchunk, 1), W, 0, st>>>(w.z2, n, W, rows_per, w.part);
-    colsum_final_kernel<<<1, W, 0, st>>>(w.part, nchunk, W, g + RI_MLP_OFF_B2);
-    RI_TRY(hipGetLastError());
-    // dh1 = dz2 W2^T (into h2's buffer), dz1 = dh1 silu'(z1)
-    RI_TRY((gemm_f32<false, true>((int)n, W, W, w.z2, W, P + RI_MLP_OFF_W2, W, w.h2, W, nullptr, nullptr, st)));
-    dz1_kernel<<<g1(n * W), 256, 0, st>>>(w.z1, n, w.h2);
-    RI_TRY(hipGetLastError());
-    // g_W1 = xh^T dz1, g_b1 = colsum dz1
-    RI_TRY((gemm_f32<true, false>(NF, W, (int)n, w.xh, NF, w.h2, W, g + RI_MLP_OFF_W1, W, nullptr, nullptr, st)));
-    colsum_partial_kernel<<<dim3(nchunk, 1), W, 0, st>>>(w.h2, n, W, rows_per, w.part);
-    colsum_final_kernel<<<1, W, 0, st>>>(w.part, nchunk, W, g + RI_MLP_OFF_B1);
+    // rows of each wave: a multiple of 16, at least 64 where there are that many
+    const int64_t rows = (int64_t)nblk * rb;
+    const int64_t per = std::max<int64_t>(64, (rows / (4 * GW2_SPLITS) + 15) / 16 * 16);
+    const int splits = (int)((rows + 4 * per - 1) / (4 * per));
+    gw2_kernel<<<16 * splits, 256, 0, st>>>(w.h1, w.dz2, rows, per, w.pw2);
     RI_TRY(hipGetLastError());
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = 1.0f - powf(b1, (float)step), c2 = 1.0f - powf(b2, (float)step);
-    adam_kernel<<<g1(RI_MLP_NPARAM), 256, 0, st>>>(P, g, m, v, RI_MLP_NPARAM, lr, b1, b2, 1e-8f, c1, c2);
+    grad_adam_kernel<<<W + (PCOLS + 31) / 32, 256, 0, st>>>(w.pw2, splits, w.part, nblk, 1.0f / (float)n, P, grad, m, v,
+                                                            loss, lr, b1, b2, 1e-8f, c1, c2);
     return hipGetLastError();
 }
 
