@@ -164,23 +164,25 @@ FockWS carve_fock(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int pr
 
 // Fock build from a density matrix (no orbitals): pair weights, gamma/J
 // buffers, and the slab buffers of K = 1/2 sum_P B^P D B^P.
-constexpr int DENSITY_SLAB = 8;
 struct DensityWS {
-    double *dpair, *jpart, *gamma, *Bf, *Y;
-    int32_t* map;
-    int js, slab;
+    double *dpair, *jpart, *gamma;
+    ri::KDensity k;
+    int js;
 };
 DensityWS carve_density(Arena& a, int N, int n_aux, int64_t n_pairs) {
     DensityWS w;
-    const int64_t n2 = (int64_t)N * N;
+    const int Npad = ri::xt_ld(N);
     w.js = ri::j_split_count(n_aux);
-    w.slab = std::min(DENSITY_SLAB, n_aux);
     w.dpair = a.take<double>(std::max<int64_t>(n_pairs, 1));
     w.jpart = a.take<double>((int64_t)w.js * std::max<int64_t>(n_pairs, 1));
     w.gamma = a.take<double>(n_aux);
-    w.map = a.take<int32_t>(n2);
-    w.Bf = a.take<double>(w.slab * n2);
-    w.Y = a.take<double>(w.slab * n2);
+    w.k.slab = ri::density_slab(N, n_aux);
+    w.k.xs = carve_sparse(a, N, w.k.slab, n_pairs);
+    w.k.ks = ri::k_split_count(N, w.k.slab, N);
+    w.k.Dp = a.take<double>(ri::cpad_elems(N, N));
+    w.k.Bf = a.take<double>(ri::xt_rows(w.k.slab, N) * Npad);
+    w.k.Y = a.take<double>(ri::xt_rows(w.k.slab, N) * Npad);
+    w.k.part = a.take<double>((int64_t)w.k.ks * Npad * Npad);
     return w;
 }
 
@@ -188,7 +190,7 @@ hipError_t jk_density(const double* Bc, const int32_t* pairs, int64_t n_pairs, i
                       double* J, double* K, double* gamma, const DensityWS& w, hipStream_t st) {
     RI_TRY(ri::dpair_density(pairs, n_pairs, D, N, w.dpair, st));
     RI_TRY(ri::gamma_j_pairs(Bc, pairs, n_pairs, N, n_aux, w.dpair, gamma ? gamma : w.gamma, w.jpart, w.js, J, st));
-    return ri::k_density(Bc, pairs, n_pairs, N, n_aux, D, w.map, w.Bf, w.Y, w.slab, K, st);
+    return ri::k_density(Bc, pairs, n_pairs, N, n_aux, D, w.k, K, st);
 }
 
 struct EnergyWS {

@@ -1,60 +1,73 @@
 // Exchange from a density matrix alone (no occupied orbitals), as needed by
 // a density start of the SCF: K = 1/2 sum_P B^P D B^P, the RI form of the
-// exchange operator for any D.  Slabs of S auxiliaries at a time: full square
-// B^P unpacked from B_c, one batched GEMM Y^P = B^P D into a side-by-side
-// panel Y = [Y^1 .. Y^S], and one GEMM K += 1/2 Y [B^1; ..; B^S] whose inner
-// dimension runs over (P, sigma).
+// exchange operator for any symmetric D.  By slabs of auxiliaries:
+// (D B^P)[i][mu], rows (P, i), over each row's significant partners (the
+// exchange half-transform with D in the place of the orbitals), the full
+// square B^P unpacked as rows (P, sigma), and the lower tiles of the product
+// of the two over all rows, in the SYRK's kernel.  The products are 2 N^2 N_aux
+// times the mean number of partners plus N^3 N_aux flops, where two dense
+// GEMMs took 4 N^3 N_aux; bound by FP64 MFMA throughput.  The second GEMM had
+// only the tiles of one N x N matrix to run on.  Measured, whole build: N =
+// 400, N_aux = 1200: 39.0 -> 5.1 ms (product 2.4, D B^P 1.4, unpacking 0.9); N
+// = 130: 5.6 -> 0.38 ms.
 #include "kernels.h"
 
 #include <algorithm>
 
 namespace {
 
-// Bf[p][mu][nu] = B_c[p][pair(max, min)] or 0
+// Bf[p][mu][nu] = B_c[p][pair(mu, nu)] or 0, rows of ld
 __global__ void unpack_full_kernel(const double* __restrict__ Bc, int64_t n_pairs, const int32_t* __restrict__ map,
-                                   int N, double* __restrict__ Bf) {
-    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t n2 = (int64_t)N * N;
-    if (e >= n2) return;
-    const int p = blockIdx.y;
-    const int mu = (int)(e / N), nu = (int)(e % N);
-    const int32_t q = map[(int64_t)max(mu, nu) * N + min(mu, nu)];
-    Bf[p * n2 + e] = q >= 0 ? Bc[(int64_t)p * n_pairs + q] : 0.0;
+                                   int N, int ld, double* __restrict__ Bf) {
+    const int nu = blockIdx.x * blockDim.x + threadIdx.x, mu = blockIdx.y, p = blockIdx.z;
+    if (nu >= ld) return;
+    const int32_t q = nu < N ? map[(int64_t)mu * N + nu] : -1;
+    Bf[((int64_t)p * N + mu) * ld + nu] = q >= 0 ? Bc[(int64_t)p * n_pairs + q] : 0.0;
 }
 
-// K <- (K + K^T) / 2
-__global__ void symmetrize_kernel(double* K, int N) {
+// Dp = (D + D^T) / 2, zero-padded to [rows][ld]
+__global__ void pad_symmetric_kernel(const double* __restrict__ D, int N, int rows, int ld, double* __restrict__ Dp) {
     const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (e >= (int64_t)N * N) return;
-    const int i = (int)(e / N), j = (int)(e % N);
-    if (j >= i) return;
-    const double v = 0.5 * (K[(int64_t)i * N + j] + K[(int64_t)j * N + i]);
-    K[(int64_t)i * N + j] = v;
-    K[(int64_t)j * N + i] = v;
+    if (e >= (int64_t)rows * ld) return;
+    const int r = (int)(e / ld), c = (int)(e % ld);
+    Dp[e] = (r < N && c < N) ? 0.5 * (D[(int64_t)r * N + c] + D[(int64_t)c * N + r]) : 0.0;
 }
 
 }  // namespace
 
 namespace ri {
 
+// Auxiliaries a slab: whole blocks of 64, as many as keep the slab's B^P and
+// D B^P at 512 MiB each, so that a slab's launches fill the chip at small N; a
+// quarter of a block where 64 would take more than 16 GiB (N over 5700).
+int density_slab(int N, int n_aux) {
+    const int64_t per = (int64_t)64 * N * xt_ld(N) * 8;
+    if (per > (int64_t(1) << 34)) return std::min(16, n_aux);
+    const int64_t want = std::max<int64_t>(1, (int64_t(1) << 29) / per) * 64;
+    return (int)std::min<int64_t>({want, n_aux, 32768});   // a grid dimension takes 65535
+}
+
 hipError_t k_density(const double* Bc, const int32_t* pairs, int64_t n_pairs, int N, int n_aux, const double* D,
-                     int32_t* map, double* Bf, double* Y, int S, double* K, hipStream_t st) {
-    const int64_t n2 = (int64_t)N * N;
-    if (n_pairs == 0) return fill(K, 0.0, n2, st);
-    RI_TRY(pair_map(pairs, n_pairs, N, map, st));
-    for (int P0 = 0; P0 < n_aux; P0 += S) {
-        const int s = std::min(S, n_aux - P0);
-        unpack_full_kernel<<<dim3((unsigned)((n2 + 255) / 256), s), 256, 0, st>>>(Bc + (int64_t)P0 * n_pairs, n_pairs,
-                                                                                  map, N, Bf);
+                     const KDensity& w, double* K, hipStream_t st) {
+    if (n_pairs == 0) return fill(K, 0.0, (int64_t)N * N, st);
+    const int ld = xt_ld(N), cld = cpad_ld(N), rows = n_tiles_1d(N) * 64;
+    RI_TRY(xs_lists(w.xs, pairs, n_pairs, N, st));
+    pad_symmetric_kernel<<<(unsigned)(((int64_t)rows * cld + 255) / 256), 256, 0, st>>>(D, N, rows, cld, w.Dp);
+    RI_TRY(hipGetLastError());
+    int used = 0;
+    for (int P0 = 0; P0 < n_aux; P0 += w.slab) {
+        const int s = std::min(w.slab, n_aux - P0);
+        const double* b = Bc + (int64_t)P0 * n_pairs;
+        RI_TRY(xs_rows(w.xs, b, n_pairs, s, st));
+        RI_TRY(xs_run(w.xs, N, s, N, w.Dp, w.Y, st));
+        unpack_full_kernel<<<dim3((ld + 255) / 256, N, s), 256, 0, st>>>(b, n_pairs, w.xs.map, N, ld, w.Bf);
         RI_TRY(hipGetLastError());
-        // Y[:, p N + sigma] = (B^p D)[:, sigma]
-        RI_TRY(gemm_f64(false, false, N, N, N, 1.0, Bf, N, n2, D, N, 0, 0.0, Y, (int64_t)S * N, N, s, 0, 0, st));
-        // K (+)= 1/2 Y [B^1; ..; B^s]
-        RI_TRY(gemm_f64(false, false, N, N, s * N, 0.5, Y, (int64_t)S * N, 0, Bf, N, 0, P0 == 0 ? 0.0 : 1.0, K, N, 0, 1,
-                        0, 0, st));
+        // every slab has the same number of splits, so that each adds to what the first wrote
+        int u = 0;
+        RI_TRY(k_product(w.Bf, w.Y, (int64_t)s * N, N, w.part, P0 == 0 ? w.ks : used, P0 > 0, &u, st));
+        used = std::max(used, u);
     }
-    symmetrize_kernel<<<(unsigned)((n2 + 255) / 256), 256, 0, st>>>(K, N);
-    return hipGetLastError();
+    return kreduce(w.part, used, N, 0.5, K, st);
 }
 
 }  // namespace ri

@@ -564,9 +564,13 @@ __global__ __launch_bounds__(256, 2) void syrk_lds_f32_kernel(const float* __res
 // the last real row, so split ends and the pipeline's look-ahead loads stay
 // in bounds and contribute nothing.
 
-template <int S>
-__device__ __forceinline__ void syrk_body_f64(int z, int t, const double* __restrict__ X, int N, int Npad,
-                                              int64_t rows_pad, int64_t chunk, double* __restrict__ part) {
+// Y: the second factor of K_part = sum_r X[r][m] Y[r][n], X itself for the
+// SYRK; any Y that makes the product symmetric will do.  ACC: part is added to.
+
+template <int S, bool ACC = false>
+__device__ __forceinline__ void syrk_body_f64(int z, int t, const double* __restrict__ X,
+                                              const double* __restrict__ Y, int N, int Npad, int64_t rows_pad,
+                                              int64_t chunk, double* __restrict__ part) {
     constexpr int LDR = 128 + 16;                  // LDS row stride (doubles)
     __shared__ double As[S][16 * LDR];
     __shared__ double Bs[S][16 * LDR];
@@ -591,7 +595,7 @@ __device__ __forceinline__ void syrk_body_f64(int z, int t, const double* __rest
     const __amdgpu_buffer_rsrc_t rsa =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(X + r0 * Npad + m0), (short)0, nrec, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsb =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(X + r0 * Npad + n0), (short)0, nrec, 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(Y + r0 * Npad + n0), (short)0, nrec, 0x00020000);
     const int vrow = ((4 * wave) * Npad + 2 * lane) * 8;
     const int last = (int)(r1 - r0);
 #endif
@@ -616,7 +620,7 @@ __device__ __forceinline__ void syrk_body_f64(int z, int t, const double* __rest
         for (int q = 0; q < 4; ++q) {
             const int row = 4 * wave + q;
             const double* ga = X + (rb + row) * Npad + m0 + 2 * lane;
-            const double* gb = X + (rb + row) * Npad + n0 + 2 * lane;
+            const double* gb = Y + (rb + row) * Npad + n0 + 2 * lane;
             __builtin_amdgcn_global_load_lds((const void*)ga, (lds_void_t)(&As[buf][row * LDR]), 16, 0, 0);
             __builtin_amdgcn_global_load_lds((const void*)gb, (lds_void_t)(&Bs[buf][row * LDR]), 16, 0, 0);
         }
@@ -662,8 +666,10 @@ __device__ __forceinline__ void syrk_body_f64(int z, int t, const double* __rest
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                out[(int64_t)(m0 + wm + 16 * i + 4 * r + lk) * Npad + n0 + wn + 16 * j + li] = acc[i][j][r];
+            for (int r = 0; r < 4; ++r) {
+                double* o = out + (int64_t)(m0 + wm + 16 * i + 4 * r + lk) * Npad + n0 + wn + 16 * j + li;
+                *o = ACC ? *o + acc[i][j][r] : acc[i][j][r];
+            }
 }
 
 template <int S>
@@ -672,14 +678,38 @@ __global__ __launch_bounds__(256, 2) void syrk_lds_kernel(const double* __restri
                                                           double* __restrict__ part) {
     const int nlow = ntile * (ntile + 1) / 2;
     const int L = xcd_remap(blockIdx.x, gridDim.x);
-    syrk_body_f64<S>(L / nlow, L % nlow, X, N, Npad, rows_pad, chunk, part);
+    syrk_body_f64<S>(L / nlow, L % nlow, X, X, N, Npad, rows_pad, chunk, part);
 }
 
-__global__ void kreduce_kernel(const double* part, int n_split, int Npad, int N, double* K) {
+template <bool ACC>
+__global__ __launch_bounds__(256, 2) void product_lds_kernel(const double* __restrict__ X, const double* __restrict__ Y,
+                                                             int N, int Npad, int64_t rows_pad, int64_t chunk,
+                                                             int ntile, double* __restrict__ part) {
+    const int nlow = ntile * (ntile + 1) / 2;
+    const int L = xcd_remap(blockIdx.x, gridDim.x);
+    syrk_body_f64<2, ACC>(L / nlow, L % nlow, X, Y, N, Npad, rows_pad, chunk, part);
+}
+
+// K = scale times the sum of the splits in order, 8 loads at a time: the
+// launch has few threads per CU at small N, so a load at a time left each
+// waiting out every split's latency (N = 370, 64 splits: 20 us).
+__global__ void kreduce_kernel(const double* __restrict__ part, int n_split, int Npad, int N, double scale,
+                               double* __restrict__ K) {
     int nu = blockIdx.x * blockDim.x + threadIdx.x, mu = blockIdx.y;
     if (nu > mu || mu >= N) return;
+    const double* p = part + (int64_t)mu * Npad + nu;
+    const int64_t st = (int64_t)Npad * Npad;
     double s = 0.0;
-    for (int k = 0; k < n_split; ++k) s += part[((int64_t)k * Npad + mu) * Npad + nu];
+    int k = 0;
+    for (; k + 8 <= n_split; k += 8) {
+        double v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = p[(k + j) * st];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += v[j];
+    }
+    for (; k < n_split; ++k) s += p[k * st];
+    s *= scale;
     K[(int64_t)mu * N + nu] = s;
     K[(int64_t)nu * N + mu] = s;
 }
@@ -879,8 +909,25 @@ hipError_t k_syrk(const void* Xt, int prec, int N, int n_aux, int n_occ, double*
         syrk_lds_f32_kernel<4><<<nlow * used, 256, 0, st>>>(x, N, Npad, rows_pad, chunk, t128, part);
     }
     RI_TRY(hipGetLastError());
-    dim3 grid((N + 255) / 256, N);
-    kreduce_kernel<<<grid, 256, 0, st>>>(part, used, Npad, N, K);
+    return kreduce(part, used, N, 1.0, K, st);
+}
+
+hipError_t kreduce(const double* part, int n_split, int N, double scale, double* K, hipStream_t st) {
+    kreduce_kernel<<<dim3((N + 63) / 64, N), 64, 0, st>>>(part, n_split, xt_ld(N), N, scale, K);
+    return hipGetLastError();
+}
+
+hipError_t k_product(double* X, double* Y, int64_t rows, int N, double* part, int n_split, bool add, int* used,
+                     hipStream_t st) {
+    const int Npad = xt_ld(N), t128 = Npad / 128;
+    const int64_t rows_pad = (rows + 15) / 16 * 16;
+    const int64_t chunk = ((rows_pad + n_split - 1) / n_split + 15) / 16 * 16;
+    *used = (int)((rows_pad + chunk - 1) / chunk);
+    RI_TRY(fill(X + rows * Npad, 0.0, (rows_pad + 16 - rows) * Npad, st));
+    RI_TRY(fill(Y + rows * Npad, 0.0, (rows_pad + 16 - rows) * Npad, st));
+    const unsigned blocks = (unsigned)(t128 * (t128 + 1) / 2 * *used);
+    if (add) product_lds_kernel<true><<<blocks, 256, 0, st>>>(X, Y, N, Npad, rows_pad, chunk, t128, part);
+    else product_lds_kernel<false><<<blocks, 256, 0, st>>>(X, Y, N, Npad, rows_pad, chunk, t128, part);
     return hipGetLastError();
 }
 
@@ -970,7 +1017,7 @@ __global__ __launch_bounds__(256, 2) void syrk_b_kernel(const ri::MolDesc* d, co
     if (!m.state[0]) return;
     const int t128 = m.npad / 128, nlow = t128 * (t128 + 1) / 2;
     if (PREC == RI_FP64)
-        syrk_body_f64<2>(loc / nlow, loc % nlow, (const double*)m.Xt, m.N, m.npad, m.rows_pad, m.chunk, m.part);
+        syrk_body_f64<2>(loc / nlow, loc % nlow, (const double*)m.Xt, (const double*)m.Xt, m.N, m.npad, m.rows_pad, m.chunk, m.part);
     else
         syrk_body_f32<4>(loc / nlow, loc % nlow, (const float*)m.Xt, m.N, m.npad, m.rows_pad, m.chunk, m.part);
 }

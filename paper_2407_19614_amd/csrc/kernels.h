@@ -73,6 +73,11 @@ hipError_t xs_prepare(const XSparse& w, const double* Bc, const int32_t* pairs, 
                       hipStream_t st);
 hipError_t xs_transform(const XSparse& w, int N, int n_aux, int n_occ, const double* C, double* Cp, double* Xt,
                         hipStream_t st);
+// The parts of the two calls above: the partner lists, the transposed copy of the
+// rows P0 .. P0 + np of B_c (BcT holds np auxiliaries then), and X^T from a padded C.
+hipError_t xs_lists(const XSparse& w, const int32_t* pairs, int64_t n_pairs, int N, hipStream_t st);
+hipError_t xs_rows(const XSparse& w, const double* Bc, int64_t n_pairs, int np, hipStream_t st);
+hipError_t xs_run(const XSparse& w, int N, int n_aux, int n_occ, const double* Cp, double* Xt, hipStream_t st);
 // gamma and (J != nullptr) J from the pair weights dpair
 hipError_t xs_gamma_j(const XSparse& w, int N, int n_aux, const double* dpair, const int32_t* pairs, double* gamma,
                       double* J, hipStream_t st);
@@ -83,6 +88,12 @@ hipError_t dpair_orbitals(const int32_t* pairs, int64_t n_pairs, int n_occ, cons
 hipError_t k_syrk(const void* Xt, int prec, int N, int n_aux, int n_occ, double* part, int n_split,
                   double* K, hipStream_t st);
 int k_split_count(int N, int n_aux, int n_occ);
+// K[m][n] = K[n][m] = scale * sum over splits of part, m >= n
+hipError_t kreduce(const double* part, int n_split, int N, double scale, double* K, hipStream_t st);
+// Lower 128-tiles of sum_r X[r][m] Y[r][n] (a product known to be symmetric) over `rows` rows of
+// stride xt_ld(N), in n_split parts (*used of them written, or added to); X and Y hold 32 rows more.
+hipError_t k_product(double* X, double* Y, int64_t rows, int N, double* part, int n_split, bool add, int* used,
+                     hipStream_t st);
 int64_t xt_rows(int n_aux, int n_occ);
 int xt_ld(int N);
 // gamma and J from the compressed FP64 tensor.
@@ -94,10 +105,6 @@ hipError_t gamma_j_pairs(const double* Bc, const int32_t* pairs, int64_t n_pairs
                          int cap = 0);
 // pair weights of a density matrix D [N][N] (symmetrised)
 hipError_t dpair_density(const int32_t* pairs, int64_t n_pairs, const double* D, int N, double* dpair, hipStream_t st);
-// K = 1/2 sum_P B^P D B^P from B_c, slab of S auxiliaries at a time (workspace map [N*N],
-// Bf [S][N][N], Y [N][S*N]); K symmetrised.
-hipError_t k_density(const double* Bc, const int32_t* pairs, int64_t n_pairs, int N, int n_aux, const double* D,
-                     int32_t* map, double* Bf, double* Y, int S, double* K, hipStream_t st);
 hipError_t gamma_j(const double* Bc, const int32_t* pairs, int64_t n_pairs, int N, int n_aux,
                    int n_occ, const double* C, double* dpair, double* gamma, double* jpart,
                    int n_jsplit, double* J, hipStream_t st, int cap = 0);
@@ -106,6 +113,15 @@ hipError_t gamma_j(const double* Bc, const int32_t* pairs, int64_t n_pairs, int 
 // gamma / J the critical path and 256 slowed X on every CU).
 constexpr int GJ_SIDE_CAP = 128;
 constexpr int64_t GJ_SIDE_MIN = 100000000;
+// K = 1/2 sum_P B^P D B^P from B_c over the significant pairs (density.hip)
+struct KDensity {
+    XSparse xs;                       // BcT: one slab of auxiliaries
+    double *Dp, *Bf, *Y, *part;       // padded D; one slab of full B^P and of D B^P, rows (P, sigma); K partials
+    int slab, ks;
+};
+int density_slab(int N, int n_aux);
+hipError_t k_density(const double* Bc, const int32_t* pairs, int64_t n_pairs, int N, int n_aux, const double* D,
+                     const KDensity& w, double* K, hipStream_t st);
 int j_split_count(int n_aux);
 
 }  // namespace ri

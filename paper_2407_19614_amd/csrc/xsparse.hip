@@ -187,7 +187,7 @@ __global__ __launch_bounds__(64 * WV, 2) void xs_kernel(const double* __restrict
         for (int k = 0; k < 4; ++k) {
             const int p = p0 + 4 * k;
             if (row < rows && i < n_occ && P0 + PT * p + t < n_aux && in_mu)
-                out[(uint32_t)(PT * p * n_occ + is * row) * (uint32_t)Npad + u] = Ls[buf][u * LS + row * 17 + p];
+                out[(int64_t)(PT * p * n_occ + is * row) * Npad + u] = Ls[buf][u * LS + row * 17 + p];
         }
     };
     int buf = 0;
@@ -309,23 +309,30 @@ __global__ __launch_bounds__(256) void j_rows_kernel(const double* __restrict__ 
 namespace ri {
 
 bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs) {
-    return n_pairs > 0 && (double)(2 * n_pairs - N) <= 0.6 * (double)N * N &&
-           xt_rows(n_aux, n_occ) * xt_ld(N) * 8 > (int64_t)RI_NOALLOC_SCRATCH_BYTES &&
-           (int64_t)xs_ldp(n_aux) * 8 <= INT32_MAX;
+    return n_pairs > 0 && (n_pairs + 1) * xs_ldp(n_aux) <= ((int64_t)1 << 33) && (double)(2 * n_pairs - N) <= 0.6 * (double)N * N &&
+           xt_rows(n_aux, n_occ) * xt_ld(N) * 8 > (int64_t)RI_NOALLOC_SCRATCH_BYTES;
 }
 
 int xs_ldp(int n_aux) { return (n_aux + 63) / 64 * 64; }
 int xs_lmax(int N) { return (N + 63) / 64 * 64 + 128; }
 
-hipError_t xs_prepare(const XSparse& w, const double* Bc, const int32_t* pairs, int64_t n_pairs, int N, int n_aux,
-                      hipStream_t st) {
+hipError_t xs_lists(const XSparse& w, const int32_t* pairs, int64_t n_pairs, int N, hipStream_t st) {
     RI_TRY(fill_i32(w.map, -1, (int64_t)N * N, st));
     pair_map_sym_kernel<<<(unsigned)((n_pairs + 255) / 256), 256, 0, st>>>(pairs, n_pairs, N, w.map);
     RI_TRY(hipGetLastError());
     row_list_kernel<<<(N + 3) / 4, 256, 0, st>>>(w.map, N, (int)n_pairs, w.lmax, w.list, w.cnt);
-    RI_TRY(hipGetLastError());
-    bc_transpose_kernel<<<dim3((unsigned)(n_pairs / 64 + 1), w.ldp / 64), 256, 0, st>>>(Bc, n_aux, n_pairs, w.BcT);
     return hipGetLastError();
+}
+
+hipError_t xs_rows(const XSparse& w, const double* Bc, int64_t n_pairs, int np, hipStream_t st) {
+    bc_transpose_kernel<<<dim3((unsigned)(n_pairs / 64 + 1), xs_ldp(np) / 64), 256, 0, st>>>(Bc, np, n_pairs, w.BcT);
+    return hipGetLastError();
+}
+
+hipError_t xs_prepare(const XSparse& w, const double* Bc, const int32_t* pairs, int64_t n_pairs, int N, int n_aux,
+                      hipStream_t st) {
+    RI_TRY(xs_lists(w, pairs, n_pairs, N, st));
+    return xs_rows(w, Bc, n_pairs, n_aux, st);
 }
 
 int64_t xs_gpart(int n_aux, int64_t n_pairs) { return ((n_pairs + GSTRIP - 1) / GSTRIP + 1) * xs_ldp(n_aux); }
@@ -348,8 +355,12 @@ hipError_t xs_gamma_j(const XSparse& w, int N, int n_aux, const double* dpair, c
 
 hipError_t xs_transform(const XSparse& w, int N, int n_aux, int n_occ, const double* C, double* Cp, double* Xt,
                         hipStream_t st) {
-    const int cld = cpad_ld(n_occ), Npad = xt_ld(N);
     RI_TRY(cpad(C, N, n_occ, Cp, st));
+    return xs_run(w, N, n_aux, n_occ, Cp, Xt, st);
+}
+
+hipError_t xs_run(const XSparse& w, int N, int n_aux, int n_occ, const double* Cp, double* Xt, hipStream_t st) {
+    const int cld = cpad_ld(n_occ), Npad = xt_ld(N);
     // whole chunks of 128 occupied columns, then what is left: whole 16-row
     // tiles plus, when the last tile would hold 12 rows or fewer, 4-row quads
     const int full = n_occ / 128, left = n_occ % 128;
