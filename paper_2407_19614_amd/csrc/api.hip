@@ -99,7 +99,7 @@ SlabWS carve_slab(Arena& a, int N, int n_aux, int prec, bool comp) {
     return w;
 }
 
-ri::XSparse carve_sparse(Arena& a, int N, int n_aux, int64_t n_pairs) {
+ri::XSparse carve_sparse(Arena& a, int N, int n_aux, int64_t n_pairs, bool f32 = false) {
     ri::XSparse w;
     w.ldp = ri::xs_ldp(n_aux);
     w.lmax = ri::xs_lmax(N);
@@ -107,8 +107,9 @@ ri::XSparse carve_sparse(Arena& a, int N, int n_aux, int64_t n_pairs) {
     w.list = a.take<int2>((int64_t)N * w.lmax);
     w.cnt = a.take<int>(N);
     w.n_pairs = n_pairs;
-    w.BcT = a.take<double>((n_pairs + 1) * w.ldp);
-    w.gpart = a.take<double>(ri::xs_gpart(n_aux, n_pairs));
+    if (f32) w.BcT32 = a.take<float>((n_pairs + 1) * w.ldp);
+    else w.BcT = a.take<double>((n_pairs + 1) * w.ldp);
+    if (!f32) w.gpart = a.take<double>(ri::xs_gpart(n_aux, n_pairs));
     return w;
 }
 
@@ -119,7 +120,8 @@ ri::XSparse carve_sparse(Arena& a, int N, int n_aux, int64_t n_pairs) {
 hipError_t x_any(const void* B, int prec, int N, int n_aux, int n_occ, const double* C, double* Cp, void* Xt,
                  const double* Bc, const int32_t* pairs, int64_t n_pairs, const SlabWS& sw, const ri::XSparse& xs,
                  hipStream_t st) {
-    if (xs.BcT && prec == RI_FP64) return ri::xs_transform(xs, N, n_aux, n_occ, C, Cp, (double*)Xt, st);
+    if (xs.on() && prec == RI_FP32) return ri::xs_transform32(xs, N, n_aux, n_occ, C, (float*)Cp, (float*)Xt, st);
+    if (xs.on()) return ri::xs_transform(xs, N, n_aux, n_occ, C, Cp, (double*)Xt, st);
     if (B) return ri::x_transform(B, prec, N, n_aux, n_occ, C, Cp, Xt, st);
     if (!sw.Bs) return hipErrorInvalidValue;
     RI_TRY(ri::pair_map(pairs, n_pairs, N, sw.map, st));
@@ -133,11 +135,12 @@ hipError_t x_any(const void* B, int prec, int N, int n_aux, int n_occ, const dou
 }
 
 struct FockWS { void* Xt; double* part; double* dpair; double* jpart; double* gamma; double* Cp; int ks, js; SlabWS sw; ri::XSparse xs; };
-// pairs_x: the exchange may run over the partner lists (not for FP32-stored B in the FP64 layout)
+// wide: FP32-stored B in the FP64 layout (FP32 iterations and an FP64 build at the end)
 FockWS carve_fock(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, bool comp = false,
-                  bool pairs_x = true) {
+                  bool wide = false) {
     FockWS w;
-    if (prec == RI_FP64 && pairs_x && ri::xs_wanted(N, n_aux, n_occ, n_pairs)) w.xs = carve_sparse(a, N, n_aux, n_pairs);
+    const int xprec = wide ? (int)RI_FP32 : prec;
+    if (ri::xs_wanted(N, n_aux, n_occ, n_pairs, xprec)) w.xs = carve_sparse(a, N, n_aux, n_pairs, xprec == RI_FP32);
     w.sw = carve_slab(a, N, n_aux, prec, comp);   // the compressed form's size contract holds for either form of X
     const int Npad = ri::xt_ld(N);
     w.js = ri::j_split_count(n_aux);
@@ -203,7 +206,7 @@ struct EnergyWS {
     DensityWS dens;
 };
 EnergyWS carve_energy(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, int diis_n,
-                      bool comp = false, bool fin_slab = false, bool pairs_x = true) {
+                      bool comp = false, bool fin_slab = false, bool wide = false) {
     EnergyWS w;
     const int64_t n2 = (int64_t)N * N;
     double** mats[] = {&w.S, &w.H, &w.Ls, &w.LinvS, &w.J, &w.K, &w.F, &w.D, &w.T1, &w.T2, &w.E, &w.Fx, &w.X, &w.X2};
@@ -228,7 +231,7 @@ EnergyWS carve_energy(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, in
     w.tpart = a.take<double>(4 * (int64_t)ri::tc2f_tiles(N));   // purification partial sums, two parities
     w.bad = a.take<int>(2);
     w.tst = a.take<int>(16);                                    // purification state, two parities
-    w.fock = carve_fock(a, N, n_aux, n_occ, n_pairs, prec, comp, pairs_x);
+    w.fock = carve_fock(a, N, n_aux, n_occ, n_pairs, prec, comp, wide);
     w.fin = fin_slab ? carve_fock(a, N, n_aux, n_occ, n_pairs, RI_FP64, true) : FockWS{};
     w.dens = carve_density(a, N, n_aux, n_pairs);
     return w;
@@ -245,7 +248,7 @@ struct GradWS { double *D, *W, *T1, *dpair, *gamma, *c, *Bij, *Xi, *Zx, *part, *
 GradWS carve_grad(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int n_centres, int prec,
                   bool comp = false) {
     GradWS w;
-    if (prec == RI_FP64 && ri::xs_wanted(N, n_aux, n_occ, n_pairs)) w.xs = carve_sparse(a, N, n_aux, n_pairs);
+    if (ri::xs_wanted(N, n_aux, n_occ, n_pairs, prec)) w.xs = carve_sparse(a, N, n_aux, n_pairs, prec == RI_FP32);
     w.sw = carve_slab(a, N, n_aux, prec, comp);   // the compressed form's size contract holds for either form of X
     const int Npad = ri::xt_ld(N);
     const int64_t n2 = (int64_t)N * N, o2 = (int64_t)n_occ * n_occ;
@@ -340,7 +343,7 @@ int32_t fock_impl(int N, int n_aux, int n_occ, const void* B, int prec, const do
         HIPC(ri::x_transform_bf16(B, prec, N, n_aux, n_occ, C, w.Cp, w.Xt, st));
         if (ev) HIPC(hipEventRecord(ev[2], st));
     }
-    const bool by_pairs = w.xs.BcT && prec == RI_FP64;
+    const bool by_pairs = w.xs.on();
     if (by_pairs && !prepared) HIPC(ri::xs_prepare(w.xs, Bc, pairs, n_pairs, N, n_aux, st));
     const bool overlap = side && fk.open(st);
     if (ev && !overlap) {
@@ -352,8 +355,8 @@ int32_t fock_impl(int N, int n_aux, int n_occ, const void* B, int prec, const do
     // that the X kernel's workgroups are not held back behind thousands of
     // theirs; beside the split-BF16 SYRK, which is shorter than capped gamma/J
     // would be, they keep the full grid
-    const bool capped = overlap && !bf && (int64_t)n_aux * n_pairs >= ri::GJ_SIDE_MIN;
-    if (by_pairs) {
+    const bool capped = overlap && !bf && !by_pairs && (int64_t)n_aux * n_pairs >= ri::GJ_SIDE_MIN;
+    if (w.xs.BcT) {
         HIPC(ri::dpair_orbitals(pairs, n_pairs, n_occ, C, w.dpair, ss));
         HIPC(ri::xs_gamma_j(w.xs, N, n_aux, w.dpair, pairs, g, J, ss));
     } else {
@@ -491,7 +494,7 @@ size_t ri_workspace_bytes(int32_t op, int32_t N, int32_t n_aux, int32_t n_occ, i
         case RI_OP_FOCK: carve_fock(a, N, n_aux, n_occ, n_pairs, prec, pp.comp); break;
         case RI_OP_ENERGY:
             carve_energy(a, N, n_aux, n_occ, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp),
-                         pp.base == RI_FP64);
+                         pp.fin && pp.base == RI_FP32);
             break;
         case RI_OP_GRADIENT:
             carve_grad(a, N, n_aux, n_occ, n_pairs, 2048, is_bf16(prec) ? RI_FP64 : prec, pp.comp || is_bf16(prec));
@@ -705,7 +708,7 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
     const int64_t n2 = (int64_t)N * N;
     Arena a{(char*)ws, ws_bytes, 0, false};
     EnergyWS w = carve_energy(a, N, na, no, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp),
-                         pp.base == RI_FP64);
+                         pp.fin && pp.base == RI_FP32);
     if (!a.ok()) return RI_E_WORKSPACE;
     std::memset(res, 0, sizeof(*res));
 
@@ -741,7 +744,7 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
         HIPC(ri::gemm_f64(true, false, N, no, N, 1.0, w.Ls, N, 0, C_occ, no, 0, 0.0, w.Cp, no, 0, 1, 2, 0, st));
     }
 
-    if (w.fock.xs.BcT) HIPC(ri::xs_prepare(w.fock.xs, Bc, pairs, n_pairs, N, na, st));
+    if (w.fock.xs.on()) HIPC(ri::xs_prepare(w.fock.xs, Bc, pairs, n_pairs, N, na, st));
     std::vector<int> slots;
     HIPC(ri::fill(w.Bfull, 0.0, 64, st));   // DIIS inner products <e_i, e_j>, indexed by ring slot
     int pushes = 0;
@@ -808,11 +811,14 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
         // hold B only to 2^-17 or 2^-25) from the FP64 B_c unpacked slab by
         // slab; the energy from the same D, h and J
         if (is_bf16(prec)) {
-            if (w.fin.xs.BcT) HIPC(ri::xs_prepare(w.fin.xs, Bc, pairs, n_pairs, N, na, st));
+            if (w.fin.xs.on()) HIPC(ri::xs_prepare(w.fin.xs, Bc, pairs, n_pairs, N, na, st));
             HIPC(x_any(nullptr, RI_FP64, N, na, no, C_occ, w.fin.Cp, w.fin.Xt, Bc, pairs, n_pairs, w.fin.sw, w.fin.xs, st));
             HIPC(ri::k_syrk(w.fin.Xt, RI_FP64, N, na, no, w.fin.part, w.fin.ks, w.K, st));
         } else {
-            HIPC(ri::x_transform(B, ri::X_F64_B32, N, na, no, C_occ, w.fock.Cp, w.fock.Xt, st));
+            // either form widens the same FP32-rounded values
+            HIPC(w.fock.xs.on()
+                     ? ri::xs_transform(w.fock.xs, N, na, no, C_occ, w.fock.Cp, (double*)w.fock.Xt, st)
+                     : ri::x_transform(B, ri::X_F64_B32, N, na, no, C_occ, w.fock.Cp, w.fock.Xt, st));
             HIPC(ri::k_syrk(w.fock.Xt, RI_FP64, N, na, no, w.fock.part, w.fock.ks, w.K, st));
         }
         HIPC(ri::energy_terms(w.D, w.H, w.J, w.K, n2, w.scal + 8, w.scal, w.red, st));
@@ -866,11 +872,11 @@ int32_t ri_gradient(const ri_system* sys, const int32_t* pairs, int64_t n_pairs,
     HIPC(ri::gemm_f64(true, false, na, 1, na, 1.0, Linv, na, 0, w.gamma, 1, 0, 0.0, w.c, 1, 0, 1, 2, 0, ss));
     HIPC(ri::grad_one_electron(sys, w.D, w.W, w.part, ss));
     // B_ij^P = (C^T B^P C)_ij from X^P = B^P C
+    if (w.xs.on()) HIPC(ri::xs_prepare(w.xs, Bc, pairs, n_pairs, N, na, st));
     if (prec == RI_FP32) {
         HIPC(x_any(B, prec, N, na, no, C, w.Cp, w.Xt32, Bc, pairs, n_pairs, w.sw, w.xs, st));
         HIPC(ri::widen(w.Xt32, (double*)w.Xt, (int64_t)na * no * Npad, st));
     } else {
-        if (w.xs.BcT) HIPC(ri::xs_prepare(w.xs, Bc, pairs, n_pairs, N, na, st));
         HIPC(x_any(B, prec, N, na, no, C, w.Cp, w.Xt, Bc, pairs, n_pairs, w.sw, w.xs, st));
     }
     // one GEMM over all (P, i) rows: the rows of X^T are stacked P-major, as B_ij's

@@ -404,6 +404,7 @@ struct Plan {
     MolDesc* d = nullptr;
     Table n2, n2s, rows, pairs, aux, syrk, tail, cq, x[33];   // x[xs], xs = 4 * tiles + quads
     Table x64[33];                                        // FP64 shapes of the final exchange (fin)
+    Table xp[33], xp64[33];                               // the same for molecules with partner lists
     // members on 64 x 64 tiles in t, on 128 x 128 tiles in t128
     struct G { ri::GemmDesc* d = nullptr; Table t, t128; bool ta = false, tb = false; };
     G g_lfx, g_t2, g_x2, g_y, g_mo, g_cp, g_c, g_d, g_fd, g_fds;
@@ -456,6 +457,8 @@ hipError_t iteration_b(const Plan& p, int max_iter, hipStream_t st) {
     HC(ri::cpad_b(d, p.cq.prefix, nm, p.cq.total, p.prec, st));
     for (int xs = 1; xs <= 32; ++xs)
         if (p.x[xs].total > 0) HC(ri::x_transform_b(d, p.x[xs].prefix, nm, p.x[xs].total, xs, p.prec, st));
+    for (int xs = 1; xs <= 32; ++xs)
+        if (p.xp[xs].total > 0) HC(ri::xs_transform_b(d, p.xp[xs].prefix, nm, p.xp[xs].total, xs, p.prec, st));
     HC(ri::syrk_b(d, p.syrk.prefix, nm, p.syrk.total, p.prec, st));
     HC(ri::kreduce_b(d, p.rows.prefix, nm, p.rows.total, st));
     // F, D, energy, error, convergence
@@ -491,6 +494,9 @@ hipError_t final_fp64_b(const Plan& p, hipStream_t st) {
     for (int xs = 1; xs <= 32; ++xs)
         if (p.x64[xs].total > 0)
             HC(ri::x_transform_b(d, p.x64[xs].prefix, nm, p.x64[xs].total, xs, ri::X_F64_B32, st));
+    for (int xs = 1; xs <= 32; ++xs)
+        if (p.xp64[xs].total > 0)
+            HC(ri::xs_transform_b(d, p.xp64[xs].prefix, nm, p.xp64[xs].total, xs, ri::X_F64_B32, st));
     HC(ri::syrk_b(d, p.syrk.prefix, nm, p.syrk.total, RI_FP64, st));
     HC(ri::kreduce_b(d, p.rows.prefix, nm, p.rows.total, st));
     energy_final_b<<<nm, 256, 0, st>>>(d, nm);
@@ -512,6 +518,11 @@ struct Carver {
         return base ? (T*)(base + o) : nullptr;
     }
 };
+
+// Smallest N whose exchange runs over the partner lists.  At N = 150 half of the
+// matrix is pairs and a row's list is some 20 steps of 4; below, the dense
+// kernel's N / 16 slices are as few and its operands need no gathers.
+constexpr int BATCH_SP_MIN = 150;
 
 int k_split_small(int64_t rows) { return (int)std::max<int64_t>(1, std::min<int64_t>(8, rows / 16384)); }
 
@@ -604,6 +615,15 @@ static int32_t batch_layout(int32_t n_mol, const ri_system* sys, const ri_batch_
             m.dF[k] = k < diis_n ? cv.take<double>(n2) : nullptr;
             m.dE[k] = k < diis_n ? cv.take<double>(n2) : nullptr;
         }
+        // over the partner lists where the pairs are few enough and the molecule large
+        // enough that a row's list fills whole steps
+        m.sp = N >= BATCH_SP_MIN && ri::xs_sparse(N, na, m.n_pairs);
+        m.lmax = ri::xs_lmax(N);
+        if (m.sp) {
+            m.plist = cv.take<int2>((int64_t)N * m.lmax);
+            m.pcnt = cv.take<int>(N);
+            m.BcT = cv.take<char>((m.n_pairs + 1) * ri::xs_ldp(na) * (prec == RI_FP64 ? 8 : 4));
+        }
         m.Y = cv.take<double>((int64_t)N * no);
         m.Cp = cv.take<double>((int64_t)N * no);
         // padded C for the X launch: FP64 [64 nt][64] doubles, FP32 the same shape in floats
@@ -647,14 +667,20 @@ static int32_t batch_layout(int32_t n_mol, const ri_system* sys, const ri_batch_
     mk(c, p.cq);
     for (int xs = 1; xs <= 32; ++xs) {
         for (int i = 0; i < n_mol; ++i)
-            c[i] = hp.mols[i].xs == xs ? hp.mols[i].nt * ((hp.mols[i].n_aux + 1) / 2) : 0;
+            c[i] = hp.mols[i].xs == xs && !hp.mols[i].sp ? hp.mols[i].nt * ((hp.mols[i].n_aux + 1) / 2) : 0;
         mk(c, p.x[xs]);
+        for (int i = 0; i < n_mol; ++i)
+            c[i] = hp.mols[i].xs == xs && hp.mols[i].sp ? ri::xs_items(hp.mols[i].N, hp.mols[i].n_aux) : 0;
+        mk(c, p.xp[xs]);
     }
     if (p.fin)
         for (int xs = 1; xs <= 32; ++xs) {
             for (int i = 0; i < n_mol; ++i)
-                c[i] = hp.mols[i].xs64 == xs ? hp.mols[i].nt * ((hp.mols[i].n_aux + 1) / 2) : 0;
+                c[i] = hp.mols[i].xs64 == xs && !hp.mols[i].sp ? hp.mols[i].nt * ((hp.mols[i].n_aux + 1) / 2) : 0;
             mk(c, p.x64[xs]);
+            for (int i = 0; i < n_mol; ++i)
+                c[i] = hp.mols[i].xs64 == xs && hp.mols[i].sp ? ri::xs_items(hp.mols[i].N, hp.mols[i].n_aux) : 0;
+            mk(c, p.xp64[xs]);
         }
     // grouped GEMMs: member i of each
     // tunable: the member runs on the molecule's tuned tile (else on 64 x 64)
@@ -927,6 +953,18 @@ int32_t ri_energy_batched(int32_t n_mol, const ri_system* sys, const ri_batch_mo
         HIPR(ri::nuclear_repulsion(&sys[i], m.scal + SC_ENUC, si));
         HIPR(ri::copy(m.T1, m.S, (int64_t)m.N * m.N, si));
         HIPR(ri::cholesky_inv(m.T1, m.N, m.N, m.LinvS, m.N, m.dinvM, bad, si));
+        if (m.sp) {
+            ri::XSparse w;
+            w.map = (int32_t*)m.T2;   // free until the first iteration
+            w.list = m.plist;
+            w.cnt = m.pcnt;
+            if (p.prec == RI_FP64) w.BcT = (double*)m.BcT;
+            else w.BcT32 = (float*)m.BcT;
+            w.n_pairs = m.n_pairs;
+            w.ldp = ri::xs_ldp(m.n_aux);
+            w.lmax = m.lmax;
+            HIPR(ri::xs_prepare(w, m.Bc, m.pairs, m.n_pairs, m.N, m.n_aux, si));
+        }
     }
     for (int k = 0; k < SETUP_STREAMS; ++k) {
         HIPR(hipEventRecord(ss.e[k], ss.s[k]));

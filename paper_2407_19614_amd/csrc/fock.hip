@@ -830,6 +830,12 @@ hipError_t cpad(const double* C, int N, int n_occ, double* Cp, hipStream_t st) {
     return hipGetLastError();
 }
 
+hipError_t cpad_f32(const double* C, int N, int n_occ, float* Cf, hipStream_t st) {
+    const int cld = cpad_ld(n_occ), rows = n_tiles_1d(N) * 64;
+    cpad_f32_kernel<<<(unsigned)(((int64_t)rows * cld + 255) / 256), 256, 0, st>>>(C, N, n_occ, rows, cld, Cf);
+    return hipGetLastError();
+}
+
 // The FP64 X launch for shape code 4 * (16-row tiles) + (4-row quads); B
 // stored as TB (double, or float widened on load).
 template <typename TB>
@@ -859,8 +865,7 @@ hipError_t x_transform(const void* B, int prec, int N, int n_aux, int n_occ, con
         const int cld = cpad_ld(n_occ), rows = nt * 64;
         if (ntl * 4096 * 4 > INT32_MAX || (int64_t)rows * cld * 4 > INT32_MAX) return hipErrorInvalidValue;
         float* Cf = (float*)Cp;      // the C workspace holds twice as many floats as the padded FP64 copy
-        cpad_f32_kernel<<<(unsigned)(((int64_t)rows * cld + 255) / 256), 256, 0, st>>>(C, N, n_occ, rows, cld, Cf);
-        RI_TRY(hipGetLastError());
+        RI_TRY(cpad_f32(C, N, n_occ, Cf, st));
         switch (mt) {
 #define XCASE(k) case k: x2_kernel_f32<k><<<grid, 256, 0, st>>>(b, nt, ntl, Cf, cld, N, n_occ, n_aux, x, Npad); break;
             XCASE(1) XCASE(2) XCASE(3) XCASE(4) XCASE(5) XCASE(6) XCASE(7) XCASE(8)

@@ -46,6 +46,7 @@ hipError_t x_transform(const void* B, int prec, int N, int n_aux, int n_occ, con
                        double* Cp, void* Xt, hipStream_t st);
 // Cp = C zero-padded to [64 * tiles][cpad_ld(n_occ)]
 hipError_t cpad(const double* C, int N, int n_occ, double* Cp, hipStream_t st);
+hipError_t cpad_f32(const double* C, int N, int n_occ, float* Cf, hipStream_t st);
 // The same X^T from the fitted tensor over each row's significant partners
 // (FP64 arithmetic; B is not read).  xs_prepare lays out, from B_c and the pairs,
 // the partner lists [N][lmax] with their counts, and the transposed fitted
@@ -55,17 +56,20 @@ struct XSparse {
     int32_t* map = nullptr;   // [N][N] pair index or -1
     int2* list = nullptr;
     int* cnt = nullptr;
-    double* BcT = nullptr;    // nullptr: the dense form is used
+    double* BcT = nullptr;    // both nullptr: the dense form is used
+    float* BcT32 = nullptr;   // in the place of BcT for FP32 (and FP32-stored) exchange
+    bool on() const { return BcT || BcT32; }
     double* gpart = nullptr;  // xs_gpart(n_aux, n_pairs) doubles
     int64_t n_pairs = 0;
     int ldp = 0, lmax = 0;
 };
 // Whether a size takes this form: the pairs fill at most 60 % of the matrix
 // (its multiplications are those of the pairs; above, the dense kernel's whole
-// tiles cost no more than the gathers) and X^T is over 64 MiB (builds that fit
-// the static scratch of ri_fock_jk_noalloc keep the dense form and its
-// workspace, which need no partner lists or transposed copy).
-bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs);
+// tiles cost no more than the gathers), the copy is at most 64 GiB, and X^T is
+// over 64 MiB (builds that fit the static scratch of ri_fock_jk_noalloc keep
+// the dense form and its workspace, which need no partner lists or copy).
+bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs, int prec);
+bool xs_sparse(int N, int n_aux, int64_t n_pairs);   // the first two conditions
 int xs_ldp(int n_aux);
 int xs_lmax(int N);
 int64_t xs_gpart(int n_aux, int64_t n_pairs);
@@ -78,7 +82,10 @@ hipError_t xs_transform(const XSparse& w, int N, int n_aux, int n_occ, const dou
 hipError_t xs_lists(const XSparse& w, const int32_t* pairs, int64_t n_pairs, int N, hipStream_t st);
 hipError_t xs_rows(const XSparse& w, const double* Bc, int64_t n_pairs, int np, hipStream_t st);
 hipError_t xs_run(const XSparse& w, int N, int n_aux, int n_occ, const double* Cp, double* Xt, hipStream_t st);
-// gamma and (J != nullptr) J from the pair weights dpair
+// FP32 arithmetic (BcT32): the dense FP32 kernel's result bit for bit
+hipError_t xs_transform32(const XSparse& w, int N, int n_aux, int n_occ, const double* C, float* Cf, float* Xt,
+                          hipStream_t st);
+// gamma and (J != nullptr) J from the pair weights dpair (FP64 copy only)
 hipError_t xs_gamma_j(const XSparse& w, int N, int n_aux, const double* dpair, const int32_t* pairs, double* gamma,
                       double* J, hipStream_t st);
 // pair weights of D = 2 C C^T
@@ -227,6 +234,12 @@ struct MolDesc {
     double* Cq;   // C_occ zero-padded to [64 * nt][64], FP64 (or FP32 for FP32 exchange)
     double *dF[8], *dE[8];
     double *Bmat, *coef, *scal;
+    // exchange over the partner lists (xsparse.hip) where sp is set: BcT float
+    // for the FP32 forms; dense tiles otherwise
+    int sp, lmax;
+    int2* plist;
+    int* pcnt;
+    void* BcT;
     int* state;   // 0 active, 1 iteration, 2 DIIS pushes, 3 converged, 4.. DIIS slot order [8], 14.. purification
 };
 
@@ -263,6 +276,9 @@ __device__ __forceinline__ void decode_item(const int* prefix, int n_mol, int L,
 // X for the molecules whose xs equals `xs` (one launch per shape present); prec may
 // also be X_F64_B32 (FP64 shapes, Cq and Xt)
 hipError_t x_transform_b(const MolDesc* d, const int* prefix, int n_mol, int total, int xs, int prec, hipStream_t st);
+// the same over the partner lists, for the molecules with sp set; xs_items work items each
+hipError_t xs_transform_b(const MolDesc* d, const int* prefix, int n_mol, int total, int xs, int prec, hipStream_t st);
+int xs_items(int N, int n_aux);
 // Cq of every active molecule from its C (prefix counts 64-row blocks), in the
 // exchange precision `prec`
 hipError_t cpad_b(const MolDesc* d, const int* prefix, int n_mol, int total, int prec, hipStream_t st);

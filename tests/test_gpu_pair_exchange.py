@@ -62,3 +62,34 @@ def test_pair_exchange_is_reproducible():
     again = pr.fock_jk(C)
     assert all(torch.equal(a, b) for a, b in zip(first, again))
     assert np.isfinite(first[1].cpu().numpy()).all()
+
+
+# FP32 over the partner lists is the dense FP32 kernel's arithmetic: per 64 nu one chain of
+# fused multiply-adds in ascending nu (zeros change nothing), added in FP64
+@pytest.mark.parametrize("nc,n_occ", [(40, 40), (37, 47), (44, 100), (38, 128), (37, 133)])
+def test_pair_exchange_fp32_error(nc, n_occ):
+    need_gpu()
+    import paper_2407_19614_amd as P
+    import synth
+    s = synth.config_system("n400", n_centres=nc, seed=70 + nc)
+    s.n_occ = n_occ
+    C = dev(synth.random_coeffs(s.N, n_occ, 9))
+    pr = problem(s, P.FP32)
+    N, A, n = s.N, s.n_aux, pr.n_pairs
+    assert A * n_occ * ((N + 127) // 128 * 128) * 4 > 64 << 20 and 2 * n - N <= 0.6 * N * N
+    K = pr.fock_jk(C)[1]
+    mu, nu = pr.pairs[:n, 0].long(), pr.pairs[:n, 1].long()
+    B = torch.zeros((64, N, N), dtype=torch.float32, device="cuda")
+    c32 = C.float()
+    k, k_abs = torch.zeros_like(K), torch.zeros_like(K)
+    for p in range(0, A, 64):
+        m = min(64, A - p)
+        B[:m, mu, nu] = pr.Bc[p:p + m].float()
+        B[:m, nu, mu] = pr.Bc[p:p + m].float()
+        b = B[:m].double()
+        X = (b.reshape(-1, N) @ c32.double()).reshape(m, N, n_occ).permute(1, 0, 2).reshape(N, -1)
+        Xa = (b.abs().reshape(-1, N) @ c32.double().abs()).reshape(m, N, n_occ).permute(1, 0, 2).reshape(N, -1)
+        k += X @ X.T
+        k_abs += Xa @ Xa.T
+    # X: chains of at most 64 products and one rounding to FP32; K: chains of at most 64 rows
+    assert bool(((K - k).abs() <= 2 * (64 + 1 + 64) * 2.0 ** -24 * k_abs).all())
