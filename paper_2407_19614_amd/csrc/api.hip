@@ -389,9 +389,9 @@ int32_t occupied_space(const double* Fx, int N, int n_occ, EnergyWS& w, bool hav
     // L_S^{-1} F L_S^{-T}, skipping the zero triangle of L_S^{-1} in both products
     HIPC(ri::gemm_f64(false, false, N, N, N, 1.0, w.LinvS, N, 0, Fx, N, 0, 0.0, w.T1, N, 0, 1, 1, 0, st));
     HIPC(ri::gemm_f64(false, true, N, N, N, 1.0, w.T1, N, 0, w.LinvS, N, 0, 0.0, w.T2, N, 0, 1, 3, 0, st));
-    HIPC(ri::gershgorin(w.T2, N, w.scal + 16, w.red, st));
+    HIPC(ri::gershgorin_rows(w.T2, N, w.red, st));
     const int tiles = ri::tc2f_tiles(N);
-    HIPC(ri::tc2f_init(w.T2, w.scal + 16, N, w.X, w.tpart, w.tst, st));
+    HIPC(ri::tc2f_init(w.T2, w.red, N, w.X, w.tpart, w.tst, st));
     int k = 0, chunk = std::max(8, std::min(pred, max_it)), hs[8] = {};
     while (true) {
         const int upto = std::min(max_it, k + chunk);

@@ -147,16 +147,17 @@ hipError_t diis_solve(const double* Bmat, int m, int ld, double* coef, hipStream
 hipError_t diis_prep(double* Bfull, const double* row, const int* slots, int m, int snew, double* Bm,
                      hipStream_t st);
 hipError_t diis_combine(const double* const* Fs, const double* coef, int m, double* out, int64_t n, hipStream_t st);
-hipError_t gershgorin(const double* F, int N, double* bounds, double* red, hipStream_t st);
+// rows[2 r], rows[2 r + 1]: the ends of row r's Gershgorin interval
+hipError_t gershgorin_rows(const double* F, int N, double* rows, hipStream_t st);
 hipError_t hash_matrix(double* R, int64_t n, uint32_t seed, hipStream_t st);
 // ---- purification, one launch per step (tc2.hip).  part: 2 * tc2f_tiles(N)
 // doubles per parity; state: 8 ints per parity ([0] countdown, [1] done,
 // [2] steps run, [3] 1 if the latest X is in the step's output buffer).
 // Step k reads parity k % 2 and writes parity (k + 1) % 2; out_id says which
 // buffer the step writes (1: Y).
+// rows: the Gershgorin interval of each row (gershgorin_rows).
 int tc2f_tiles(int N);
-hipError_t tc2f_init(const double* F, const double* bounds, int N, double* X, double* part, int* state,
-                     hipStream_t st);
+hipError_t tc2f_init(const double* F, const double* rows, int N, double* X, double* part, int* state, hipStream_t st);
 hipError_t tc2f_step(const double* X, double* Y, int N, int n_occ, const double* part_in, double* part_out,
                      const int* st_in, int* st_out, int out_id, hipStream_t st);
 hipError_t tc2f_final(double* X, const double* Y, int N, const int* state, hipStream_t st);

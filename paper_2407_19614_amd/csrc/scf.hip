@@ -141,25 +141,6 @@ __global__ __launch_bounds__(256) void gersh_rows_kernel(const double* F, int N,
     }
 }
 
-__global__ __launch_bounds__(256) void gersh_final_kernel(const double* red, int N, double* bounds) {
-    double lo = 1e300, hi = -1e300;
-    for (int r = threadIdx.x; r < N; r += 256) {
-        lo = fmin(lo, red[2 * r]);
-        hi = fmax(hi, red[2 * r + 1]);
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = fmin(lo, __shfl_down(lo, o));
-        hi = fmax(hi, __shfl_down(hi, o));
-    }
-    __shared__ double sl[4], sh[4];
-    if ((threadIdx.x & 63) == 0) { sl[threadIdx.x >> 6] = lo; sh[threadIdx.x >> 6] = hi; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        bounds[0] = fmin(fmin(sl[0], sl[1]), fmin(sl[2], sl[3]));
-        bounds[1] = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
-    }
-}
-
 // Counter-based pseudo-random values in [-1, 1) (a 32-bit integer hash of
 // the element index); any full-rank block serves as a subspace start.
 __global__ void hash_kernel(double* R, int64_t n, uint32_t seed) {
@@ -247,10 +228,8 @@ hipError_t diis_combine(const double* const* Fs, const double* coef, int m, doub
     combine_kernel<<<nb(n), 256, 0, st>>>(p, coef, m, out, n);
     return hipGetLastError();
 }
-hipError_t gershgorin(const double* F, int N, double* bounds, double* red, hipStream_t st) {
-    gersh_rows_kernel<<<(N + 3) / 4, 256, 0, st>>>(F, N, red);
-    RI_TRY(hipGetLastError());
-    gersh_final_kernel<<<1, 256, 0, st>>>(red, N, bounds);
+hipError_t gershgorin_rows(const double* F, int N, double* rows, hipStream_t st) {
+    gersh_rows_kernel<<<(N + 3) / 4, 256, 0, st>>>(F, N, rows);
     return hipGetLastError();
 }
 hipError_t hash_matrix(double* R, int64_t n, uint32_t seed, hipStream_t st) {
