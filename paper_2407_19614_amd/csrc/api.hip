@@ -197,9 +197,9 @@ hipError_t jk_density(const double* Bc, const int32_t* pairs, int64_t n_pairs, i
 }
 
 struct EnergyWS {
-    double *S, *H, *Ls, *LinvS, *J, *K, *F, *D, *T1, *T2, *E, *Fx, *X, *X2;
+    double *S, *H, *Ls, *LinvS, *J, *K, *F, *D, *T1, *T2, *Fx, *X, *X2;
     double *dF[8], *dE[8];
-    double *Bmat, *Bfull, *coef, *row, *Y, *Cp, *R, *Mo, *LinvM, *dinvS, *dinvM, *scal, *red, *tpart;
+    double *Bfull, *coef, *Y, *Cp, *R, *Mo, *LinvM, *dinvS, *dinvM, *scal, *red, *tpart;
     int *bad, *tst;
     FockWS fock;
     FockWS fin;   // final FP64 exchange build of the split-BF16 forms: FP64 Xt and slabs of B_c
@@ -209,16 +209,14 @@ EnergyWS carve_energy(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, in
                       bool comp = false, bool fin_slab = false, bool wide = false) {
     EnergyWS w;
     const int64_t n2 = (int64_t)N * N;
-    double** mats[] = {&w.S, &w.H, &w.Ls, &w.LinvS, &w.J, &w.K, &w.F, &w.D, &w.T1, &w.T2, &w.E, &w.Fx, &w.X, &w.X2};
+    double** mats[] = {&w.S, &w.H, &w.Ls, &w.LinvS, &w.J, &w.K, &w.F, &w.D, &w.T1, &w.T2, &w.Fx, &w.X, &w.X2};
     for (double** m : mats) *m = a.take<double>(n2);
     for (int i = 0; i < 8; ++i) {
         w.dF[i] = i < diis_n ? a.take<double>(n2) : nullptr;
         w.dE[i] = i < diis_n ? a.take<double>(n2) : nullptr;
     }
-    w.Bmat = a.take<double>(64);
     w.Bfull = a.take<double>(64);
     w.coef = a.take<double>(8);
-    w.row = a.take<double>(8);
     w.Y = a.take<double>((int64_t)N * n_occ);
     w.Cp = a.take<double>((int64_t)N * n_occ);
     w.R = a.take<double>((int64_t)N * n_occ);
@@ -387,8 +385,8 @@ int32_t occupied_space(const double* Fx, int N, int n_occ, EnergyWS& w, bool hav
                        int max_it, int& pred, hipStream_t st) {
     const int64_t n2 = (int64_t)N * N;
     // L_S^{-1} F L_S^{-T}, skipping the zero triangle of L_S^{-1} in both products
-    HIPC(ri::gemm_f64(false, false, N, N, N, 1.0, w.LinvS, N, 0, Fx, N, 0, 0.0, w.T1, N, 0, 1, 1, 0, st));
-    HIPC(ri::gemm_f64(false, true, N, N, N, 1.0, w.T1, N, 0, w.LinvS, N, 0, 0.0, w.T2, N, 0, 1, 3, 0, st));
+    HIPC(ri::gemm_scf(false, false, N, N, N, 1.0, w.LinvS, N, Fx, N, w.T1, N, 1, st));
+    HIPC(ri::gemm_scf(false, true, N, N, N, 1.0, w.T1, N, w.LinvS, N, w.T2, N, 3, st));
     HIPC(ri::gershgorin_rows(w.T2, N, w.red, st));
     const int tiles = ri::tc2f_tiles(N);
     HIPC(ri::tc2f_init(w.T2, w.red, N, w.X, w.tpart, w.tst, st));
@@ -412,15 +410,13 @@ int32_t occupied_space(const double* Fx, int N, int n_occ, EnergyWS& w, bool hav
     HIPC(ri::tc2f_final(w.X, w.X2, N, w.tst + 8 * (k & 1), st));
     if (!have_prev) HIPC(ri::hash_matrix(w.Cp, (int64_t)N * n_occ, 0x5eed1234u, st));
     for (int pass = 0; pass < 2; ++pass) {
-        HIPC(ri::gemm_f64(false, false, N, n_occ, N, 1.0, w.X, N, 0, w.Cp, n_occ, 0, 0.0, w.Y, n_occ, 0, 1, 0, 0, st));
-        HIPC(ri::gemm_f64(true, false, n_occ, n_occ, N, 1.0, w.Y, n_occ, 0, w.Y, n_occ, 0, 0.0, w.Mo, n_occ, 0, 1, 0,
-                          0, st));
-        HIPC(ri::cholesky_inv(w.Mo, n_occ, n_occ, w.LinvM, n_occ, w.dinvM, w.bad + 1, st));
-        HIPC(ri::gemm_f64(false, true, N, n_occ, n_occ, 1.0, w.Y, n_occ, 0, w.LinvM, n_occ, 0, 0.0, w.Cp, n_occ, 0,
-                          1, 0, 0, st));
+        HIPC(ri::gemm_scf(false, false, N, n_occ, N, 1.0, w.X, N, w.Cp, n_occ, w.Y, n_occ, 0, st));
+        HIPC(ri::gemm_scf(true, false, n_occ, n_occ, N, 1.0, w.Y, n_occ, w.Y, n_occ, w.Mo, n_occ, 0, st));
+        HIPC(n_occ <= 64 ? ri::chol_small(w.Mo, n_occ, w.LinvM, w.bad + 1, st)
+                         : ri::cholesky_inv(w.Mo, n_occ, n_occ, w.LinvM, n_occ, w.dinvM, w.bad + 1, st));
+        HIPC(ri::gemm_scf(false, true, N, n_occ, n_occ, 1.0, w.Y, n_occ, w.LinvM, n_occ, w.Cp, n_occ, 0, st));
     }
-    HIPC(ri::gemm_f64(true, false, N, n_occ, N, 1.0, w.LinvS, N, 0, w.Cp, n_occ, 0, 0.0, C_out, n_occ, 0, 1, 2, 0,
-                      st));
+    HIPC(ri::gemm_scf(true, false, N, n_occ, N, 1.0, w.LinvS, N, w.Cp, n_occ, C_out, n_occ, 2, st));
     return RI_OK;
 }
 
@@ -741,7 +737,7 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
     } else {
         HIPC(ri::copy(C_occ, guess, (int64_t)N * no, st));
         // the guess in the orthonormal frame, C' = L_S^T C, seeds the subspace passes
-        HIPC(ri::gemm_f64(true, false, N, no, N, 1.0, w.Ls, N, 0, C_occ, no, 0, 0.0, w.Cp, no, 0, 1, 2, 0, st));
+        HIPC(ri::gemm_scf(true, false, N, no, N, 1.0, w.Ls, N, C_occ, no, w.Cp, no, 2, st));
     }
 
     if (w.fock.xs.on()) HIPC(ri::xs_prepare(w.fock.xs, Bc, pairs, n_pairs, N, na, st));
@@ -755,13 +751,20 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
         rc = fock_impl(N, na, no, B, prec, Bc, pairs, n_pairs, C_occ, w.J, w.K, nullptr, w.fock, st, nullptr, true,
                        true);
         if (rc) return rc;
-        HIPC(ri::fock_assemble(w.H, w.J, w.K, w.F, n2, st));
-        HIPC(ri::gemm_f64(false, true, N, N, no, 2.0, C_occ, no, 0, C_occ, no, 0, 0.0, w.D, N, 0, 1, 0, 0, st));
-        HIPC(ri::energy_terms(w.D, w.H, w.J, w.K, n2, w.scal + 8, w.scal, w.red, st));
-        HIPC(ri::gemm_f64(false, false, N, N, N, 1.0, w.F, N, 0, w.D, N, 0, 0.0, w.T1, N, 0, 1, 0, 0, st));
-        HIPC(ri::gemm_f64(false, false, N, N, N, 1.0, w.T1, N, 0, w.S, N, 0, 0.0, w.T2, N, 0, 1, 0, 0, st));
-        HIPC(ri::commutator(w.T2, w.E, N, st));
-        HIPC(ri::max_abs(w.E, n2, w.scal + 5, w.red, st));
+        // the new (F, e) goes into the DIIS ring with the step's sums: the slot order
+        // depends on the iteration count only
+        const int sn = pushes % dn;
+        ++pushes;
+        for (size_t k = 0; k < slots.size(); ++k)
+            if (slots[k] == sn) { slots.erase(slots.begin() + k); break; }
+        slots.push_back(sn);
+        const int m = (int)slots.size();
+        HIPC(ri::gemm_scf(false, true, N, N, no, 2.0, C_occ, no, C_occ, no, w.D, N, 0, st));
+        HIPC(ri::fock_energy(w.H, w.J, w.K, w.D, w.F, n2, w.red, st));
+        HIPC(ri::gemm_scf(false, false, N, N, N, 1.0, w.F, N, w.D, N, w.T1, N, 0, st));
+        HIPC(ri::gemm_scf(false, false, N, N, N, 1.0, w.T1, N, w.S, N, w.T2, N, 0, st));
+        HIPC(ri::error_push(w.T2, w.F, w.dE, w.dF[sn], slots.data(), m, N, w.red, st));
+        HIPC(ri::step_finish(w.red, w.scal + 8, w.scal, w.Bfull, slots.data(), m, N, w.coef, st));
         HIPC(hipMemcpyAsync(host, w.scal, 6 * sizeof(double), hipMemcpyDeviceToHost, st));
         HIPC(hipStreamSynchronize(st));
         res->E_total = host[0];
@@ -779,26 +782,10 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
             }
         }
         E_old = host[0];
-        // DIIS: store (F, e) in the ring, update the B matrix row, extrapolate.
-        const int s = pushes % dn;
-        ++pushes;
-        HIPC(ri::copy(w.dF[s], w.F, n2, st));
-        HIPC(ri::copy(w.dE[s], w.E, n2, st));
-        for (size_t k = 0; k < slots.size(); ++k)
-            if (slots[k] == s) { slots.erase(slots.begin() + k); break; }
-        slots.push_back(s);
-        const int m = (int)slots.size();
-        {
-            const double* es[8];
-            for (int k = 0; k < m; ++k) es[k] = w.dE[slots[k]];
-            HIPC(ri::diis_dots(es, m, w.dE[s], w.row, n2, w.red, st));
-            HIPC(ri::diis_prep(w.Bfull, w.row, slots.data(), m, s, w.Bmat, st));
-        }
         const double* Fx = w.F;
         if (m >= 2) {
             const double* fs[8];
             for (int k = 0; k < m; ++k) fs[k] = w.dF[slots[k]];
-            HIPC(ri::diis_solve(w.Bmat, m, 8, w.coef, st));
             HIPC(ri::diis_combine(fs, w.coef, m, w.Fx, n2, st));
             Fx = w.Fx;
         }

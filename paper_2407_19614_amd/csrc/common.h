@@ -93,6 +93,8 @@ __device__ __forceinline__ double lane_bcast(double v, int src) {
 // in registers: an accumulator tile (element q of lane (c, g) holds row
 // 4q + g of column c) is already the B operand of the next product over its
 // 16 rows.
+// Diagonal blocks at or past nb are the identity the caller put there: their
+// steps change nothing and are left out.
 template <class Bad, class Store>
 __device__ __forceinline__ void chol_inv64_blocked(double (*S)[65], int nb, Bad bad, Store store) {
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
@@ -101,6 +103,10 @@ __device__ __forceinline__ void chol_inv64_blocked(double (*S)[65], int nb, Bad 
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
         const int o = 16 * kb;
+        if (o >= nb) {
+            for (int e = lane; e < 256; e += 64) Di[kb][e >> 4][e & 15] = (e >> 4) == (e & 15) ? 1.0 : 0.0;
+            continue;
+        }
         // factor of the diagonal block: lane r keeps its row
         double a[16];
         double rd = 1.0;
@@ -273,8 +279,6 @@ hipError_t tri_inverse_steps(const double* L, int n, int64_t lda, const double* 
 
 hipError_t fill(double* p, double v, int64_t n, hipStream_t s);
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
-// max |x_i| into *out; red: scratch of 256 doubles
-hipError_t max_abs(const double* x, int64_t n, double* out, double* red, hipStream_t s);
 hipError_t copy(double* dst, const double* src, int64_t n, hipStream_t s);
 hipError_t widen(const float* x, double* y, int64_t n, hipStream_t s);   // y = (double) x
 

@@ -355,38 +355,6 @@ __global__ void f32_to_f64_kernel(const float* x, double* y, int64_t n) {
         y[i] = (double)x[i];
 }
 
-__device__ double block_sum(double v) {
-    __shared__ double sh[16];
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
-    int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    if (l == 0) sh[w] = v;
-    __syncthreads();
-    double r = 0.0;
-    if (threadIdx.x == 0)
-        for (int i = 0; i < (int)(blockDim.x >> 6); ++i) r += sh[i];
-    return r;
-}
-__device__ double block_max(double v) {
-    __shared__ double sh[16];
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_down(v, o));
-    int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    if (l == 0) sh[w] = v;
-    __syncthreads();
-    double r = 0.0;
-    if (threadIdx.x == 0)
-        for (int i = 0; i < (int)(blockDim.x >> 6); ++i) r = fmax(r, sh[i]);
-    return r;
-}
-
-// max |x| in two stages: 256 workgroups over grid-stride shares, then one
-__global__ __launch_bounds__(1024) void maxabs_kernel(const double* x, int64_t n, double* out) {
-    double s = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        s = fmax(s, fabs(x[i]));
-    s = block_max(s);
-    if (threadIdx.x == 0) out[blockIdx.x] = s;
-}
-
 // Band of the factor in the leaf kernel's operand order: slot (k, d) of
 // P (4096 doubles each, 4 slots per 64-row block k) holds Dinv_k for d = 0
 // and -L_{k+d, k} (zero beyond row n) for d = 1..3, element
@@ -682,12 +650,6 @@ hipError_t fill(double* p, double v, int64_t n, hipStream_t s) {
 }
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s) {
     fill_i32_kernel<<<nblk(n), 256, 0, s>>>(p, v, n);
-    return hipGetLastError();
-}
-hipError_t max_abs(const double* x, int64_t n, double* out, double* red, hipStream_t s) {
-    maxabs_kernel<<<256, 1024, 0, s>>>(x, n, red);
-    RI_TRY(hipGetLastError());
-    maxabs_kernel<<<1, 1024, 0, s>>>(red, 256, out);
     return hipGetLastError();
 }
 hipError_t widen(const float* x, double* y, int64_t n, hipStream_t s) {

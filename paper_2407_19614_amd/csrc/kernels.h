@@ -136,19 +136,27 @@ int j_split_count(int n_aux);
 namespace ri {
 // ---- SCF helpers (scf.hip)
 hipError_t fock_assemble(const double* h, const double* J, const double* K, double* F, int64_t n, hipStream_t st);
-hipError_t commutator(const double* M, double* e, int N, hipStream_t st);   // e = M - M^T
 // Reductions over N x N matrices take a scratch `red` of red_elems(N) doubles.
 int red_elems(int N);
-hipError_t diis_dots(const double* const* es, int m, const double* enew, double* row, int64_t n, double* red,
-                     hipStream_t st);
-hipError_t diis_solve(const double* Bmat, int m, int ld, double* coef, hipStream_t st);
-// DIIS inner products into the slot-indexed 8 x 8 matrix Bfull, and the m x m
-// matrix of slots[0..m) gathered into Bm (ld 8); no host round trip.
-hipError_t diis_prep(double* Bfull, const double* row, const int* slots, int m, int snew, double* Bm,
-                     hipStream_t st);
+// One SCF step's bookkeeping in three launches, no host round trip:
+// F = h + J - K and the partial sums of D.h, D.J, D.K;
+hipError_t fock_energy(const double* h, const double* J, const double* K, const double* D, double* F, int64_t n,
+                       double* red, hipStream_t st);
+// e = M - M^T (M = F D S) and F into the DIIS ring's slot slots[m - 1], with the partial
+// sums of <e_k, e> over the slots (oldest first) and of max |e|;
+hipError_t error_push(const double* M, const double* F, double* const* dE, double* dFnew, const int* slots, int m,
+                      int N, double* red, hipStream_t st);
+// and all the sums: scal[0..4] the energies, scal[5] max |e|, the DIIS inner products into
+// the slot-indexed 8 x 8 matrix Bfull, and for m >= 2 the extrapolation coefficients.
+hipError_t step_finish(double* red, const double* enuc, double* scal, double* Bfull, const int* slots, int m, int N,
+                       double* coef, hipStream_t st);
 hipError_t diis_combine(const double* const* Fs, const double* coef, int m, double* out, int64_t n, hipStream_t st);
 // rows[2 r], rows[2 r + 1]: the ends of row r's Gershgorin interval
 hipError_t gershgorin_rows(const double* F, int N, double* rows, hipStream_t st);
+// ---- small products (small.hip): C = alpha op(A) op(B); chol_small: Linv of an n <= 64 Gram matrix
+hipError_t gemm_scf(bool ta, bool tb, int M, int N, int K, double alpha, const double* A, int lda, const double* B,
+                    int ldb, double* C, int ldc, int tri, hipStream_t s);
+hipError_t chol_small(const double* A, int n, double* Linv, int* bad, hipStream_t s);
 hipError_t hash_matrix(double* R, int64_t n, uint32_t seed, hipStream_t st);
 // ---- purification, one launch per step (tc2.hip).  part: 2 * tc2f_tiles(N)
 // doubles per parity; state: 8 ints per parity ([0] countdown, [1] done,

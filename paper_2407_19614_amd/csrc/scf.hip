@@ -15,17 +15,11 @@ __global__ void fock_kernel(const double* h, const double* J, const double* K, d
         F[i] = h[i] + J[i] - K[i];
 }
 
-__global__ void comm_kernel(const double* M, double* e, int N) {
-    int c = blockIdx.x * blockDim.x + threadIdx.x, r = blockIdx.y;
-    if (c >= N) return;
-    e[(int64_t)r * N + c] = M[(int64_t)r * N + c] - M[(int64_t)c * N + r];
-}
-
 struct Ptrs { const double* p[8]; };
 
-// Two-stage, deterministic reductions over N^2-element matrices: RED_BLOCKS
-// workgroups each reduce a fixed grid-stride share into a partial row of
-// `red`, then one workgroup combines the partials in order.
+// Two-stage, deterministic reductions over N^2-element matrices: the workgroups
+// of a first launch each reduce a fixed share into a partial row of `red`, then
+// one workgroup combines the partials in order.
 constexpr int RED_BLOCKS = 256;
 
 // sum of v over the 256 threads of a workgroup (fixed order)
@@ -37,84 +31,182 @@ __device__ __forceinline__ double wg_sum(double v, double* sh) {
     return sh[0] + sh[1] + sh[2] + sh[3];
 }
 
-// partial[b][k] = sum over block b's share of x_k * enew (k < m)
-__global__ __launch_bounds__(256) void multi_dot_part_kernel(Ptrs es, const double* enew, int m, int64_t n,
-                                                             double* red) {
+struct Slots { int s[8]; };
+struct MutPtrs { double* p[8]; };
+
+// Where `red` holds what between the launches of one step: RED_BLOCKS rows of
+// the energies' partial sums, then one row per 32 x 32 upper tile of the error
+// (8 inner products and the maximum).
+constexpr int RE = 3 * RED_BLOCKS, ROW = 9;
+__host__ __device__ inline int err_tiles(int N) {
+    const int nt = (N + 31) / 32;
+    return nt * (nt + 1) / 2;
+}
+
+// F = h + J - K; partial[b] = (D.h, D.J, D.K) over block b's share
+__global__ __launch_bounds__(256) void fock_energy_kernel(const double* __restrict__ h, const double* __restrict__ J,
+                                                          const double* __restrict__ K, const double* __restrict__ D,
+                                                          double* __restrict__ F, int64_t n,
+                                                          double* __restrict__ red) {
     __shared__ double sh[4];
-    double s[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) s[k] = 0.0;
+    double a = 0.0, b = 0.0, c = 0.0;
     for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const double e = enew[i];
+        const double d = D[i], hi = h[i], j = J[i], k = K[i];
+        F[i] = hi + j - k;
+        a += d * hi;
+        b += d * j;
+        c += d * k;
+    }
+    a = wg_sum(a, sh);
+    b = wg_sum(b, sh);
+    c = wg_sum(c, sh);
+    if (threadIdx.x == 0) {
+        red[blockIdx.x * 3 + 0] = a;
+        red[blockIdx.x * 3 + 1] = b;
+        red[blockIdx.x * 3 + 2] = c;
+    }
+}
+
+// One upper 32 x 32 tile of e = M - M^T with its mirror -e^T, both written to the
+// ring with the same entries of F, and the tile pair's sums.
+__global__ __launch_bounds__(256) void error_push_kernel(const double* __restrict__ M, const double* __restrict__ F,
+                                                         MutPtrs dE, double* __restrict__ dFnew, Slots sl, int m,
+                                                         int N, double* __restrict__ red) {
+    __shared__ double t1[32][33], t2[32][33], sh[4];
+    const int nt = (N + 31) / 32;
+    int I = 0, rem = blockIdx.x;
+    while (rem >= nt - I) {
+        rem -= nt - I;
+        ++I;
+    }
+    const int J = I + rem, c = threadIdx.x & 31, r0 = threadIdx.x >> 5;
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (k < m) s[k] += es.p[k][i] * e;
+    for (int k = 0; k < 4; ++k) {
+        const int r = r0 + 8 * k;
+        t1[r][c] = (32 * I + r < N && 32 * J + c < N) ? M[(int64_t)(32 * I + r) * N + 32 * J + c] : 0.0;
+        t2[r][c] = (32 * J + r < N && 32 * I + c < N) ? M[(int64_t)(32 * J + r) * N + 32 * I + c] : 0.0;
     }
-    for (int k = 0; k < m; ++k) {
-        const double t = wg_sum(s[k], sh);
-        if (threadIdx.x == 0) red[blockIdx.x * 8 + k] = t;
+    __syncthreads();
+    double dot[8], big = 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) dot[k] = 0.0;
+    double* en = dE.p[m - 1];
+    auto put = [&](int row, int col, double e) {
+        if (row >= N || col >= N) return;
+        const int64_t i = (int64_t)row * N + col;
+#pragma unroll
+        for (int k = 0; k < 7; ++k)
+            if (k < m - 1) dot[k] += dE.p[k][i] * e;
+        en[i] = e;
+        dFnew[i] = F[i];
+        dot[7] += e * e;
+        big = fmax(big, fabs(e));
+    };
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int r = r0 + 8 * k;
+        put(32 * I + r, 32 * J + c, t1[r][c] - t2[c][r]);
+        if (I != J) put(32 * J + r, 32 * I + c, t2[r][c] - t1[c][r]);
     }
+    double* out = red + RE + (int64_t)blockIdx.x * ROW;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {                  // slot 7: <e, e>
+        if (k < m - 1 || k == 7) {
+            const double v = wg_sum(dot[k], sh);
+            if (threadIdx.x == 0) out[k] = v;
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_down(big, o));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = big;
+    __syncthreads();
+    if (threadIdx.x == 0) out[8] = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
 }
 
-__global__ __launch_bounds__(256) void multi_dot_final_kernel(const double* red, int m, double* row) {
-    __shared__ double sh[4];
-    for (int k = 0; k < m; ++k) {
-        const double t = wg_sum(threadIdx.x < RED_BLOCKS ? red[threadIdx.x * 8 + k] : 0.0, sh);
-        if (threadIdx.x == 0) row[k] = t;
-    }
+// LDS writes of this wave are seen by its later reads
+__device__ __forceinline__ void lds_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-// Solve [B -1; -1 0] [c; l] = [0; -1] by Gaussian elimination with partial
-// pivoting (one thread; m <= 8).
-__global__ void diis_solve_kernel(const double* Bm, int m, int ld, double* coef) {
-    if (threadIdx.x != 0) return;
-    double a[9][10];
+// The sums of one step, the DIIS matrix (row and column of the new slot into the
+// slot-indexed Bfull) and the solution of [B -1; -1 0] [c; l] = [0; -1] by
+// Gaussian elimination with partial pivoting, on the first wave: the matrix lies
+// in LDS, a lane per element of an update (one thread with the matrix in
+// scratch memory took 38 us).
+__global__ __launch_bounds__(256) void step_finish_kernel(const double* __restrict__ red,
+                                                          const double* __restrict__ enuc, double* __restrict__ scal,
+                                                          double* __restrict__ Bfull, Slots sl, int m, int tiles,
+                                                          double* __restrict__ coef) {
+    __shared__ double sh[4], row[8], a[9][11], x[9];
+    const int tid = threadIdx.x;
+    double e3[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) e3[k] = wg_sum(red[tid * 3 + k], sh);
+    for (int k = 0; k < 8; ++k) {
+        if (k >= m - 1 && k != 7) continue;
+        double v = 0.0;
+        for (int t = tid; t < tiles; t += 256) v += red[RE + (int64_t)t * ROW + k];
+        v = wg_sum(v, sh);
+        if (tid == 0) row[k == 7 ? m - 1 : k] = v;
+    }
+    double big = 0.0;
+    for (int t = tid; t < tiles; t += 256) big = fmax(big, red[RE + (int64_t)t * ROW + 8]);
+    for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_down(big, o));
+    __syncthreads();
+    if ((tid & 63) == 0) sh[tid >> 6] = big;
+    __syncthreads();
+    if (tid == 0) {
+        const double en = *enuc;
+        scal[0] = e3[0] + 0.5 * e3[1] - 0.5 * e3[2] + en;   // E_total
+        scal[1] = en;
+        scal[2] = e3[0];                                    // E_1e
+        scal[3] = 0.5 * e3[1];                              // E_J
+        scal[4] = -0.5 * e3[2];                             // E_K
+        scal[5] = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
+    }
+    if (tid < m) {
+        Bfull[sl.s[m - 1] * 8 + sl.s[tid]] = row[tid];
+        Bfull[sl.s[tid] * 8 + sl.s[m - 1]] = row[tid];
+    }
+    __syncthreads();
+    if (m < 2 || tid >= 64) return;
     const int n = m + 1;
-    for (int i = 0; i < m; ++i) {
-        for (int j = 0; j < m; ++j) a[i][j] = Bm[i * ld + j];
-        a[i][m] = -1.0;
-        a[i][n] = 0.0;
+    for (int e = tid; e < n * (n + 1); e += 64) {
+        const int i = e / (n + 1), j = e % (n + 1);
+        a[i][j] = i < m && j < m   ? Bfull[sl.s[i] * 8 + sl.s[j]]
+                  : i < m          ? (j == m ? -1.0 : 0.0)
+                  : (j == m ? 0.0 : -1.0);
     }
-    for (int j = 0; j < m; ++j) a[m][j] = -1.0;
-    a[m][m] = 0.0;
-    a[m][n] = -1.0;
+    lds_wave_sync();
     for (int c = 0; c < n; ++c) {
         int piv = c;
         for (int r = c + 1; r < n; ++r)
             if (fabs(a[r][c]) > fabs(a[piv][c])) piv = r;
-        if (piv != c)
-            for (int k = 0; k <= n; ++k) { double t = a[c][k]; a[c][k] = a[piv][k]; a[piv][k] = t; }
+        if (piv != c && tid <= n) {
+            const double t = a[c][tid];
+            a[c][tid] = a[piv][tid];
+            a[piv][tid] = t;
+        }
+        lds_wave_sync();
         double d = a[c][c];
         if (d == 0.0) d = 1e-300;
-        for (int r = c + 1; r < n; ++r) {
-            double f = a[r][c] / d;
-            for (int k = c; k <= n; ++k) a[r][k] -= f * a[c][k];
+        // rows below c, columns right of c; the factors' column is not read again
+        const int w = n - c, cnt = (n - 1 - c) * w;
+        for (int e = tid; e < cnt; e += 64) {
+            const int r = c + 1 + e / w, k = c + 1 + e % w;
+            a[r][k] -= a[r][c] / d * a[c][k];
         }
+        lds_wave_sync();
     }
-    double x[9];
-    for (int r = n - 1; r >= 0; --r) {
-        double s = a[r][n];
-        for (int k = r + 1; k < n; ++k) s -= a[r][k] * x[k];
-        x[r] = s / (a[r][r] == 0.0 ? 1e-300 : a[r][r]);
-    }
-    for (int i = 0; i < m; ++i) coef[i] = x[i];
-}
-
-// DIIS matrix on the device.  row[k] = <e_{slot k}, e_new> for the slots in
-// order (the new one last) goes into row and column `snew` of the
-// slot-indexed 8 x 8 matrix Bfull; then the m x m matrix of the slots in order
-// is gathered into Bm (ld 8) for the solve.  The slot order is host
-// bookkeeping that depends on the iteration count only.
-struct Slots { int s[8]; };
-__global__ void diis_prep_kernel(double* Bfull, const double* row, Slots sl, int m, int snew, double* Bm) {
-    if (threadIdx.x == 0)
-        for (int k = 0; k < m; ++k) {
-            Bfull[snew * 8 + sl.s[k]] = row[k];
-            Bfull[sl.s[k] * 8 + snew] = row[k];
+    if (tid == 0) {
+        for (int r = n - 1; r >= 0; --r) {
+            double s = a[r][n];
+            for (int k = r + 1; k < n; ++k) s -= a[r][k] * x[k];
+            x[r] = s / (a[r][r] == 0.0 ? 1e-300 : a[r][r]);
         }
-    __syncthreads();
-    const int i = threadIdx.x >> 3, j = threadIdx.x & 7;
-    if (threadIdx.x < 64 && i < m && j < m) Bm[i * 8 + j] = Bfull[sl.s[i] * 8 + sl.s[j]];
+        for (int i = 0; i < m; ++i) coef[i] = x[i];
+    }
 }
 
 __global__ void combine_kernel(Ptrs Fs, const double* coef, int m, double* out, int64_t n) {
@@ -196,30 +288,29 @@ hipError_t fock_assemble(const double* h, const double* J, const double* K, doub
     fock_kernel<<<nb(n), 256, 0, st>>>(h, J, K, F, n);
     return hipGetLastError();
 }
-hipError_t commutator(const double* M, double* e, int N, hipStream_t st) {
-    comm_kernel<<<dim3((N + 255) / 256, N), 256, 0, st>>>(M, e, N);
+hipError_t fock_energy(const double* h, const double* J, const double* K, const double* D, double* F, int64_t n,
+                       double* red, hipStream_t st) {
+    fock_energy_kernel<<<RED_BLOCKS, 256, 0, st>>>(h, J, K, D, F, n, red);
     return hipGetLastError();
 }
-hipError_t diis_dots(const double* const* es, int m, const double* enew, double* row, int64_t n, double* red,
-                     hipStream_t st) {
+hipError_t error_push(const double* M, const double* F, double* const* dE, double* dFnew, const int* slots, int m,
+                      int N, double* red, hipStream_t st) {
     if (m < 1 || m > 8) return hipErrorInvalidValue;
-    Ptrs p{};
-    for (int i = 0; i < m; ++i) p.p[i] = es[i];
-    multi_dot_part_kernel<<<RED_BLOCKS, 256, 0, st>>>(p, enew, m, n, red);
-    RI_TRY(hipGetLastError());
-    multi_dot_final_kernel<<<1, 256, 0, st>>>(red, m, row);
+    MutPtrs e{};
+    Slots sl{};
+    for (int k = 0; k < m; ++k) {
+        e.p[k] = dE[slots[k]];
+        sl.s[k] = slots[k];
+    }
+    error_push_kernel<<<err_tiles(N), 256, 0, st>>>(M, F, e, dFnew, sl, m, N, red);
     return hipGetLastError();
 }
-hipError_t diis_prep(double* Bfull, const double* row, const int* slots, int m, int snew, double* Bm,
-                     hipStream_t st) {
+hipError_t step_finish(double* red, const double* enuc, double* scal, double* Bfull, const int* slots, int m, int N,
+                       double* coef, hipStream_t st) {
     if (m < 1 || m > 8) return hipErrorInvalidValue;
     Slots sl{};
     for (int k = 0; k < m; ++k) sl.s[k] = slots[k];
-    diis_prep_kernel<<<1, 64, 0, st>>>(Bfull, row, sl, m, snew, Bm);
-    return hipGetLastError();
-}
-hipError_t diis_solve(const double* Bmat, int m, int ld, double* coef, hipStream_t st) {
-    diis_solve_kernel<<<1, 64, 0, st>>>(Bmat, m, ld, coef);
+    step_finish_kernel<<<1, 256, 0, st>>>(red, enuc, scal, Bfull, sl, m, err_tiles(N), coef);
     return hipGetLastError();
 }
 hipError_t diis_combine(const double* const* Fs, const double* coef, int m, double* out, int64_t n, hipStream_t st) {
@@ -244,6 +335,6 @@ hipError_t energy_terms(const double* D, const double* h, const double* J, const
     return hipGetLastError();
 }
 
-int red_elems(int N) { return std::max(RED_BLOCKS * 8, 2 * N); }
+int red_elems(int N) { return std::max(RE + ROW * err_tiles(N), 2 * N); }
 
 }  // namespace ri
