@@ -458,6 +458,27 @@ __global__ __launch_bounds__(256) void greduce_kernel(const double* part, int ro
     if (threadIdx.x == 0) grad[i] = sh[0];
 }
 
+// The blocks B_ij^P and Xi^P are symmetric in ij.  pack: Bp[P][e] = B[P][i][j] for
+// the entries e = i (i + 1) / 2 + j, j <= i, times sqrt 2 off the diagonal, so
+// that sums over all ij are sums over e; unpack: both halves of Xi[P] from Xp[P].
+__global__ __launch_bounds__(256) void pack_ij_kernel(const double* __restrict__ B, int o, double* __restrict__ Bp) {
+    const int i = blockIdx.x;
+    const int64_t P = blockIdx.y;
+    const double* row = B + (P * o + i) * o;
+    double* out = Bp + P * ((int64_t)o * (o + 1) / 2) + (int64_t)i * (i + 1) / 2;
+    for (int j = threadIdx.x; j <= i; j += blockDim.x) out[j] = j == i ? row[j] : 1.41421356237309504880 * row[j];
+}
+__global__ __launch_bounds__(256) void unpack_ij_kernel(const double* __restrict__ Xp, int o, double* __restrict__ Xi) {
+    const int i = blockIdx.x;
+    const int64_t P = blockIdx.y;
+    const double* in = Xp + P * ((int64_t)o * (o + 1) / 2);
+    double* out = Xi + (P * o + i) * o;
+    for (int j = threadIdx.x; j < o; j += blockDim.x) {
+        const int hi = max(i, j), lo = min(i, j);
+        out[j] = (i == j ? 1.0 : 0.70710678118654752440) * in[(int64_t)hi * (hi + 1) / 2 + lo];
+    }
+}
+
 // out[r][c] = sum_z part[z][r][c] for c <= r, z in order.
 __global__ void sum_lower_kernel(const double* part, int S, int64_t stride, int n, double* out) {
     const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -493,6 +514,14 @@ __global__ __launch_bounds__(256) void gamma_row_kernel(const double* Bc, int64_
 
 namespace ri {
 
+hipError_t pack_ij(const double* B, int o, int np, double* Bp, hipStream_t st) {
+    pack_ij_kernel<<<dim3(o, np), o > 64 ? 128 : 64, 0, st>>>(B, o, Bp);
+    return hipGetLastError();
+}
+hipError_t unpack_ij(const double* Xp, int o, int np, double* Xi, hipStream_t st) {
+    unpack_ij_kernel<<<dim3(o, np), o > 64 ? 128 : 64, 0, st>>>(Xp, o, Xi);
+    return hipGetLastError();
+}
 hipError_t grad_one_electron(const ri_system* s, const double* D, const double* W, double* part, hipStream_t st) {
     if (s->n_centres > MAXC) return hipErrorInvalidValue;
     g1e_kernel<<<GRAD_BLOCKS, 256, 3 * s->n_centres * sizeof(double), st>>>(s->xyz, s->Z, s->n_centres, s->fn_centre, s->fn_exp, s->n_fn, D, W, part);
