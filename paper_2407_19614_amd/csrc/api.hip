@@ -242,7 +242,7 @@ EnergyWS carve_energy(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, in
 int energy_layout(const Prec& p) { return p.fin && !is_bf16(p.base) ? RI_FP64 : p.base; }
 bool energy_fin_slab(const Prec& p) { return p.fin && is_bf16(p.base); }
 
-struct GradWS { double *D, *W, *T1, *dpair, *gamma, *c, *Bij, *Xi, *Zx, *part, *Cp, *WY; int32_t* rows; void* Xt; float* Xt32; SlabWS sw; ri::XSparse xs; };
+struct GradWS { double *D, *W, *T1, *dpair, *gamma, *c, *Bij, *Xi, *Zx, *part, *Cp, *WY, *pscr; int32_t* rows; void* Xt; float* Xt32; SlabWS sw; ri::XSparse xs; };
 GradWS carve_grad(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int n_centres, int prec,
                   bool comp = false) {
     GradWS w;
@@ -263,6 +263,7 @@ GradWS carve_grad(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int n_
     w.Cp = a.take<double>(ri::cpad_elems(N, n_occ));
     w.WY = a.take<double>((int64_t)ri::grad_slab(N, n_aux) * N * N);   // U^P C^T, one slab of P
     w.rows = a.take<int32_t>(N + 1);
+    w.pscr = a.take<double>(ri::grad_pair_elems(n_pairs));
     // X^T for B_ij, reused afterwards for U^P = C Xi^P ([n_aux][N][n_occ])
     w.Xt = a.take<char>((int64_t)n_aux * n_occ * Npad * 8 + 8);
     w.Xt32 = prec == RI_FP32 ? a.take<float>((int64_t)n_aux * n_occ * Npad) : nullptr;
@@ -885,7 +886,7 @@ int32_t ri_gradient(const ri_system* sys, const int32_t* pairs, int64_t n_pairs,
     HIPC(ri::u_products(C, w.Xi, N, no, na, U, st));
     HIPC(fk.close());   // c and the one-electron rows are ready on st from here
     HIPC(ri::grad_metric(sys, w.Zx, w.c, w.part + GB * rowlen, st));
-    HIPC(ri::grad_three_centre(sys, pairs, n_pairs, U, C, no, w.D, w.c, w.WY, w.rows, w.part + 2 * GB * rowlen, st));
+    HIPC(ri::grad_three_centre(sys, pairs, n_pairs, U, C, no, w.D, w.c, w.WY, w.rows, w.pscr, w.part + 2 * GB * rowlen, st));
     HIPC(ri::grad_nuclear(sys, w.part + 3 * GB * rowlen, st));
     HIPC(ri::grad_reduce(w.part, 3 * GB + 1, nc, grad, st));
     return RI_OK;

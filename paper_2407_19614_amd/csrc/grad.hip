@@ -67,6 +67,96 @@ __device__ __forceinline__ void boys_f01(double t, double& f0, double& f1) {
     }
 }
 
+// F0(t) and F1(t) together, from a table of F_0 .. F_9 at multiples of 1/8 below
+// t = 40: the Taylor expansions F_m(t) = sum_k F_{m+k}(t_j) (t_j - t)^k / k! to k = 8
+// about the nearest point (|t_j - t| <= 1/16: the first omitted term is below
+// 6e-18 of F_m); t >= 40 as above.  With the table rounded from double-double, F0
+// is off by at most 2.0e-16 (rms 6e-17) and F1 by 2.1e-16 (7e-17), where the
+// direct forms are off by 2.9e-16 (8e-17) and 4.9e-16 (1.1e-16).  The direct
+// forms took most of the three-centre kernel's time (N = 1000: 3.5 -> 1.75 ms);
+// the one-electron kernel keeps them: its blocks' copies of the table cost what
+// they give (0.68 against 0.89 ms at N = 1000).
+constexpr int BT_N = 322, BT_M = 11;               // points 0 .. 321; ten values in an odd row length
+
+struct dd {
+    double h, l;
+};
+__device__ __forceinline__ dd dd_fast(double h, double l) {
+#pragma clang fp contract(off)
+    const double s = h + l;
+    return {s, l - (s - h)};
+}
+__device__ __forceinline__ dd dd_add(dd a, dd b) {
+    const double s = a.h + b.h, v = s - a.h;
+    return dd_fast(s, (a.h - (s - v)) + (b.h - v) + (a.l + b.l));
+}
+__device__ __forceinline__ dd dd_mul(dd a, dd b) {
+#pragma clang fp contract(off)
+    const double p = a.h * b.h;
+    return dd_fast(p, fma(a.h, b.h, -p) + (a.h * b.l + a.l * b.h));
+}
+__device__ __forceinline__ dd dd_div(dd a, double c) {
+#pragma clang fp contract(off)
+    const double rc = 1.0 / c, q = a.h * rc;
+    return dd_fast(q, (fma(-q, c, a.h) + a.l) * rc);
+}
+
+// Row j of the table, t = j / 8: F_9 from its series exp(-t) sum_k (2t)^k / (19 *
+// 21 ... (2k + 19)), all terms positive, then the downward relation F_{m-1} =
+// (2t F_m + exp(-t)) / (2m - 1), in double-double.
+__device__ void boys_row(int j, double* T) {
+    const dd x = {0.25 * j, 0.0};
+    dd term = {1.0, 0.0}, sum, e = {1.0, 0.0}, b = {0x1.c3d6a24ed8222p-1, -0x1.e1e0a76cb0685p-55};   // b = exp(-1/8)
+    for (int k = j; k > 0; k >>= 1) {
+        if (k & 1) e = dd_mul(e, b);
+        b = dd_mul(b, b);
+    }
+    term = dd_div(term, 19.0);
+    sum = term;
+    for (int k = 1; k < 200; ++k) {
+        term = dd_div(dd_mul(term, x), 2.0 * k + 19.0);
+        sum = dd_add(sum, term);
+        if (term.h < 1e-22 * sum.h) break;
+    }
+    dd f = dd_mul(e, sum);
+    T[9] = f.h;
+    for (int m = 9; m > 0; --m) {
+        f = dd_div(dd_add(dd_mul(x, f), e), 2.0 * m - 1.0);
+        T[m - 1] = f.h;
+    }
+    T[10] = 0.0;
+}
+
+__device__ __forceinline__ void boys_f01(const double* T, double t, double& f0, double& f1) {
+    const int j = (int)fma(fmin(t, 40.0), 8.0, 0.5);
+    const double* f = T + j * BT_M;
+    const double d = fma((double)j, 0.125, -t);
+    double a = f[8], b = f[9];
+#pragma unroll
+    for (int k = 8; k > 0; --k) {
+        const double x = d * (1.0 / k);
+        a = fma(x, a, f[k - 1]);
+        b = fma(x, b, f[k]);
+    }
+    f0 = a;
+    f1 = b;
+    if (t >= 40.0) {
+        f0 = 0.88622692545275801365 / sqrt(t);
+        f1 = f0 / (2.0 * t);
+    }
+}
+
+// r = 1 / sqrt(x) and i = 1 / x to rounding: the hardware estimate, a Newton step,
+// and one more on the exact residual 1 - x r^2
+__device__ __forceinline__ void rsqrt_rcp(double x, double& r, double& i) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    const double h = x * y, l = fma(x, y, -h);
+    r = fma(0.5 * y, fma(-l, y, fma(-h, y, 1.0)), y);
+    const double z = r * r;
+    i = fma(z, fma(-x, z, 1.0), z);
+}
+
 // Sum over the wave; every lane receives the total.
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -181,38 +271,79 @@ __global__ __launch_bounds__(256) void g2c_kernel(const double* xyz, const int32
     flush(g, 3 * nc, part);
 }
 
-// sum_P sum_pairs w Y^P_mu_nu (mu nu|P)',  Y = c_P D_mu_nu - 2 (U^P C^T)_mu_nu,
-// U^P = C Xi^P.  Auxiliary indices P0 .. P0 + np - 1: WY[P - P0][q] =
-// (U^P C^T)_mu_nu of pair q; contributions are added to the block's partial
-// row.  Work items are (block of 256 pairs, chunk of G3_PC auxiliaries): one
-// pair per thread, its Gaussian product and prefactor formed once, then the
-// chunk's auxiliaries in turn (their exponents, normalisation and centres
-// staged in LDS).  The pair's two centres accumulate in registers; the
-// auxiliary's centre is the same for the whole wave at each step, so its
-// share is summed over the wave before one LDS add.  g holds 3 * nc doubles
-// of dynamic LDS.
+// Constants of each pair for the derivative integrals, as PC_N arrays over the
+// pairs, and its two centres; the first two blocks make the table T.
+constexpr int PC_P = 0, PC_K = 1, PC_X = 2, PC_M = 5, PC_A = 6, PC_B = 7, PC_D = 8, PC_W = 11, PC_N = 12;
+
+__global__ __launch_bounds__(256) void pair_consts_kernel(const double* __restrict__ xyz,
+                                                          const int32_t* __restrict__ fc,
+                                                          const double* __restrict__ fe,
+                                                          const int32_t* __restrict__ pairs, int64_t n_pairs,
+                                                          const double* __restrict__ D, int N,
+                                                          double* __restrict__ pc, int2* __restrict__ ctr,
+                                                          double* __restrict__ T) {
+    const int64_t q = (blockIdx.x - 2ll) * 256 + threadIdx.x;
+    if (q < 0 && q + 512 < BT_N) boys_row((int)(q + 512), T + (q + 512) * BT_M);
+    if (q < 0 || q >= n_pairs) return;
+    const int mu = pairs[2 * q], nu = pairs[2 * q + 1], ca = fc[mu], cb = fc[nu];
+    const double a = fe[mu], b = fe[nu], p = a + b, ip = 1.0 / p, m = a * b * ip;
+    const double* A = xyz + 3 * ca;
+    const double* B = xyz + 3 * cb;
+    const double dx = A[0] - B[0], dy = A[1] - B[1], dz = A[2] - B[2];
+    auto put = [&](int k, double v) { pc[k * n_pairs + q] = v; };
+    put(PC_P, p);
+    put(PC_K, norm_s(a) * norm_s(b) * exp(-m * (dx * dx + dy * dy + dz * dz)) * TWO_PI_52 * ip);
+    put(PC_X, (a * A[0] + b * B[0]) * ip);
+    put(PC_X + 1, (a * A[1] + b * B[1]) * ip);
+    put(PC_X + 2, (a * A[2] + b * B[2]) * ip);
+    put(PC_M, m);
+    put(PC_A, a * ip);
+    put(PC_B, b * ip);
+    put(PC_D, dx);
+    put(PC_D + 1, dy);
+    put(PC_D + 2, dz);
+    put(PC_W, (mu == nu ? 1.0 : 2.0) * D[(int64_t)mu * N + nu]);
+    ctr[q] = make_int2(mu == nu ? ~ca : ca, cb);   // the diagonal's weight is 1, the others' 2
+}
+
+// sum_P sum_pairs w Y^P_mu_nu (mu nu|P)',  Y = c_P D_mu_nu - 2 (U^P C^T)_mu_nu, for
+// auxiliary indices P0 .. P0 + np - 1 (WY[P - P0][q] = (U^P C^T)_mu_nu of pair q),
+// added to the block's partial row.  Work items are (bpi blocks of 256 pairs,
+// chunk of G3_PC auxiliaries), a pair per thread, the chunk's auxiliaries in
+// turn (their constants staged in LDS).  With e = P - R_aux and g = 2 w c0 F1, an
+// entry adds I y to s and g y e to G: the pair's centres take -2 m s (A - B) -
+// (a/p) G and +2 m s (A - B) - (b/p) G at the end of the chunk, and the
+// auxiliary's centre +G, kept in registers over the item's pairs and summed over
+// the wave once (a wave sum per entry cost 36 lane exchanges of the some 100
+// instructions that an entry takes).  Bound by FP64 throughput and the table's
+// LDS reads; an entry at a time keeps to the registers (all eight
+// unrolled together: 91 spilled, 3.05 ms; 1.75 ms so, and 220 -> 153 us at N = 300).  g holds 3 * nc
+// doubles of dynamic LDS.
 constexpr int G3_PC = 8;
 
-__global__ __launch_bounds__(256) void g3c_kernel(const double* xyz, const int32_t* fc, const double* fe,
-                                                  const int32_t* ac, const double* ae, int P0, int np, int nc,
-                                                  const int32_t* pairs, int64_t n_pairs, const double* WY,
-                                                  const double* D, int N, const double* cv, double* part) {
+__global__ __launch_bounds__(256, 2) void g3c_kernel(const double* __restrict__ xyz, const int32_t* __restrict__ ac,
+                                                     const double* __restrict__ ae, int P0, int np, int nc,
+                                                     int64_t n_pairs, int bpi, const double* __restrict__ pc,
+                                                     const int2* __restrict__ ctr, const double* __restrict__ WY,
+                                                     const double* __restrict__ cv, const double* __restrict__ bt, double* __restrict__ part) {
     extern __shared__ double g[];
+    __shared__ double T[BT_N * BT_M];
     __shared__ double sp[G3_PC][6];   // alpha, norm(alpha) / alpha, centre (3), c_P
     __shared__ int sc[G3_PC];
     const int tid = threadIdx.x, lane = tid & 63;
     for (int i = tid; i < 3 * nc; i += 256) g[i] = 0.0;
-    const int64_t pb = (n_pairs + 255) / 256;
+    for (int i = tid; i < BT_N * BT_M; i += 256) T[i] = bt[i];
+    const int64_t pb = (n_pairs + 256ll * bpi - 1) / (256ll * bpi);
     const int64_t items = pb * ((np + G3_PC - 1) / G3_PC);
     for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
         const int pc0 = (int)(it / pb) * G3_PC, pcn = min(G3_PC, np - pc0);
-        const int64_t q = (it % pb) * 256 + tid;
-        __syncthreads();   // the previous item's reads of sp are done (g zeroed before the first)
-        if (tid < pcn) {
-            const int P = P0 + pc0 + tid, c = ac[P];
+        __syncthreads();   // the previous item's reads of sp are done (g and T ready before the first)
+        if (tid < G3_PC) {
+            // past the last auxiliary: its own values again, with zero weight
+            const int P = P0 + min(pc0 + tid, np - 1), c = ac[P];
             const double al = ae[P];
             sp[tid][0] = al;
-            sp[tid][1] = norm_s(al) / al;
+            sp[tid][1] = tid < pcn ? norm_s(al) / al : 0.0;
             sp[tid][2] = xyz[3 * c];
             sp[tid][3] = xyz[3 * c + 1];
             sp[tid][4] = xyz[3 * c + 2];
@@ -220,46 +351,52 @@ __global__ __launch_bounds__(256) void g3c_kernel(const double* xyz, const int32
             sc[tid] = c;
         }
         __syncthreads();
-        const bool live = q < n_pairs;
-        int mu = 0, nu = 0;
-        if (live) {
-            mu = pairs[2 * q];
-            nu = pairs[2 * q + 1];
+        double ga[G3_PC][3];
+#pragma unroll
+        for (int k = 0; k < G3_PC; ++k) ga[k][0] = ga[k][1] = ga[k][2] = 0.0;
+        for (int blk = 0; blk < bpi; ++blk) {
+            const int64_t qq = ((it % pb) * bpi + blk) * 256 + tid;
+            if (((it % pb) * bpi + blk) * 256 >= n_pairs) break;
+            const bool live = qq < n_pairs;
+            const int64_t q = live ? qq : n_pairs - 1;
+            auto con = [&](int k) { return pc[k * n_pairs + q]; };
+            const int2 cc = ctr[q];
+            const double p = con(PC_P), kp = live ? con(PC_K) : 0.0;   // lanes past the pairs add zeros
+            const double Px = con(PC_X), Py = con(PC_X + 1), Pz = con(PC_X + 2), dw = con(PC_W);
+            const double w2 = cc.x < 0 ? 2.0 : 4.0;
+            const double* wy = WY + (int64_t)pc0 * n_pairs + q;
+            double s = 0.0, gx = 0.0, gy = 0.0, gz = 0.0, yc[G3_PC];
+#pragma unroll
+            for (int k = 0; k < G3_PC; ++k) yc[k] = wy[(int64_t)min(k, pcn - 1) * n_pairs];
+#pragma unroll
+            for (int k = 0; k < G3_PC; ++k) {
+                __builtin_amdgcn_sched_barrier(0);   // an entry at a time, to stay in registers
+                const double al = sp[k][0];
+                const double y = fma(sp[k][5], dw, -w2 * yc[k]);
+                double r, isa;
+                rsqrt_rcp(p + al, r, isa);
+                const double w = p * al * isa;
+                const double ex = Px - sp[k][2], ey = Py - sp[k][3], ez = Pz - sp[k][4];
+                double F0, F1;
+                boys_f01(T, w * (ex * ex + ey * ey + ez * ez), F0, F1);
+                const double c0 = kp * sp[k][1] * r * y;
+                s = fma(c0, F0, s);
+                const double gg = 2.0 * w * c0 * F1;
+                const double vx = gg * ex, vy = gg * ey, vz = gg * ez;
+                gx += vx; gy += vy; gz += vz;
+                ga[k][0] += vx; ga[k][1] += vy; ga[k][2] += vz;
+            }
+            if (live) {
+                const double f = 2.0 * con(PC_M) * s, ap = con(PC_A), bp = con(PC_B);
+                const double fx = f * con(PC_D), fy = f * con(PC_D + 1), fz = f * con(PC_D + 2);
+                lds_add3(g, cc.x < 0 ? ~cc.x : cc.x, -fx - ap * gx, -fy - ap * gy, -fz - ap * gz);
+                lds_add3(g, cc.y, fx - bp * gx, fy - bp * gy, fz - bp * gz);
+            }
         }
-        const double wq = live ? (mu == nu ? 1.0 : 2.0) : 0.0;   // lanes past the pairs add zeros
-        const double dmn = D[(int64_t)mu * N + nu];
-        const double a = fe[mu], b = fe[nu];
-        const int ca = fc[mu], cb = fc[nu];
-        const double* A = xyz + 3 * ca;
-        const double* B = xyz + 3 * cb;
-        const double p = a + b, ip = 1.0 / p, m = a * b * ip;
-        const double dx = A[0] - B[0], dy = A[1] - B[1], dz = A[2] - B[2];
-        // c0 = norm(a) norm(b) norm(alpha) exp(-m |A-B|^2) 2 pi^{5/2} / (p alpha sqrt(p + alpha))
-        const double kp = norm_s(a) * norm_s(b) * exp(-m * (dx * dx + dy * dy + dz * dz)) * TWO_PI_52 * ip;
-        const double Px = (a * A[0] + b * B[0]) * ip, Py = (a * A[1] + b * B[1]) * ip, Pz = (a * A[2] + b * B[2]) * ip;
-        const double* wy = WY + (int64_t)pc0 * n_pairs + (live ? q : 0);
-        double gax = 0, gay = 0, gaz = 0, gbx = 0, gby = 0, gbz = 0;
-        for (int k = 0; k < pcn; ++k) {
-            const double al = sp[k][0];
-            const double y = (sp[k][5] * dmn - 2.0 * wy[(int64_t)k * n_pairs]) * wq;
-            const double isa = 1.0 / (p + al), w = p * al * isa;
-            const double ex = Px - sp[k][2], ey = Py - sp[k][3], ez = Pz - sp[k][4];
-            double F0, F1;
-            boys_f01(w * (ex * ex + ey * ey + ez * ez), F0, F1);
-            const double c0 = kp * sp[k][1] * sqrt(isa);
-            const double I = c0 * F0, gg = c0 * F1 * 2.0 * w;
-            // dI/dA = -2 m (A-B) I - gg (a/p) (P-R);  dI/dB = 2 m (A-B) I - gg (b/p) (P-R)
-            const double t1 = -2.0 * m * I * y, ta = -gg * a * ip * y, tb = -gg * b * ip * y;
-            const double Ax = t1 * dx + ta * ex, Ay = t1 * dy + ta * ey, Az = t1 * dz + ta * ez;
-            const double Bx = -t1 * dx + tb * ex, By = -t1 * dy + tb * ey, Bz = -t1 * dz + tb * ez;
-            gax += Ax; gay += Ay; gaz += Az;
-            gbx += Bx; gby += By; gbz += Bz;
-            const double sx = wave_sum(Ax + Bx), sy = wave_sum(Ay + By), sz = wave_sum(Az + Bz);
-            if (lane == 0) lds_add3(g, sc[k], -sx, -sy, -sz);
-        }
-        if (live) {
-            lds_add3(g, ca, gax, gay, gaz);
-            lds_add3(g, cb, gbx, gby, gbz);
+#pragma unroll
+        for (int k = 0; k < G3_PC; ++k) {
+            const double sx = wave_sum(ga[k][0]), sy = wave_sum(ga[k][1]), sz = wave_sum(ga[k][2]);
+            if (lane == 0) lds_add3(g, sc[k], sx, sy, sz);
         }
     }
     flush_add(g, 3 * nc, part);
@@ -579,13 +716,19 @@ hipError_t u_products(const double* C, const double* Xi, int N, int K, int np, d
 }
 hipError_t grad_three_centre(const ri_system* s, const int32_t* pairs, int64_t n_pairs, const double* U,
                              const double* C, int n_occ, const double* D, const double* c, double* WY, int32_t* rows,
-                             double* part, hipStream_t st) {
+                             double* pscratch, double* part, hipStream_t st) {
     if (s->n_centres > MAXC) return hipErrorInvalidValue;
     const int N = s->n_fn, na = s->n_aux;
     const size_t lds = 3 * s->n_centres * sizeof(double);
     RI_TRY(fill(part, 0.0, (int64_t)GRAD_BLOCKS * 3 * s->n_centres, st));
     if (n_pairs == 0) return hipSuccess;
     pair_rows_kernel<<<(N + 256) / 256, 256, 0, st>>>(pairs, n_pairs, N, rows);
+    RI_TRY(hipGetLastError());
+    double* pc = pscratch;
+    int2* ctr = (int2*)(pc + PC_N * n_pairs);
+    double* bt = (double*)(ctr + n_pairs);
+    pair_consts_kernel<<<(unsigned)((n_pairs + 255) / 256 + 2), 256, 0, st>>>(s->xyz, s->fn_centre, s->fn_exp, pairs,
+                                                                              n_pairs, D, N, pc, ctr, bt);
     RI_TRY(hipGetLastError());
     // auxiliaries at a time that WY holds (at least twice grad_slab: a pair counts once)
     const int ns = (int)std::min<int64_t>(na, (int64_t)grad_slab(N, na) * N * N / n_pairs);
@@ -604,13 +747,16 @@ hipError_t grad_three_centre(const ri_system* s, const int32_t* pairs, int64_t n
             }
             RI_TRY(hipGetLastError());
         }
-        g3c_kernel<<<GRAD_BLOCKS, 256, lds, st>>>(
-            s->xyz, s->fn_centre, s->fn_exp, s->aux_centre, s->aux_exp, P0, np, s->n_centres, pairs, n_pairs, WY, D,
-            N, c, part);
+        // blocks of pairs per item: as many as leave every workgroup two items
+        const int64_t one = (n_pairs + 255) / 256 * ((np + G3_PC - 1) / G3_PC);
+        const int bpi = (int)std::max<int64_t>(1, std::min<int64_t>(8, one / (2 * GRAD_BLOCKS)));
+        g3c_kernel<<<GRAD_BLOCKS, 256, lds, st>>>(s->xyz, s->aux_centre, s->aux_exp, P0, np, s->n_centres, n_pairs, bpi, pc,
+                                                  ctr, WY, c, bt, part);
         RI_TRY(hipGetLastError());
     }
     return hipSuccess;
 }
+int64_t grad_pair_elems(int64_t n_pairs) { return (PC_N + 1) * n_pairs + BT_N * BT_M; }
 hipError_t grad_nuclear(const ri_system* s, double* part, hipStream_t st) {
     gnuc_kernel<<<1, 256, 0, st>>>(s->xyz, s->Z, s->n_centres, part);
     return hipGetLastError();

@@ -190,14 +190,15 @@ hipError_t grad_metric_z(const double* Xi, int n_aux, int64_t K, double* tmp, in
 // Three-centre term, U^P = C Xi^P, [n_aux][N][n_occ].  (U^P C^T)_mu_nu is formed
 // on MFMA at the significant pairs, for as many auxiliary indices at a time as
 // WY holds (workspace of grad_slab * N * N doubles), and the derivative kernel
-// reads it there.  rows: N + 1 ints of scratch.
+// reads it there.  rows: N + 1 ints of scratch; pscratch: grad_pair_elems doubles.
 int grad_slab(int N, int n_aux);
 // U[p] = C Xi^p for p < np: C [N][K], Xi [np][K][K] with symmetric blocks,
 // U [np][N][K].
 hipError_t u_products(const double* C, const double* Xi, int N, int K, int np, double* U, hipStream_t st);
 hipError_t grad_three_centre(const ri_system* s, const int32_t* pairs, int64_t n_pairs, const double* U,
                              const double* C, int n_occ, const double* D, const double* c, double* WY, int32_t* rows,
-                             double* part, hipStream_t st);
+                             double* pscratch, double* part, hipStream_t st);
+int64_t grad_pair_elems(int64_t n_pairs);
 hipError_t grad_nuclear(const ri_system* s, double* part, hipStream_t st);
 hipError_t grad_reduce(const double* part, int rows, int n_centres, double* grad, hipStream_t st);
 hipError_t gamma_only(const double* Bc, const int32_t* pairs, int64_t n_pairs, int n_aux, int n_occ,
