@@ -23,24 +23,44 @@ __global__ void pair_map_kernel(const int32_t* pairs, int64_t n_pairs, int N, in
     map[(int64_t)pairs[2 * q] * N + pairs[2 * q + 1]] = (int32_t)q;
 }
 
-// B[P][tile][r*64+c] = Bc[P][pair(64I+r, 64J+c)] or 0, for PB consecutive P
-// per workgroup so that each pair-map lookup serves all of them.
-constexpr int PACK_PB = 4;
+// B[P][tile][r*64+c] = Bc[P][pair(64I+r, 64J+c)] or 0, for PACK_PB consecutive P
+// per workgroup so that each pair-map lookup serves all of them.  Bound by the
+// stores of B: a thread takes two neighbouring columns, so that it has 2 *
+// PACK_PB loads in flight and stores whole pairs of elements, and a wave without a
+// significant pair only stores.  An element at a time over four P took
+// 26 us where this takes 18 (N = 170), and 480 for 411 beside the solve (N = 1000).
+constexpr int PACK_PB = 8;
 template <typename T>
-__global__ __launch_bounds__(256) void pack_kernel(const double* Bc, int64_t n_pairs, const int32_t* map,
-                                                   int N, int64_t ntl, int n_aux, T* B) {
-    const int t = blockIdx.x, P0 = blockIdx.y * PACK_PB;
+__global__ __launch_bounds__(256) void pack_kernel(const double* __restrict__ Bc, int64_t n_pairs,
+                                                   const int32_t* __restrict__ map, int N, int64_t ntl, int n_aux,
+                                                   T* __restrict__ B) {
+    struct T2 {   // aligned as T: B need not start on a multiple of two elements
+        T x, y;
+    };
+    const int t = blockIdx.x, P0 = blockIdx.y * PACK_PB, np = min(PACK_PB, n_aux - P0);
     int I, J;
     tile_ij(t, I, J);
-    for (int e = threadIdx.x; e < 4096; e += 256) {
+    const double* row = Bc + (int64_t)P0 * n_pairs;
+    T* out = B + ((int64_t)P0 * ntl + t) * 4096;
+    for (int e = 2 * threadIdx.x; e < 4096; e += 512) {
         const int mu = 64 * I + (e >> 6), nu = 64 * J + (e & 63);
-        int32_t q = -1;
-        if (mu < N && nu < N) q = map[(int64_t)max(mu, nu) * N + min(mu, nu)];
+        int32_t q[2];
 #pragma unroll
-        for (int p = 0; p < PACK_PB; ++p) {
-            const int P = P0 + p;
-            if (P < n_aux) B[((int64_t)P * ntl + t) * 4096 + e] = (T)(q >= 0 ? Bc[(int64_t)P * n_pairs + q] : 0.0);
+        for (int c = 0; c < 2; ++c)
+            q[c] = (mu < N && nu + c < N) ? map[(int64_t)max(mu, nu + c) * N + min(mu, nu + c)] : -1;
+        double v[PACK_PB][2];
+#pragma unroll
+        for (int p = 0; p < PACK_PB; ++p) v[p][0] = v[p][1] = 0.0;
+        if (__any(q[0] >= 0 || q[1] >= 0)) {
+#pragma unroll
+            for (int p = 0; p < PACK_PB; ++p)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) v[p][c] = row[(int64_t)min(p, np - 1) * n_pairs + max(q[c], 0)];
         }
+#pragma unroll
+        for (int p = 0; p < PACK_PB; ++p)
+            if (p < np)
+                *(T2*)(out + (int64_t)p * ntl * 4096 + e) = T2{(T)(q[0] >= 0 ? v[p][0] : 0.0), (T)(q[1] >= 0 ? v[p][1] : 0.0)};
     }
 }
 
@@ -737,14 +757,26 @@ __global__ void dpair_density_kernel(const int32_t* pairs, int64_t n_pairs, cons
 
 // gamma_P, one block per auxiliary index at a time (grid-stride, so a small
 // grid can run beside the exchange kernels); the sum order per P does not
-// depend on the grid.
-__global__ __launch_bounds__(256) void gamma_kernel(const double* Bc, int n_aux, int64_t n_pairs, const double* dp,
-                                                    double* gamma) {
+// depend on the grid.  Bound by the read of B_c, 8 loads in flight a thread
+// (without: 753 -> 589 us beside the split-BF16 SYRK at N = 730).
+__global__ __launch_bounds__(256) void gamma_kernel(const double* __restrict__ Bc, int n_aux, int64_t n_pairs,
+                                                    const double* __restrict__ dp, double* __restrict__ gamma) {
     __shared__ double sh[4];
     for (int P = blockIdx.x; P < n_aux; P += gridDim.x) {
         const double* row = Bc + (int64_t)P * n_pairs;
         double s = 0.0;
-        for (int64_t q = threadIdx.x; q < n_pairs; q += 256) s += row[q] * dp[q];
+        int64_t q = threadIdx.x;
+        for (; q + 7 * 256 < n_pairs; q += 8 * 256) {
+            double b[8], d[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                b[k] = row[q + k * 256];
+                d[k] = dp[q + k * 256];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s += b[k] * d[k];
+        }
+        for (; q < n_pairs; q += 256) s += row[q] * dp[q];
         for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
         if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
         __syncthreads();
