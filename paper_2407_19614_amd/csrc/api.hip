@@ -566,12 +566,15 @@ int32_t ri_metric_factor(const ri_system* sys, const int32_t* pairs, int64_t n_p
         RI_TRY(hipEventRecord(e, st));
         return hipStreamWaitEvent(ss, e, 0);
     };
-    HIPC(ri::tri_inverse_begin(Linv, na, na, ss));
-    auto inverse_step = [&](int k) -> hipError_t {
-        RI_TRY(side_waits());
-        return ri::tri_inverse_steps(L, na, na, w.dinv, Linv, na, k, k + 1, ss);
-    };
-    HIPC(ri::cholesky_inv(L, na, na, nullptr, na, w.dinv, w.bad, st, inverse_step));
+    if (side) {
+        HIPC(ri::tri_inverse_begin(Linv, na, na, ss));
+        HIPC(ri::cholesky_inv(L, na, na, nullptr, na, w.dinv, w.bad, st, [&](int k) -> hipError_t {
+            RI_TRY(side_waits());
+            return ri::tri_inverse_step(L, na, na, w.dinv, Linv, na, k, ss);
+        }));
+    } else {
+        HIPC(ri::cholesky_inv(L, na, na, Linv, na, w.dinv, w.bad, st));
+    }
     int bad = INT_MAX;
     HIPC(hipMemcpyAsync(&bad, w.bad, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPC(hipStreamSynchronize(st));

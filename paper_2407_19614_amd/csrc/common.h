@@ -266,16 +266,24 @@ hipError_t cholesky_inv(double* A, int n, int64_t lda, double* Linv, int64_t ldi
                         double* dwork, int* d_bad, hipStream_t s,
                         const std::function<hipError_t(int)>& block_done = nullptr);
 
-// Linv = L^{-1} from the factor and its diagonal-block inverses (as left by
-// cholesky_inv with Linv == nullptr).
-hipError_t tri_inverse(const double* L, int n, int64_t lda, const double* Dinv, double* Linv, int64_t ldi,
-                       hipStream_t s);
-// The same in parts, for callers that spread the launches out: begin sets
-// Linv to the identity, then steps k0 .. k1-1 (of ceil(n/64)) run in order,
-// all on one stream.
+// One product of cholesky_inv: C = alpha A op(B) + beta C, K <= 64.
+struct Gemm64 {
+    const double* A;
+    int64_t lda;
+    const double* B;
+    int64_t ldb;
+    double* C;
+    int64_t ldc;
+    int M, N, K;
+    double alpha, beta;
+};
+
+// Linv = L^{-1} in parts, for callers that run it on a stream of its own (with
+// cholesky_inv's Linv == nullptr): begin sets Linv to the identity, then steps
+// 0 .. ceil(n/64) - 1 run in order, step k once cholesky_inv's block_done(k).
 hipError_t tri_inverse_begin(double* Linv, int n, int64_t ldi, hipStream_t s);
-hipError_t tri_inverse_steps(const double* L, int n, int64_t lda, const double* Dinv, double* Linv, int64_t ldi,
-                             int k0, int k1, hipStream_t s);
+hipError_t tri_inverse_step(const double* L, int n, int64_t lda, const double* Dinv, double* Linv, int64_t ldi, int k,
+                            hipStream_t s);
 
 hipError_t fill(double* p, double v, int64_t n, hipStream_t s);
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);

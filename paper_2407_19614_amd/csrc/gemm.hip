@@ -153,6 +153,83 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(
                         C + (int64_t)bz * sC, ldc, tri, m0, n0);
 }
 
+// C = alpha A op(B) + beta C over a 64 x 64 tile with K <= 64, all of the tile's
+// operands and C loaded at once: bound by latency, of which the sliced loop above
+// waits out one per 16 of K and one for C.  Sums and rounding as there.
+template <bool TB>
+__device__ __forceinline__ void gemm_tile64_k64(double (*As)[LDP], double (*Bs)[LDP], const ri::Gemm64& p, int m0,
+                                                int n0) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32, li = lane & 15, lk = lane >> 4;
+    double ra[16], rb[16], cv[2][2][4];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int i = wave + 4 * r;   // A: row i, column lane
+        ra[r] = p.A[(int64_t)min(m0 + i, p.M - 1) * p.lda + min(lane, p.K - 1)];
+        rb[r] = TB ? p.B[(int64_t)min(n0 + i, p.N - 1) * p.ldb + min(lane, p.K - 1)]
+                   : p.B[(int64_t)min(i, p.K - 1) * p.ldb + min(n0 + lane, p.N - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int gm = min(m0 + wm + 16 * i + 4 * r + lk, p.M - 1), gn = min(n0 + wn + 16 * j + li, p.N - 1);
+                cv[i][j][r] = p.beta != 0.0 ? p.C[(int64_t)gm * p.ldc + gn] : 0.0;
+            }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int i = wave + 4 * r;
+        As[lane][i] = (m0 + i < p.M && lane < p.K) ? ra[r] : 0.0;
+        if (TB) Bs[lane][i] = (n0 + i < p.N && lane < p.K) ? rb[r] : 0.0;
+        else Bs[i][lane] = (n0 + lane < p.N && i < p.K) ? rb[r] : 0.0;
+    }
+    __syncthreads();
+    d4_t acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < p.K; k0 += BK)
+#pragma unroll
+        for (int kk = k0; kk < k0 + BK; kk += 4) {
+            const double a0 = As[kk + lk][wm + li], a1 = As[kk + lk][wm + 16 + li];
+            const double b0 = Bs[kk + lk][wn + li], b1 = Bs[kk + lk][wn + 16 + li];
+            acc[0][0] = mfma_f64(a0, b0, acc[0][0]);
+            acc[0][1] = mfma_f64(a0, b1, acc[0][1]);
+            acc[1][0] = mfma_f64(a1, b0, acc[1][0]);
+            acc[1][1] = mfma_f64(a1, b1, acc[1][1]);
+        }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int gm = m0 + wm + 16 * i + 4 * r + lk, gn = n0 + wn + 16 * j + li;
+                if (gm < p.M && gn < p.N)
+                    p.C[(int64_t)gm * p.ldc + gn] = p.alpha * acc[i][j][r] + (p.beta != 0.0 ? p.beta * cv[i][j][r] : 0.0);
+            }
+}
+
+// Two independent products with K <= 64 in one launch: p's tiles (op(B) = B^T;
+// with lower, only those not above the diagonal matter), then q's (op(B) = B).
+__global__ __launch_bounds__(256) void gemm64_pair_kernel(ri::Gemm64 p, int pt, bool lower, ri::Gemm64 q) {
+    __shared__ double As[64][LDP];
+    __shared__ double Bs[64][LDP];
+    int t = blockIdx.x;
+    if (t < pt) {
+        const int gx = (p.N + BN - 1) / BN, m0 = t / gx * BM, n0 = t % gx * BN;
+        if (lower && n0 > m0 + BM - 1) return;
+        gemm_tile64_k64<true>(As, Bs, p, m0, n0);
+    } else {
+        t -= pt;
+        const int gx = (q.N + BN - 1) / BN;
+        gemm_tile64_k64<false>(As, Bs, q, t / gx * BM, t % gx * BN);
+    }
+}
+
 // Grouped GEMM: problem g owns tiles prefix[g] .. prefix[g+1]-1 (row-major
 // over its 64 x 64 tiles); a problem whose `active` flag is 0 is skipped.
 template <bool TA, bool TB>
@@ -318,8 +395,16 @@ __global__ __launch_bounds__(64) void potrf_diag_kernel(double* A, int n, int64_
                                                          int* bad) {
     __shared__ double S[64][65];
     const int lane = threadIdx.x, o = kb * 64, nb = min(64, n - o);
-    for (int r = 0; r < 64; ++r)
-        S[r][lane] = (r < nb && lane < nb) ? A[(int64_t)(o + r) * lda + o + lane] : (r == lane ? 1.0 : 0.0);
+    // 32 rows' loads in flight (one row after the other: the kernel 33.5 us, now 27.5)
+#pragma unroll
+    for (int r0 = 0; r0 < 64; r0 += 32) {
+        double v[32];
+#pragma unroll
+        for (int r = 0; r < 32; ++r) v[r] = A[(int64_t)(o + min(r0 + r, nb - 1)) * lda + o + min(lane, nb - 1)];
+#pragma unroll
+        for (int r = 0; r < 32; ++r)
+            S[r0 + r][lane] = (r0 + r < nb && lane < nb) ? v[r] : (r0 + r == lane ? 1.0 : 0.0);
+    }
     __syncthreads();
     chol_inv64_blocked(S, nb, [&](int j) { atomicMin(bad, o + j); }, [&](int i, int c, double v) { Dinv[i * 64 + c] = v; });
     __syncthreads();
@@ -534,32 +619,50 @@ hipError_t gemm_f64(bool ta, bool tb, int M, int N, int K, double alpha, const d
     return hipGetLastError();
 }
 
+// p (C += A B^T, K <= 64) and q (A B) side by side; either may be empty (M = 0)
+static hipError_t gemm64_pair(const Gemm64& p, bool lower, const Gemm64& q, hipStream_t s) {
+    auto tiles = [](const Gemm64& g) { return ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN); };
+    const int pt = tiles(p), n = pt + tiles(q);
+    if (n == 0) return hipSuccess;
+    gemm64_pair_kernel<<<n, 256, 0, s>>>(p, pt, lower, q);
+    return hipGetLastError();
+}
+
+// Step k of L X = I by blocks, X_k = Dinv_k (I_k - L_{k,<k} X_{<k}): row block k of
+// X, then its share of the rows below
+static Gemm64 inverse_row(const double* dwork, double* Linv, int64_t ldi, int n, int k) {
+    const int o = k * 64, w = min(64, n - o);
+    double* Xk = Linv + (int64_t)o * ldi;
+    return {dwork + (int64_t)k * 4096, 64, Xk, ldi, Xk, ldi, w, o + w, w, 1.0, 0.0};
+}
+static Gemm64 inverse_rest(const double* A, int64_t lda, double* Linv, int64_t ldi, int n, int k) {
+    const int o = k * 64, w = min(64, n - o);
+    return {A + (int64_t)(o + w) * lda + o, lda, Linv + (int64_t)o * ldi, ldi, Linv + (int64_t)(o + w) * ldi, ldi,
+            n - o - w, o + w, w, -1.0, 1.0};
+}
+
+// Each step's panel and row block of the inverse are one launch, the trailing
+// updates of both another: small matrices are bound by the chain of launches
+// (four products a step, a launch each: a setup of N_aux = 510 850 -> 730 us).
 hipError_t cholesky_inv(double* A, int n, int64_t lda, double* Linv, int64_t ldi, double* dwork,
                         int* d_bad, hipStream_t s, const std::function<hipError_t(int)>& block_done) {
     const int nb = (n + 63) / 64;
+    if (Linv) RI_TRY(tri_inverse_begin(Linv, n, ldi, s));
     for (int k = 0; k < nb; ++k) {
         const int o = k * 64, w = min(64, n - o), rest = n - o - w;
+        double* panel = A + (int64_t)(o + w) * lda + o;
         potrf_diag_kernel<<<1, 64, 0, s>>>(A, n, lda, k, dwork + (int64_t)k * 4096, d_bad);
         RI_TRY(hipGetLastError());
-        if (rest > 0) {
-            double* panel = A + (int64_t)(o + w) * lda + o;
-            // panel <- panel * Dinv^T  (rows below the diagonal block)
-            RI_TRY(gemm_f64(false, true, rest, w, w, 1.0, panel, lda, 0, dwork + (int64_t)k * 4096, 64, 0,
-                            0.0, panel, lda, 0, 1, 0, 0, s));
-        }
+        // panel <- panel * Dinv^T  (rows below the diagonal block)
+        RI_TRY(gemm64_pair({panel, lda, dwork + (int64_t)k * 4096, 64, panel, lda, rest, w, w, 1.0, 0.0}, false,
+                           Linv ? inverse_row(dwork, Linv, ldi, n, k) : Gemm64{}, s));
         if (block_done) RI_TRY(block_done(k));
-        if (rest > 0) {
-            double* panel = A + (int64_t)(o + w) * lda + o;
-            // trailing lower update
-            double* trail = A + (int64_t)(o + w) * lda + o + w;
-            RI_TRY(gemm_f64(false, true, rest, rest, w, -1.0, panel, lda, 0, panel, lda, 0, 1.0, trail,
-                            lda, 0, 1, 0, 1, s));
-        }
+        // trailing lower update
+        RI_TRY(gemm64_pair({panel, lda, panel, lda, panel + w, lda, rest, rest, w, -1.0, 1.0}, true,
+                           Linv ? inverse_rest(A, lda, Linv, ldi, n, k) : Gemm64{}, s));
     }
     zero_upper_kernel<<<nblk((int64_t)n * n), 256, 0, s>>>(A, n, lda);
-    RI_TRY(hipGetLastError());
-    if (!Linv) return hipSuccess;
-    return tri_inverse(A, n, lda, dwork, Linv, ldi, s);
+    return hipGetLastError();
 }
 
 hipError_t tri_inverse_begin(double* Linv, int n, int64_t ldi, hipStream_t s) {
@@ -567,25 +670,10 @@ hipError_t tri_inverse_begin(double* Linv, int n, int64_t ldi, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t tri_inverse_steps(const double* A, int n, int64_t lda, const double* dwork, double* Linv, int64_t ldi,
-                             int k0, int k1, hipStream_t s) {
-    // Solve L X = I by blocks: X_k = Dinv_k (I_k - L_{k,<k} X_{<k}).
-    for (int k = k0; k < k1; ++k) {
-        const int o = k * 64, w = min(64, n - o), rest = n - o - w, cols = o + w;
-        double* Xk = Linv + (int64_t)o * ldi;
-        RI_TRY(gemm_f64(false, false, w, cols, w, 1.0, dwork + (int64_t)k * 4096, 64, 0, Xk, ldi, 0, 0.0,
-                        Xk, ldi, 0, 1, 0, 0, s));
-        if (rest > 0)
-            RI_TRY(gemm_f64(false, false, rest, cols, w, -1.0, A + (int64_t)(o + w) * lda + o, lda, 0, Xk,
-                            ldi, 0, 1.0, Linv + (int64_t)(o + w) * ldi, ldi, 0, 1, 0, 0, s));
-    }
-    return hipSuccess;
-}
-
-hipError_t tri_inverse(const double* A, int n, int64_t lda, const double* dwork, double* Linv, int64_t ldi,
-                       hipStream_t s) {
-    RI_TRY(tri_inverse_begin(Linv, n, ldi, s));
-    return tri_inverse_steps(A, n, lda, dwork, Linv, ldi, 0, (n + 63) / 64, s);
+hipError_t tri_inverse_step(const double* A, int n, int64_t lda, const double* dwork, double* Linv, int64_t ldi, int k,
+                            hipStream_t s) {
+    RI_TRY(gemm64_pair({}, false, inverse_row(dwork, Linv, ldi, n, k), s));
+    return gemm64_pair({}, false, inverse_rest(A, lda, Linv, ldi, n, k), s);
 }
 
 // Recursive form: B1 = L11^{-1} B1, B2 -= L21 B1, B2 = L22^{-1} B2, splitting
