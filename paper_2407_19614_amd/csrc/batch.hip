@@ -149,12 +149,32 @@ __global__ __launch_bounds__(256) void energy_conv_b(const MolDesc* d, int n_mol
     __shared__ double sh[4];
     const int64_t n = (int64_t)m.N * m.N;
     double a = 0.0, b = 0.0, c = 0.0, e = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += 256) {
-        double dd = m.D[i];
-        a += dd * m.H[i];
-        b += dd * m.J[i];
-        c += dd * m.K[i];
-        e = fmax(e, fabs(m.E[i]));
+    const double *D = m.D, *H = m.H, *J = m.J, *K = m.K, *Er = m.E;
+    int64_t i = threadIdx.x;
+    for (; i + 3 * 256 < n; i += 4 * 256) {   // four elements' loads in flight: 627 -> 264 us for 60 molecules
+        double v[4][5];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k][0] = D[i + 256 * k];
+            v[k][1] = H[i + 256 * k];
+            v[k][2] = J[i + 256 * k];
+            v[k][3] = K[i + 256 * k];
+            v[k][4] = Er[i + 256 * k];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            a += v[k][0] * v[k][1];
+            b += v[k][0] * v[k][2];
+            c += v[k][0] * v[k][3];
+            e = fmax(e, fabs(v[k][4]));
+        }
+    }
+    for (; i < n; i += 256) {
+        const double dd = D[i];
+        a += dd * H[i];
+        b += dd * J[i];
+        c += dd * K[i];
+        e = fmax(e, fabs(Er[i]));
     }
     a = block_sum256(a, sh);
     b = block_sum256(b, sh);
@@ -242,7 +262,18 @@ __global__ __launch_bounds__(256) void diis_dots_b(const MolDesc* d, int n_mol) 
     const double* y = m.dE[sk];
     const int64_t n = (int64_t)m.N * m.N;
     double s = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += 256) s += x[i] * y[i];
+    int64_t i = threadIdx.x;
+    for (; i + 7 * 256 < n; i += 8 * 256) {   // eight elements' loads in flight: 491 -> 155 us for 60 molecules
+        double u[8], v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            u[q] = x[i + 256 * q];
+            v[q] = y[i + 256 * q];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += u[q] * v[q];
+    }
+    for (; i < n; i += 256) s += x[i] * y[i];
     s = block_sum256(s, sh);
     if (threadIdx.x == 0) {
         m.Bmat[snew * 8 + sk] = s;
@@ -297,12 +328,24 @@ __global__ __launch_bounds__(256) void gersh_b(const MolDesc* d, int n_mol) {
     __shared__ double sh[4];
     double lo = 1e300, hi = -1e300;
     for (int r = threadIdx.x; r < m.N; r += 256) {
-        const double* row = m.T2 + (int64_t)r * m.N;
+        // row r of T2 by its column, which holds the same bits (the product wrote
+        // every entry to its mirror position): neighbouring lanes read one line, eight
+        // rows' loads in flight (433 -> 110 us for 60 molecules)
+        const double* col = m.T2 + r;
+        const int64_t N = m.N;
         double off = 0.0;
-        for (int c = 0; c < m.N; ++c)
-            if (c != r) off += fabs(row[c]);
-        lo = fmin(lo, row[r] - off);
-        hi = fmax(hi, row[r] + off);
+        int c = 0;
+        for (; c + 8 <= m.N; c += 8) {
+            double v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = col[(c + k) * N];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) off = c + k != r ? off + fabs(v[k]) : off;
+        }
+        for (; c < m.N; ++c) off = c != r ? off + fabs(col[c * N]) : off;
+        const double diag = col[r * N];
+        lo = fmin(lo, diag - off);
+        hi = fmax(hi, diag + off);
     }
     lo = -block_max256(-lo, sh);
     hi = block_max256(hi, sh);
@@ -531,6 +574,7 @@ int k_split_small(int64_t rows) { return (int)std::max<int64_t>(1, std::min<int6
 struct HostPlan {
     std::vector<MolDesc> mols;
     std::vector<int> tile;                            // GEMM tile edge per molecule
+    std::vector<int> by_size;                         // molecules by descending N: the grouped GEMMs' members
     std::vector<Table*> tabs;                         // every table, in layout order
     std::vector<std::vector<int>> prefixes;           // each table's prefix (same order)
     std::vector<Plan::G*> gs;                         // every grouped GEMM
@@ -682,7 +726,11 @@ static int32_t batch_layout(int32_t n_mol, const ri_system* sys, const ri_batch_
                 c[i] = hp.mols[i].xs64 == xs && hp.mols[i].sp ? ri::xs_items(hp.mols[i].N, hp.mols[i].n_aux) : 0;
             mk(c, p.xp64[xs]);
         }
-    // grouped GEMMs: member i of each
+    // grouped GEMMs: a member of each for every molecule, the longest reductions
+    // first, so that a launch does not end on its longest tiles
+    hp.by_size.resize(n_mol);
+    for (int i = 0; i < n_mol; ++i) hp.by_size[i] = i;
+    std::stable_sort(hp.by_size.begin(), hp.by_size.end(), [&](int a, int b) { return hp.mols[a].N > hp.mols[b].N; });
     // tunable: the member runs on the molecule's tuned tile (else on 64 x 64)
     auto mkg = [&](Plan::G& g, bool ta, bool tb, bool tunable, auto fill, int act = ST_ACTIVE, bool sym = false) {
         g.ta = ta;
@@ -690,11 +738,12 @@ static int32_t batch_layout(int32_t n_mol, const ri_system* sys, const ri_batch_
         std::vector<ri::GemmDesc> v(n_mol);
         std::vector<int> c64(n_mol), c128(n_mol);
         for (int i = 0; i < n_mol; ++i) {
-            fill(hp.mols[i], v[i]);
+            MolDesc& m = hp.mols[hp.by_size[i]];
+            fill(m, v[i]);
             v[i].sym = sym;
             // runs while this flag is set (no pointer in the sizing pass, whose carver has no base)
-            v[i].active = hp.mols[i].state ? hp.mols[i].state + act : nullptr;
-            const bool big = tunable && hp.tile[i] == 128;
+            v[i].active = m.state ? m.state + act : nullptr;
+            const bool big = tunable && hp.tile[hp.by_size[i]] == 128;
             c64[i] = big ? 0 : gemm_tiles(v[i].M, v[i].N, 64, sym);
             c128[i] = big ? gemm_tiles(v[i].M, v[i].N, 128, sym) : 0;
         }
@@ -811,8 +860,8 @@ int32_t autotune_impl(int32_t n_mol, const ri_system* sys, const ri_batch_mol* m
         float best = 1e30f;
         for (int tile : {64, 128}) {
             std::vector<int> pre(n_mol + 1, 0);
-            for (int i = 0; i < n_mol; ++i) {
-                const int M = hp.mols[i].N;
+            for (int i = 0; i < n_mol; ++i) {   // in the grouped products' order
+                const int M = hp.mols[hp.by_size[i]].N;
                 const int t = gemm_tiles(M, M, tile, true);
                 pre[i + 1] = pre[i] + (tune_bucket(M, RI_TUNE_BUCKETS) == b ? t : 0);
             }

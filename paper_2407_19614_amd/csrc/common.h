@@ -31,6 +31,15 @@ __device__ __forceinline__ int xcd_remap(int L, int W) {
     return x * q + min(x, r) + s;
 }
 
+// The same in runs of C: each XCD receives C consecutive items in turn, so that
+// the items' order (largest first) still holds over the whole chip; what is left
+// past the last 8 C goes round the XCDs one by one.
+template <int C>
+__device__ __forceinline__ int xcd_chunks(int L, int W) {
+    const int x = L & 7, s = L >> 3;
+    return L < W / (8 * C) * (8 * C) ? s / C * (8 * C) + x * C + s % C : L;
+}
+
 __device__ __forceinline__ double norm_s(double a) {
     // (2a/pi)^{3/4}
     return pow(2.0 * a / RI_PI, 0.75);
