@@ -25,32 +25,6 @@ sys.path.insert(0, ROOT)
 PEAK_FP64_TFLOPS = 78.6     # MI355X dense FP64 MFMA
 PEAK_HBM_GBS = 8000.0
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense BF16 MFMA
-COUNTERS = os.path.join(ROOT, "profiles", "x_kernel_n1000_counters.md")
-KERNEL_SRC = os.path.join(ROOT, "paper_2407_19614_amd", "csrc", "fock.hip")
-
-
-def x_kernel_hash():
-    """First 16 hex digits of the sha256 of the FP64 X kernel's source text
-    (x2_body_f64 through x2_kernel_f64)."""
-    import hashlib
-    src = open(KERNEL_SRC).read()
-    a = src.index("__device__ __forceinline__ void x2_body_f64(")
-    b = src.index("void x2_kernel_f64(", a)
-    c = src.index("\n}\n", b) + 3
-    return hashlib.sha256(src[a:c].encode()).hexdigest()[:16]
-
-
-def measured_traffic():
-    """HBM bytes per launch of the X kernel from the committed counter
-    summary, or None when the kernel's source changed since it was taken."""
-    try:
-        txt = open(COUNTERS).read()
-        val = float(txt.split("traffic_bytes_per_launch:")[1].split()[0])
-        sha = txt.split("x_kernel_source_sha256_16:")[1].split()[0]
-        cur = x_kernel_hash()
-    except (OSError, IndexError, ValueError):
-        return None
-    return val if cur == sha else None
 
 
 def main():
@@ -165,10 +139,11 @@ def main():
     t_j, t_x, t_k = ph.mean(0)
 
     # algorithmic work per build (N, not padded sizes)
-    fl_x = 2.0 * N * N * no * na
+    # X runs over the significant pairs (both orders of each, the diagonal once)
+    fl_x = 2.0 * (2 * npairs - N) * no * na
     fl_k = float(N) * (N + 1) * no * na
     by_j = 2.0 * 8 * na * npairs
-    achieved = fl_x / (t_x * 1e-3) / 1e12
+    achieved = fl_k / (t_k * 1e-3) / 1e12
     out = {
         "metric": "RI-JK Fock builds/s + %MFMA peak at N=1000; batched SCF/s at dE<=1e-6 Eh",
         "value": round(args.steps / wall, 3),
@@ -180,15 +155,16 @@ def main():
         "config": {"workload": "n1000: 100 He-like centres, N=1000, N_aux=3000, n_occ=100, tau=1e-12, "
                                "decompressed packed-tile FP64 B",
                    "n_pairs": int(npairs), "parallelism": "single GPU"},
-        "roofline": {"bound": "mfma", "kernel": "x_kernel_f64 (X^P = B^P C_occ)",
+        "roofline": {"bound": "mfma", "kernel": "syrk_lds_kernel (K = sum_P X^P X^P^T)",
                      "achieved": round(achieved, 2), "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(achieved / PEAK_FP64_TFLOPS, 4), "traffic": measured_traffic(),
-                     "flops_per_launch": fl_x, "avg_launch_ms": round(t_x, 4)},
+                     "frac": round(achieved / PEAK_FP64_TFLOPS, 4), "traffic": None,
+                     "flops_per_launch": fl_k, "avg_launch_ms": round(t_k, 4)},
         "phases_ms": {"gamma_J": round(t_j, 4), "X": round(t_x, 4), "K_syrk": round(t_k, 4)},
         "fock_build_frac_fp64_peak": round((fl_x + fl_k) / (ms_step * 1e-3) / 1e12 / PEAK_FP64_TFLOPS, 4),
         "K_syrk_tflops": round(fl_k / (t_k * 1e-3) / 1e12, 2),
-        # gamma/J runs beside X on the side stream (128 workgroups at this size): its span
-        # is hidden under the exchange, so its rate here is not its bandwidth when alone
+        "X_pairs_tflops": round(fl_x / (t_x * 1e-3) / 1e12, 2),   # with the transposition of B_c that precedes it
+        # gamma/J runs beside X on the side stream: its span is hidden under the exchange,
+        # so its rate here is not its bandwidth when alone
         "gamma_J_beside_X": {"ms": round(t_j, 4), "GBs": round(by_j / (t_j * 1e-3) / 1e9, 1)},
         "pipeline_s": phases,
         "pipeline_cold_s": cold,
@@ -325,8 +301,8 @@ def precision_leg(s, C, res64, args, P, torch, np, ms_fp64, scf_s64=None, K64=No
 
 def density_leg(pr, C, torch, np, reps=3):
     """Fock build from the density alone at the same workload (as a density
-    start needs): K = 1/2 sum_P B^P D B^P on FP64 MFMA GEMMs, 4 N^3 N_aux
-    flops.  Reports its time, rate, and the largest difference of its J and
+    start needs): K = 1/2 sum_P B^P D B^P on FP64 MFMA, D B^P over the
+    significant pairs and the lower triangle of its product with B^P.  Reports its time, rate, and the largest difference of its J and
     K from the orbital build for D = 2 C C^T."""
     N, na = pr.N, pr.n_aux
     D = 2.0 * C @ C.T
@@ -338,7 +314,7 @@ def density_leg(pr, C, torch, np, reps=3):
         J1, K1 = pr.fock_jk_density(D)
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t) / reps
-    fl = 4.0 * N ** 3 * na
+    fl = 2.0 * (2 * pr.n_pairs - N) * N * na + float(N) * N * (N + 1) * na
     return {"ms_per_build": round(dt * 1e3, 2), "flops": fl, "tflops": round(fl / dt / 1e12, 2),
             "frac_fp64_peak": round(fl / dt / 1e12 / PEAK_FP64_TFLOPS, 4),
             "max_abs_dJ_vs_orbital": float((J1 - J0).abs().max()),

@@ -186,7 +186,9 @@ int32_t ri_pack_b(int32_t N, int32_t n_aux, const double* Bc, const int32_t* pai
  * utilisation section).
  *   B       packed B in precision `prec` (from ri_metric_factor), or NULL
  *           with prec | RI_COMPRESSED: X^P is then formed slab by slab from
- *           Bc (Algorithm 1's per-iteration decompression).
+ *           Bc (Algorithm 1's per-iteration decompression).  In FP64 and FP32,
+ *           large builds with at most 60 % of the pairs significant form X^P
+ *           over those pairs, from Bc, and do not read B.
  *   Bc      [n_aux][n_pairs] FP64 fitted tensor on compressed pairs, and
  *   pairs   [n_pairs][2]: gamma and J are formed from these in FP64 for
  *           every precision.
@@ -276,8 +278,9 @@ typedef struct {
  * density form, eq. k with the RI factorisation eq. ri_eri, which reads
  * K = 1/2 sum_P B^P D B^P (the C_occ-factored eq. tp / eq. k_ri_2 needs
  * orbitals; the Exchange-build remark notes that a density start makes the
- * first build slower).  Cost 4 N^3 N_aux FP64 MFMA flops, against
- * 3 N^2 n_occ N_aux for ri_fock_jk.
+ * first build slower).  Cost 2 N N_aux flops per significant (mu, nu)
+ * and N^3 N_aux for the product, in FP64 MFMA, against 2 n_occ N_aux and
+ * N^2 n_occ N_aux for ri_fock_jk.
  *   Bc, pairs  as from ri_metric_factor (B itself is not used).
  *   D          [N][N] device FP64, symmetric (its symmetric part is used).
  *   J, K       [N][N] out; gamma [n_aux] out or NULL.
@@ -325,7 +328,8 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec, const doubl
  *   g = sum D h' - sum W S' + sum Y (mu nu|P)' - 1/2 sum Z (P|Q)' + E_nn'.
  *   B, prec, Bc, pairs, Linv as returned by ri_metric_factor (B may be NULL
  *            with prec | RI_COMPRESSED).  With RI_FP64 or RI_FP32 the
- *            half-transform X^P = B^P C for B_ij reads B in that precision.
+ *            half-transform X^P = B^P C for B_ij is in that precision, and
+ *            reads B or Bc as ri_fock_jk does.
  *            With RI_BF16X3 or RI_BF16X6, B is not read (it may be NULL):
  *            B_ij, Xi and every sum are formed in FP64 from Bc, unpacked
  *            RI_COMPRESSED_SLAB auxiliaries at a time as for RI_COMPRESSED,
