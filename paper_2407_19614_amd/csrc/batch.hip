@@ -420,11 +420,13 @@ __global__ __launch_bounds__(64) void small_chol_b(const MolDesc* d, int n_mol) 
     chol_inv64_blocked(S, nb, [&](int) { atomicAdd(bad, 1); }, [&](int i, int c, double v) { out[i * 64 + c] = v; });
 }
 
-__global__ void count_active_b(const MolDesc* d, int n_mol, int* out) {
-    if (threadIdx.x != 0) return;
+// molecules that are active and, if asked, still purifying
+__global__ __launch_bounds__(256) void count_active_b(const MolDesc* d, int n_mol, bool purifying, int* out) {
     int c = 0;
-    for (int i = 0; i < n_mol; ++i) c += d[i].state[ST_ACTIVE];
-    *out = c;
+    for (int i = threadIdx.x; i < n_mol; i += 256)
+        c += d[i].state[ST_ACTIVE] && (!purifying || d[i].state[ST_TC2]);
+    c = __syncthreads_count(c > 0);   // all that the host asks is whether any is left
+    if (threadIdx.x == 0) *out = c;
 }
 
 // -------------------------------------------------- host side
@@ -433,16 +435,18 @@ struct Table {
     int total = 0;
 };
 
+constexpr int TC2_FIRST = 32, TC2_MORE = 8;
+
 struct Plan {
-    // purification steps of each launch sequence: tc2_iters inside the
-    // captured iteration, tc2_start for the core-Hamiltonian start.  Steps
-    // grow with log(spectral width / gap): converged Fock matrices of the
-    // 10-60-centre molecules need 27-30, their core Hamiltonians 34-67, and a
-    // DIIS-extrapolated Fock matrix of an early iteration can have a smaller
-    // gap still (3 of the 256 molecules of the batched workload need more
-    // than 64 steps there).  Molecules whose purification has finished skip
-    // the remaining steps of the sequence at once.
-    int n_mol = 0, prec = 0, tc2_iters = 128, tc2_start = 128;
+    // Purification steps at most.  Steps grow with log(spectral width / gap):
+    // converged Fock matrices of 10-60-centre molecules need 27-32, their core
+    // Hamiltonians 34-67, and a DIIS-extrapolated one of an early iteration can
+    // need more.  Steps after a molecule's last exit at once, but each is still
+    // three launches (12 us), so the host looks whether any molecule is left
+    // after the first TC2_FIRST and then after every TC2_MORE (a look: 0.05 ms;
+    // all 128 enqueued unseen: 0.8 to 1.1 ms of empty launches an iteration).
+    int n_mol = 0, prec = 0, tc2_iters = 128;
+    int first_steps() const { return std::min(TC2_FIRST, tc2_iters); }
     bool fin = false;                                     // FP64 exchange once after the FP32 SCF
     MolDesc* d = nullptr;
     Table n2, n2s, rows, pairs, aux, syrk, tail, cq, x[33];   // x[xs], xs = 4 * tiles + quads
@@ -460,40 +464,68 @@ struct Plan {
         if (_e != hipSuccess) return _e;       \
     } while (0)
 
-hipError_t occupied_space_b(const Plan& p, int tc2_steps, hipStream_t st) {
-    const MolDesc* d = p.d;
-    const int nm = p.n_mol;
-    auto gg = [&](const Plan::G& g) {
-        hipError_t e = ri::gemm_grouped(g.ta, g.tb, g.d, g.t.prefix, nm, g.t.total, st, 64);
-        return e == hipSuccess ? ri::gemm_grouped(g.ta, g.tb, g.d, g.t128.prefix, nm, g.t128.total, st, 128) : e;
-    };
-    HC(gg(p.g_lfx));
-    HC(gg(p.g_t2));
-    gersh_b<<<nm, 256, 0, st>>>(d, nm);
-    tc2_init_b<<<p.n2.total, 256, 0, st>>>(d, p.n2.prefix, nm);
-    for (int k = 0; k < tc2_steps; ++k) {
-        HC(gg(p.g_x2));
-        traces_b<<<nm, 256, 0, st>>>(d, nm);
-        tc2_update_b<<<p.n2s.total, 256, 0, st>>>(d, p.n2s.prefix, nm);
+hipError_t grouped(const Plan& p, const Plan::G& g, hipStream_t st) {
+    HC(ri::gemm_grouped(g.ta, g.tb, g.d, g.t.prefix, p.n_mol, g.t.total, st, 64));
+    return ri::gemm_grouped(g.ta, g.tb, g.d, g.t128.prefix, p.n_mol, g.t128.total, st, 128);
+}
+
+// The occupied space in three parts: up to the first `steps` purification steps,
+// further steps, and what follows the last.
+hipError_t purify_steps_b(const Plan& p, int steps, hipStream_t st) {
+    for (int k = 0; k < steps; ++k) {
+        HC(grouped(p, p.g_x2, st));
+        traces_b<<<p.n_mol, 256, 0, st>>>(p.d, p.n_mol);
+        tc2_update_b<<<p.n2s.total, 256, 0, st>>>(p.d, p.n2s.prefix, p.n_mol);
     }
-    tc2_check_b<<<nm, 64, 0, st>>>(d, nm);
-    for (int pass = 0; pass < 2; ++pass) {
-        HC(gg(p.g_y));
-        HC(gg(p.g_mo));
-        small_chol_b<<<nm, 64, 0, st>>>(d, nm);
-        HC(gg(p.g_cp));
-    }
-    HC(gg(p.g_c));
+    count_active_b<<<1, 256, 0, st>>>(p.d, p.n_mol, true, p.n_active + 2);
     return hipGetLastError();
 }
 
+hipError_t purify_begin_b(const Plan& p, hipStream_t st) {
+    HC(grouped(p, p.g_lfx, st));
+    HC(grouped(p, p.g_t2, st));
+    gersh_b<<<p.n_mol, 256, 0, st>>>(p.d, p.n_mol);
+    tc2_init_b<<<p.n2.total, 256, 0, st>>>(p.d, p.n2.prefix, p.n_mol);
+    return purify_steps_b(p, p.first_steps(), st);
+}
+
+hipError_t purify_end_b(const Plan& p, hipStream_t st) {
+    const MolDesc* d = p.d;
+    const int nm = p.n_mol;
+    tc2_check_b<<<nm, 64, 0, st>>>(d, nm);
+    for (int pass = 0; pass < 2; ++pass) {
+        HC(grouped(p, p.g_y, st));
+        HC(grouped(p, p.g_mo, st));
+        small_chol_b<<<nm, 64, 0, st>>>(d, nm);
+        HC(grouped(p, p.g_cp, st));
+    }
+    HC(grouped(p, p.g_c, st));
+    count_active_b<<<1, 256, 0, st>>>(d, nm, false, p.n_active);
+    return hipGetLastError();
+}
+
+// The steps past the first, TC2_MORE at a time while a molecule purifies, and the
+// end; `more` enqueues TC2_MORE of them (a captured graph or the launches).
+template <class More>
+hipError_t purify_rest_b(const Plan& p, hipStream_t st, More more) {
+    for (int done = p.first_steps(); done < p.tc2_iters;) {
+        int left = 0;
+        HC(hipMemcpyAsync(&left, p.n_active + 2, sizeof(int), hipMemcpyDeviceToHost, st));
+        HC(hipStreamSynchronize(st));
+        if (left == 0) break;
+        const int n = std::min(TC2_MORE, p.tc2_iters - done);
+        HC(n == TC2_MORE ? more() : purify_steps_b(p, n, st));
+        done += n;
+    }
+    return hipSuccess;
+}
+
+// One iteration, up to the first purification steps (purify_rest_b and
+// purify_end_b complete it).
 hipError_t iteration_b(const Plan& p, int max_iter, hipStream_t st) {
     const MolDesc* d = p.d;
     const int nm = p.n_mol;
-    auto gg = [&](const Plan::G& g) {
-        hipError_t e = ri::gemm_grouped(g.ta, g.tb, g.d, g.t.prefix, nm, g.t.total, st, 64);
-        return e == hipSuccess ? ri::gemm_grouped(g.ta, g.tb, g.d, g.t128.prefix, nm, g.t128.total, st, 128) : e;
-    };
+    auto gg = [&](const Plan::G& g) { return grouped(p, g, st); };
     // Fock build
     HC(ri::zero_tail_b(d, p.tail.prefix, nm, p.tail.total, p.prec, st));
     HC(ri::gamma_j_b(d, nm, p.pairs.prefix, p.pairs.total, p.aux.prefix, p.aux.total, p.n2.prefix, p.n2.total, st));
@@ -517,9 +549,7 @@ hipError_t iteration_b(const Plan& p, int max_iter, hipStream_t st) {
     diis_dots_b<<<dim3(nm, 8), 256, 0, st>>>(d, nm);
     diis_solve_b<<<nm, 64, 0, st>>>(d, nm);
     diis_combine_b<<<p.n2.total, 256, 0, st>>>(d, p.n2.prefix, nm);
-    HC(occupied_space_b(p, p.tc2_iters, st));
-    count_active_b<<<1, 64, 0, st>>>(d, nm, p.n_active);
-    return hipGetLastError();
+    return purify_begin_b(p, st);
 }
 
 
@@ -955,7 +985,7 @@ int32_t ri_energy_batched(int32_t n_mol, const ri_system* sys, const ri_batch_mo
         m.tol_err = opts->tol_err;
         m.diis_n = opts->diis_n;
     }
-    if (opts->max_purify > 0) p.tc2_iters = p.tc2_start = opts->max_purify;
+    if (opts->max_purify > 0) p.tc2_iters = opts->max_purify;
     rc = upload_plan(p, hp, st);
     if (rc != RI_OK) return rc;
     // per-molecule setup: S, h, E_nn, Cholesky of S and L_S^{-1}.  Each
@@ -1028,39 +1058,54 @@ int32_t ri_energy_batched(int32_t n_mol, const ri_system* sys, const ri_batch_mo
     if (hbad != INT_MAX) return RI_E_NOT_PD;
     // core-Hamiltonian start
     copy_h_b<<<p.n2.total, 256, 0, st>>>(p.d, p.n2.prefix, n_mol);
-    HIPR(occupied_space_b(p, p.tc2_start, st));
+    HIPR(purify_begin_b(p, st));
+    HIPR(purify_rest_b(p, st, [&] { return purify_steps_b(p, TC2_MORE, st); }));
+    HIPR(purify_end_b(p, st));
     // iterations.  A graph is captured on a private non-blocking stream (the
     // caller's stream may be the legacy default stream, which cannot be
     // captured); the host waits for every iteration, so ordering with the
     // caller's stream is kept by synchronising before the first replay.
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    hipStream_t cs = st;
-    if (use_graph) {
-        HIPR(hipStreamSynchronize(st));
-        HIPR(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-        hipError_t e0 = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-        hipError_t e = e0 == hipSuccess ? iteration_b(p, opts->max_iter, cs) : e0;
-        hipError_t e2 = e0 == hipSuccess ? hipStreamEndCapture(cs, &graph) : hipSuccess;
-        hipError_t e3 = (e == hipSuccess && e2 == hipSuccess) ? hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0)
-                                                               : hipSuccess;
-        if (e != hipSuccess || e2 != hipSuccess || e3 != hipSuccess) {
-            if (graph) hipGraphDestroy(graph);
-            hipStreamDestroy(cs);
-            HIPR(e != hipSuccess ? e : (e2 != hipSuccess ? e2 : e3));
+    struct Graph {
+        hipGraph_t g = nullptr;
+        hipGraphExec_t exec = nullptr;
+        ~Graph() {
+            if (exec) (void)hipGraphExecDestroy(exec);
+            if (g) (void)hipGraphDestroy(g);
         }
-    }
-    int active = n_mol;
+    };
+    hipStream_t cs = st;
     hipError_t loop_err = hipSuccess;
-    for (int it = 0; it < opts->max_iter && active > 0; ++it) {
-        loop_err = use_graph ? hipGraphLaunch(exec, cs) : iteration_b(p, opts->max_iter, cs);
-        if (loop_err == hipSuccess) loop_err = hipMemcpyAsync(&active, p.n_active, sizeof(int), hipMemcpyDeviceToHost, cs);
-        if (loop_err == hipSuccess) loop_err = hipStreamSynchronize(cs);
-        if (loop_err != hipSuccess) break;
+    {
+        Graph head, more, tail;   // an iteration's three parts
+        auto capture = [&](Graph& gr, auto body) -> hipError_t {
+            hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+            if (e != hipSuccess) return e;
+            e = body();
+            const hipError_t e2 = hipStreamEndCapture(cs, &gr.g);
+            if (e != hipSuccess || e2 != hipSuccess) return e != hipSuccess ? e : e2;
+            return hipGraphInstantiate(&gr.exec, gr.g, nullptr, nullptr, 0);
+        };
+        auto first = [&] { return iteration_b(p, opts->max_iter, cs); };
+        auto steps = [&] { return purify_steps_b(p, TC2_MORE, cs); };
+        auto end = [&] { return purify_end_b(p, cs); };
+        if (use_graph) {
+            HIPR(hipStreamSynchronize(st));
+            HIPR(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+            loop_err = capture(head, first);
+            if (loop_err == hipSuccess) loop_err = capture(more, steps);
+            if (loop_err == hipSuccess) loop_err = capture(tail, end);
+        }
+        int active = n_mol;
+        auto iteration = [&]() -> hipError_t {
+            HC(use_graph ? hipGraphLaunch(head.exec, cs) : first());
+            HC(purify_rest_b(p, cs, [&] { return use_graph ? hipGraphLaunch(more.exec, cs) : steps(); }));
+            HC(use_graph ? hipGraphLaunch(tail.exec, cs) : end());
+            HC(hipMemcpyAsync(&active, p.n_active, sizeof(int), hipMemcpyDeviceToHost, cs));
+            return hipStreamSynchronize(cs);
+        };
+        for (int it = 0; it < opts->max_iter && active > 0 && loop_err == hipSuccess; ++it) loop_err = iteration();
     }
-    if (exec) hipGraphExecDestroy(exec);
-    if (graph) hipGraphDestroy(graph);
-    if (cs != st) hipStreamDestroy(cs);
+    if (cs != st) (void)hipStreamDestroy(cs);
     HIPR(loop_err);
     if (p.fin) {
         std::vector<MolDesc> d64 = hp.mols;
