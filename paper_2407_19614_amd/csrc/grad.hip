@@ -402,17 +402,64 @@ __global__ __launch_bounds__(256, 2) void g3c_kernel(const double* __restrict__ 
     flush_add(g, 3 * nc, part);
 }
 
-// rows: first pair of each mu (pairs are sorted by mu), rows[N] = n_pairs
-__global__ void pair_rows_kernel(const int32_t* __restrict__ pairs, int64_t n_pairs, int N, int32_t* __restrict__ rows) {
-    const int mu = blockIdx.x * blockDim.x + threadIdx.x;
-    if (mu > N) return;
+// The pairs by rows: sp, a copy of the pairs, and rows, the first of each mu in it
+// (rows[N] = n_pairs).  Pairs that are not sorted by mu set rows[N + 1], which is 0
+// before, and are sorted by pair_sort_kernel.
+struct Pair {   // aligned as the caller's ints
+    int32_t x, y;
+};
+
+__global__ __launch_bounds__(256) void pair_rows_kernel(const Pair* __restrict__ pairs, int64_t n_pairs, int N,
+                                                        int32_t* __restrict__ rows, Pair* __restrict__ sp) {
+    const int64_t t = blockIdx.x * 256ll + threadIdx.x;
+    if (t < n_pairs) {
+        sp[t] = pairs[t];
+        if (t + 1 < n_pairs && pairs[t].x > pairs[t + 1].x) rows[N + 1] = 1;
+    }
+    if (t > N) return;
     int64_t lo = 0, hi = n_pairs;
     while (lo < hi) {
         const int64_t mid = (lo + hi) / 2;
-        if (pairs[2 * mid] < mu) lo = mid + 1;
+        if (pairs[mid].x < t) lo = mid + 1;
         else hi = mid;
     }
-    rows[mu] = (int32_t)lo;
+    rows[t] = (int32_t)lo;
+}
+
+// Counting sort of pairs in another order, one workgroup, a row per thread; each
+// row keeps the order of its pairs.
+__global__ __launch_bounds__(1024) void pair_sort_kernel(const Pair* __restrict__ pairs, int64_t n_pairs, int N,
+                                                         int32_t* rows, Pair* __restrict__ sp) {
+    if (rows[N + 1] == 0) return;
+    __shared__ Pair sh[1024];
+    __shared__ int32_t n_row[1024];
+    int32_t base = 0;
+    for (int m0 = 0; m0 < N; m0 += 1024) {
+        const int mu = m0 + threadIdx.x;
+        int32_t at = 0;
+        for (int pass = 0; pass < 2; ++pass) {   // count, then place
+            for (int64_t q0 = 0; q0 < n_pairs; q0 += 1024) {
+                const int n = (int)min((int64_t)1024, n_pairs - q0);
+                __syncthreads();
+                if ((int)threadIdx.x < n) sh[threadIdx.x] = pairs[q0 + threadIdx.x];
+                __syncthreads();
+                for (int k = 0; k < n; ++k)
+                    if (sh[k].x == mu) {
+                        if (pass == 1) sp[at] = sh[k];
+                        ++at;
+                    }
+            }
+            if (pass == 0) {
+                n_row[threadIdx.x] = at;
+                __syncthreads();
+                at = base;
+                for (int k = 0; k < (int)threadIdx.x; ++k) at += n_row[k];
+                for (int k = 0; k < 1024; ++k) base += n_row[k];
+                if (mu < N) rows[mu] = at;
+            }
+        }
+    }
+    if (threadIdx.x == 0) rows[N] = base;
 }
 
 // WY[p][q] (+)= sum_k U[p][mu][k] C[nu][k] over K columns for the significant pairs q =
@@ -722,11 +769,18 @@ hipError_t grad_three_centre(const ri_system* s, const int32_t* pairs, int64_t n
     const size_t lds = 3 * s->n_centres * sizeof(double);
     RI_TRY(fill(part, 0.0, (int64_t)GRAD_BLOCKS * 3 * s->n_centres, st));
     if (n_pairs == 0) return hipSuccess;
-    pair_rows_kernel<<<(N + 256) / 256, 256, 0, st>>>(pairs, n_pairs, N, rows);
-    RI_TRY(hipGetLastError());
     double* pc = pscratch;
     int2* ctr = (int2*)(pc + PC_N * n_pairs);
-    double* bt = (double*)(ctr + n_pairs);
+    Pair* sp = (Pair*)(ctr + n_pairs);
+    double* bt = (double*)(sp + n_pairs);
+    // nothing below needs the given order, so rows of it are made where it has none
+    const Pair* given = (const Pair*)pairs;
+    RI_TRY(fill_i32(rows + N + 1, 0, 1, st));
+    pair_rows_kernel<<<(unsigned)((std::max<int64_t>(n_pairs, N + 1) + 255) / 256), 256, 0, st>>>(given, n_pairs, N, rows,
+                                                                                                  sp);
+    pair_sort_kernel<<<1, 1024, 0, st>>>(given, n_pairs, N, rows, sp);
+    RI_TRY(hipGetLastError());
+    pairs = (const int32_t*)sp;
     pair_consts_kernel<<<(unsigned)((n_pairs + 255) / 256 + 2), 256, 0, st>>>(s->xyz, s->fn_centre, s->fn_exp, pairs,
                                                                               n_pairs, D, N, pc, ctr, bt);
     RI_TRY(hipGetLastError());
@@ -756,7 +810,7 @@ hipError_t grad_three_centre(const ri_system* s, const int32_t* pairs, int64_t n
     }
     return hipSuccess;
 }
-int64_t grad_pair_elems(int64_t n_pairs) { return (PC_N + 1) * n_pairs + BT_N * BT_M; }
+int64_t grad_pair_elems(int64_t n_pairs) { return (PC_N + 2) * n_pairs + BT_N * BT_M; }
 hipError_t grad_nuclear(const ri_system* s, double* part, hipStream_t st) {
     gnuc_kernel<<<1, 256, 0, st>>>(s->xyz, s->Z, s->n_centres, part);
     return hipGetLastError();
