@@ -3,6 +3,7 @@
 // kernels, BF16 inference for the 256 x 256 layer, and the scatter of
 // predicted pair densities into a dense symmetric matrix.
 #include "kernels.h"
+#include "mlp_split.h"
 
 #include <algorithm>
 
@@ -561,8 +562,6 @@ __global__ void density_add_kernel(const int32_t* pairs, int64_t n_pairs, const 
 
 // Rows per workgroup: 64, or 32 where 64 would leave most of the 256 CUs idle.
 int block_rows(int64_t n) { return n > 64 * 256 / 2 ? 64 : 32; }
-// Most splits of g_W2's row sum: 16 tiles x 32 = two workgroups per CU.
-constexpr int GW2_SPLITS = 32;
 
 inline unsigned g1(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
@@ -630,10 +629,9 @@ hipError_t mlp_train_step(const ri_mlp* net, float* m, float* v, int step, float
         mlp_kernel<false, true, 1><<<nblk, 512, 0, st>>>(feat, n, net->mu, net->sigma, P, nullptr, nullptr, target,
                                                          w.h1, w.dz2, w.part);
     RI_TRY(hipGetLastError());
-    // rows of each wave: a multiple of 16, at least 64 where there are that many
     const int64_t rows = (int64_t)nblk * rb;
-    const int64_t per = std::max<int64_t>(64, (rows / (4 * GW2_SPLITS) + 15) / 16 * 16);
-    const int splits = (int)((rows + 4 * per - 1) / (4 * per));
+    const auto [per, splits] = gw2_split(rows);
+    if (splits > GW2_SPLITS) return hipErrorInvalidValue;
     gw2_kernel<<<16 * splits, 256, 0, st>>>(w.h1, w.dz2, rows, per, w.pw2);
     RI_TRY(hipGetLastError());
     const float b1 = 0.9f, b2 = 0.999f;
