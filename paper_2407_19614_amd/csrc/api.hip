@@ -874,12 +874,12 @@ int32_t ri_gradient(const ri_system* sys, const int32_t* pairs, int64_t n_pairs,
     // one GEMM over all (P, i) rows: the rows of X^T are stacked P-major, as B_ij's
     HIPC(ri::gemm_f64(false, false, na * no, no, N, 1.0, (const double*)w.Xt, Npad, 0, C, no, 0, 0.0, w.Bij, no, 0,
                       1, 0, 0, st, 128));
-    // B_ij and Xi are symmetric in ij: half the columns (i >= j, sqrt 2 off the
-    // diagonal) carry Xi = L^{-T} B_ij and Zx = -2 sum_ij Xi_ij Xi_ij^T.  Packed B_ij goes
+    // B_ij (in FP32 the mean of its halves) and Xi are symmetric in ij: half the
+    // columns (i >= j, sqrt 2 off the diagonal) carry Xi = L^{-T} B_ij and Zx = -2 sum_ij Xi_ij Xi_ij^T.  Packed B_ij goes
     // where X was, packed Xi over B_ij, and Xi is unpacked for the products with C.
     const int64_t oh = (int64_t)no * (no + 1) / 2;
     double* Bp = (double*)w.Xt;
-    HIPC(ri::pack_ij(w.Bij, no, na, Bp, st));
+    HIPC(ri::pack_ij(w.Bij, no, na, prec == RI_FP32, Bp, st));
     HIPC(ri::gemm_f64(true, false, na, (int)oh, na, 1.0, Linv, na, 0, Bp, oh, 0, 0.0, w.Bij, oh, 0, 1, 2, 0, st));
     // lower tiles; Z = c c^T + Zx inside the contraction
     HIPC(ri::grad_metric_z(w.Bij, na, oh, w.WY, (int64_t)ri::grad_slab(N, na) * N * N, w.Zx, st));

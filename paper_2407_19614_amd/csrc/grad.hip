@@ -642,19 +642,29 @@ __global__ __launch_bounds__(256) void greduce_kernel(const double* part, int ro
     if (threadIdx.x == 0) grad[i] = sh[0];
 }
 
-// The blocks B_ij^P and Xi^P are symmetric in ij.  pack: Bp[P][e] = B[P][i][j] for
-// the entries e = i (i + 1) / 2 + j, j <= i, times sqrt 2 off the diagonal, so
-// that sums over all ij are sums over e; unpack: both halves of Xi[P] from Xp[P].
+// The blocks B_ij^P and Xi^P are symmetric in ij up to rounding.  pack: Bp[P][e] =
+// B[P][i][j] for the entries e = i (i + 1) / 2 + j, j <= i, times sqrt 2 off the
+// diagonal, so that sums over all ij are sums over e; unpack: both halves of
+// Xi[P] from Xp[P].  MEAN takes the mean of the two halves: after an FP32
+// half-transform they are rounded independently at 2^-24 (j's column of C in
+// FP32, i's in FP64), and one of them alone would carry sqrt 2 times the error
+// of both.  A workgroup per row (P, i); the mean's column reads stay within P's
+// block, which the rows beside it read too.
+template <bool MEAN>
 __global__ __launch_bounds__(256) void pack_ij_kernel(const double* __restrict__ B, int o, double* __restrict__ Bp) {
-    const int i = blockIdx.x;
-    const int64_t P = blockIdx.y;
+    const int64_t P = blockIdx.x / o;
+    const int i = (int)(blockIdx.x % o);
     const double* row = B + (P * o + i) * o;
+    const double* col = B + P * o * o + i;
     double* out = Bp + P * ((int64_t)o * (o + 1) / 2) + (int64_t)i * (i + 1) / 2;
-    for (int j = threadIdx.x; j <= i; j += blockDim.x) out[j] = j == i ? row[j] : 1.41421356237309504880 * row[j];
+    for (int j = threadIdx.x; j <= i; j += blockDim.x) {
+        const double v = MEAN ? 0.5 * (row[j] + col[(int64_t)j * o]) : row[j];
+        out[j] = j == i ? v : 1.41421356237309504880 * v;
+    }
 }
 __global__ __launch_bounds__(256) void unpack_ij_kernel(const double* __restrict__ Xp, int o, double* __restrict__ Xi) {
-    const int i = blockIdx.x;
-    const int64_t P = blockIdx.y;
+    const int64_t P = blockIdx.x / o;
+    const int i = (int)(blockIdx.x % o);
     const double* in = Xp + P * ((int64_t)o * (o + 1) / 2);
     double* out = Xi + (P * o + i) * o;
     for (int j = threadIdx.x; j < o; j += blockDim.x) {
@@ -698,12 +708,14 @@ __global__ __launch_bounds__(256) void gamma_row_kernel(const double* Bc, int64_
 
 namespace ri {
 
-hipError_t pack_ij(const double* B, int o, int np, double* Bp, hipStream_t st) {
-    pack_ij_kernel<<<dim3(o, np), o > 64 ? 128 : 64, 0, st>>>(B, o, Bp);
+hipError_t pack_ij(const double* B, int o, int np, bool mean, double* Bp, hipStream_t st) {
+    const unsigned blocks = (unsigned)np * (unsigned)o, threads = o > 64 ? 128 : 64;
+    if (mean) pack_ij_kernel<true><<<blocks, threads, 0, st>>>(B, o, Bp);
+    else pack_ij_kernel<false><<<blocks, threads, 0, st>>>(B, o, Bp);
     return hipGetLastError();
 }
 hipError_t unpack_ij(const double* Xp, int o, int np, double* Xi, hipStream_t st) {
-    unpack_ij_kernel<<<dim3(o, np), o > 64 ? 128 : 64, 0, st>>>(Xp, o, Xi);
+    unpack_ij_kernel<<<(unsigned)np * (unsigned)o, o > 64 ? 128 : 64, 0, st>>>(Xp, o, Xi);
     return hipGetLastError();
 }
 hipError_t grad_one_electron(const ri_system* s, const double* D, const double* W, double* part, hipStream_t st) {

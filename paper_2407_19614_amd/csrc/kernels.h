@@ -180,8 +180,9 @@ namespace ri {
 constexpr int GRAD_BLOCKS = 1024;
 hipError_t grad_one_electron(const ri_system* s, const double* D, const double* W, double* part, hipStream_t st);
 hipError_t grad_metric(const ri_system* s, const double* Z, const double* c, double* part, hipStream_t st);
-// [np][o][o] blocks, symmetric: entries j <= i times sqrt 2 off the diagonal ([np][o (o + 1) / 2]), and back
-hipError_t pack_ij(const double* B, int o, int np, double* Bp, hipStream_t st);
+// [np][o][o] blocks, symmetric up to rounding: entries j <= i (mean: of both halves) times sqrt 2 off the
+// diagonal ([np][o (o + 1) / 2]), and back
+hipError_t pack_ij(const double* B, int o, int np, bool mean, double* Bp, hipStream_t st);
 hipError_t unpack_ij(const double* Xp, int o, int np, double* Xi, hipStream_t st);
 // Zx = -2 Xi Xi^T (lower 128-tiles) for Xi [n_aux][K], split over K through
 // tmp (tmp_elems doubles of scratch).
