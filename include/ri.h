@@ -188,7 +188,8 @@ int32_t ri_pack_b(int32_t N, int32_t n_aux, const double* Bc, const int32_t* pai
  *           with prec | RI_COMPRESSED: X^P is then formed slab by slab from
  *           Bc (Algorithm 1's per-iteration decompression).  In FP64 and FP32,
  *           large builds with at most 60 % of the pairs significant form X^P
- *           over those pairs, from Bc, and do not read B.
+ *           over those pairs, from Bc, and do not read B (where the workspace
+ *           has room for it, see ri_workspace_bytes).
  *   Bc      [n_aux][n_pairs] FP64 fitted tensor on compressed pairs, and
  *   pairs   [n_pairs][2]: gamma and J are formed from these in FP64 for
  *           every precision.
@@ -523,7 +524,13 @@ int32_t ri_md_kinetic(int32_t n_atoms, const double* mass, const double* vel, do
 enum { RI_OP_BUILD_3C = 0, RI_OP_METRIC = 1, RI_OP_FOCK = 2, RI_OP_ENERGY = 3,
        RI_OP_GRADIENT = 4, RI_OP_MLP = 5, RI_OP_FOCK_DENSITY = 6 };
 
-/* Bytes of workspace an operation needs (0 on invalid arguments). */
+/* Bytes of workspace an operation needs (0 on invalid arguments).  The Fock
+ * build, the SCF and the gradient run X^P over the significant pairs of large
+ * builds with at most 60 % of them (ri_fock_jk), for which the size holds a
+ * second, transposed copy of B_c; it is therefore not monotone in n_pairs, but
+ * a workspace sized for a longer list is always enough for a shorter one: where
+ * it has no room for the copy, X^P is formed from packed tiles (the same bits in
+ * FP32; in FP64 the sums run in another order). */
 size_t ri_workspace_bytes(int32_t op, int32_t N, int32_t n_aux, int32_t n_occ,
                           int64_t n_pairs, int32_t prec);
 

@@ -44,6 +44,32 @@ struct Arena {
     bool ok() const { return dry || off + 256 <= cap; }
 };
 
+// A layout is carve(arena, lists): with the partner lists and the transposed
+// fitted tensor of the exchange over significant pairs where the size takes
+// that form (ri::xs_wanted), or without them.  The list form is up to 60 % fill
+// only, so sizes would shrink where a pair list grows past that: a workspace
+// sized for a longer list, which holds every form without lists of a shorter
+// one, is therefore taken for the latter.
+template <class F>
+bool carve_fit(void* ws, size_t bytes, F carve) {
+    for (bool lists : {true, false}) {
+        Arena a{(char*)ws, bytes, 0, false};
+        carve(a, lists);
+        if (a.ok()) return true;
+    }
+    return false;
+}
+template <class F>
+size_t carve_bytes(F carve) {
+    size_t most = 0;
+    for (bool lists : {true, false}) {
+        Arena a{nullptr, 0, 0, true};
+        carve(a, lists);
+        most = std::max(most, a.off);
+    }
+    return most + 256;
+}
+
 bool valid_sys(const ri_system* s) {
     return s && s->n_centres > 0 && s->n_fn > 0 && s->n_aux > 0 && s->n_occ > 0 && s->n_occ <= s->n_fn &&
            s->xyz && s->Z && s->fn_centre && s->fn_exp && s->aux_centre && s->aux_exp;
@@ -136,11 +162,11 @@ hipError_t x_any(const void* B, int prec, int N, int n_aux, int n_occ, const dou
 
 struct FockWS { void* Xt; double* part; double* dpair; double* jpart; double* gamma; double* Cp; int ks, js; SlabWS sw; ri::XSparse xs; };
 // wide: FP32-stored B in the FP64 layout (FP32 iterations and an FP64 build at the end)
-FockWS carve_fock(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, bool comp = false,
+FockWS carve_fock(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, bool comp = false,
                   bool wide = false) {
     FockWS w;
     const int xprec = wide ? (int)RI_FP32 : prec;
-    if (ri::xs_wanted(N, n_aux, n_occ, n_pairs, xprec)) w.xs = carve_sparse(a, N, n_aux, n_pairs, xprec == RI_FP32);
+    if (lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, xprec)) w.xs = carve_sparse(a, N, n_aux, n_pairs, xprec == RI_FP32);
     w.sw = carve_slab(a, N, n_aux, prec, comp);   // the compressed form's size contract holds for either form of X
     const int Npad = ri::xt_ld(N);
     w.js = ri::j_split_count(n_aux);
@@ -205,7 +231,7 @@ struct EnergyWS {
     FockWS fin;   // final FP64 exchange build of the split-BF16 forms: FP64 Xt and slabs of B_c
     DensityWS dens;
 };
-EnergyWS carve_energy(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, int diis_n,
+EnergyWS carve_energy(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, int diis_n,
                       bool comp = false, bool fin_slab = false, bool wide = false) {
     EnergyWS w;
     const int64_t n2 = (int64_t)N * N;
@@ -229,8 +255,8 @@ EnergyWS carve_energy(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, in
     w.tpart = a.take<double>(4 * (int64_t)ri::tc2f_tiles(N));   // purification partial sums, two parities
     w.bad = a.take<int>(2);
     w.tst = a.take<int>(16);                                    // purification state, two parities
-    w.fock = carve_fock(a, N, n_aux, n_occ, n_pairs, prec, comp, wide);
-    w.fin = fin_slab ? carve_fock(a, N, n_aux, n_occ, n_pairs, RI_FP64, true) : FockWS{};
+    w.fock = carve_fock(a, lists, N, n_aux, n_occ, n_pairs, prec, comp, wide);
+    w.fin = fin_slab ? carve_fock(a, lists, N, n_aux, n_occ, n_pairs, RI_FP64, true) : FockWS{};
     w.dens = carve_density(a, N, n_aux, n_pairs);
     return w;
 }
@@ -243,10 +269,10 @@ int energy_layout(const Prec& p) { return p.fin && !is_bf16(p.base) ? RI_FP64 : 
 bool energy_fin_slab(const Prec& p) { return p.fin && is_bf16(p.base); }
 
 struct GradWS { double *D, *W, *T1, *dpair, *gamma, *c, *Bij, *Xi, *Zx, *part, *Cp, *WY, *pscr; int32_t* rows; void* Xt; float* Xt32; SlabWS sw; ri::XSparse xs; };
-GradWS carve_grad(Arena& a, int N, int n_aux, int n_occ, int64_t n_pairs, int n_centres, int prec,
+GradWS carve_grad(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_pairs, int n_centres, int prec,
                   bool comp = false) {
     GradWS w;
-    if (ri::xs_wanted(N, n_aux, n_occ, n_pairs, prec)) w.xs = carve_sparse(a, N, n_aux, n_pairs, prec == RI_FP32);
+    if (lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, prec)) w.xs = carve_sparse(a, N, n_aux, n_pairs, prec == RI_FP32);
     w.sw = carve_slab(a, N, n_aux, prec, comp);   // the compressed form's size contract holds for either form of X
     const int Npad = ri::xt_ld(N);
     const int64_t n2 = (int64_t)N * N, o2 = (int64_t)n_occ * n_occ;
@@ -489,14 +515,18 @@ size_t ri_workspace_bytes(int32_t op, int32_t N, int32_t n_aux, int32_t n_occ, i
     switch (op) {
         case RI_OP_BUILD_3C: carve_build(a, N); break;
         case RI_OP_METRIC: carve_metric(a, N, n_aux, n_pairs); break;
-        case RI_OP_FOCK: carve_fock(a, N, n_aux, n_occ, n_pairs, prec, pp.comp); break;
+        case RI_OP_FOCK:
+            return carve_bytes([&](Arena& b, bool lists) { carve_fock(b, lists, N, n_aux, n_occ, n_pairs, prec, pp.comp); });
         case RI_OP_ENERGY:
-            carve_energy(a, N, n_aux, n_occ, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp),
-                         pp.fin && pp.base == RI_FP32);
-            break;
+            return carve_bytes([&](Arena& b, bool lists) {
+                carve_energy(b, lists, N, n_aux, n_occ, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp),
+                             pp.fin && pp.base == RI_FP32);
+            });
         case RI_OP_GRADIENT:
-            carve_grad(a, N, n_aux, n_occ, n_pairs, 2048, is_bf16(prec) ? RI_FP64 : prec, pp.comp || is_bf16(prec));
-            break;
+            return carve_bytes([&](Arena& b, bool lists) {
+                carve_grad(b, lists, N, n_aux, n_occ, n_pairs, 2048, is_bf16(prec) ? RI_FP64 : prec,
+                           pp.comp || is_bf16(prec));
+            });
         case RI_OP_FOCK_DENSITY: carve_density(a, N, n_aux, n_pairs); break;
         case RI_OP_MLP: {
             size_t off = 0;
@@ -626,9 +656,9 @@ int32_t ri_fock_jk(int32_t N, int32_t n_aux, int32_t n_occ, const void* B, int32
         return RI_E_ARG;
     if (!pp.ok || (is_bf16(prec) && n_occ > 128)) return RI_E_UNSUPPORTED;
     if (pp.comp) B = nullptr;
-    Arena a{(char*)ws, ws_bytes, 0, false};
-    FockWS w = carve_fock(a, N, n_aux, n_occ, n_pairs, prec, pp.comp);
-    if (!a.ok()) return RI_E_WORKSPACE;
+    FockWS w;
+    if (!carve_fit(ws, ws_bytes, [&](Arena& a, bool lists) { w = carve_fock(a, lists, N, n_aux, n_occ, n_pairs, prec, pp.comp); }))
+        return RI_E_WORKSPACE;
     return fock_impl(N, n_aux, n_occ, B, prec, Bc, pairs, n_pairs, C, J, K, gamma, w, st);
 }
 
@@ -643,13 +673,13 @@ int32_t ri_fock_jk_noalloc(int32_t N, int32_t n_aux, int32_t n_occ, const void* 
     if (!pp.ok || (is_bf16(prec) && n_occ > 128)) return RI_E_UNSUPPORTED;
     if (pp.comp) B = nullptr;
     Arena dry{nullptr, 0, 0, true};
-    carve_fock(dry, N, n_aux, n_occ, n_pairs, prec, pp.comp);
+    carve_fock(dry, false, N, n_aux, n_occ, n_pairs, prec, pp.comp);
     if (dry.off + 256 > RI_NOALLOC_SCRATCH_BYTES) return RI_E_WORKSPACE;
     void* ws = nullptr;
     const int32_t rc = noalloc_scratch(&ws);
     if (rc != RI_OK) return rc;
     Arena a{(char*)ws, RI_NOALLOC_SCRATCH_BYTES, 0, false};
-    FockWS w = carve_fock(a, N, n_aux, n_occ, n_pairs, prec, pp.comp);
+    FockWS w = carve_fock(a, false, N, n_aux, n_occ, n_pairs, prec, pp.comp);
     return fock_impl(N, n_aux, n_occ, B, prec, Bc, pairs, n_pairs, C, J, K, gamma, w, st, nullptr, false);
 }
 
@@ -664,9 +694,9 @@ int32_t ri_fock_jk_timed(int32_t N, int32_t n_aux, int32_t n_occ, const void* B,
         return RI_E_ARG;
     if (!pp.ok || (is_bf16(prec) && n_occ > 128)) return RI_E_UNSUPPORTED;
     if (pp.comp) B = nullptr;
-    Arena a{(char*)ws, ws_bytes, 0, false};
-    FockWS w = carve_fock(a, N, n_aux, n_occ, n_pairs, prec, pp.comp);
-    if (!a.ok()) return RI_E_WORKSPACE;
+    FockWS w;
+    if (!carve_fit(ws, ws_bytes, [&](Arena& a, bool lists) { w = carve_fock(a, lists, N, n_aux, n_occ, n_pairs, prec, pp.comp); }))
+        return RI_E_WORKSPACE;
     return fock_impl(N, n_aux, n_occ, B, prec, Bc, pairs, n_pairs, C, J, K, gamma, w, st, events);
 }
 
@@ -707,10 +737,12 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
     if (prec == RI_BF16X3 && !pp.fin) return RI_E_UNSUPPORTED;
     const int N = sys->n_fn, na = sys->n_aux, no = sys->n_occ, dn = opts->diis_n;
     const int64_t n2 = (int64_t)N * N;
-    Arena a{(char*)ws, ws_bytes, 0, false};
-    EnergyWS w = carve_energy(a, N, na, no, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp),
-                         pp.fin && pp.base == RI_FP32);
-    if (!a.ok()) return RI_E_WORKSPACE;
+    EnergyWS w;
+    if (!carve_fit(ws, ws_bytes, [&](Arena& a, bool lists) {
+            w = carve_energy(a, lists, N, na, no, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp),
+                             pp.fin && pp.base == RI_FP32);
+        }))
+        return RI_E_WORKSPACE;
     std::memset(res, 0, sizeof(*res));
 
     HIPC(ri::one_electron(sys, w.S, w.H, st));
@@ -846,9 +878,9 @@ int32_t ri_gradient(const ri_system* sys, const int32_t* pairs, int64_t n_pairs,
     const int N = sys->n_fn, na = sys->n_aux, no = sys->n_occ, nc = sys->n_centres;
     const int Npad = ri::xt_ld(N);
     const int64_t o2 = (int64_t)no * no;
-    Arena a{(char*)ws, ws_bytes, 0, false};
-    GradWS w = carve_grad(a, N, na, no, n_pairs, 2048, prec, slabs);
-    if (!a.ok()) return RI_E_WORKSPACE;
+    GradWS w;
+    if (!carve_fit(ws, ws_bytes, [&](Arena& a, bool lists) { w = carve_grad(a, lists, N, na, no, n_pairs, 2048, prec, slabs); }))
+        return RI_E_WORKSPACE;
     // D = 2 C C^T, W = 1/2 D F D
     HIPC(ri::gemm_f64(false, true, N, N, no, 2.0, C, no, 0, C, no, 0, 0.0, w.D, N, 0, 1, 0, 0, st));
     HIPC(ri::gemm_f64(false, false, N, N, N, 1.0, F, N, 0, w.D, N, 0, 0.0, w.T1, N, 0, 1, 0, 0, st));

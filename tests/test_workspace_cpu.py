@@ -1,0 +1,44 @@
+"""A workspace sized for a longer pair list is enough for every shorter one, without a GPU: the calls get past their size
+check and fail at the HIP runtime, before anything is read."""
+import ctypes
+
+import pytest
+
+import paper_2407_19614_amd as P
+from paper_2407_19614_amd import binding as Bd
+
+WORKSPACE, HIP = 4, 6
+
+
+def _call(op, N, na, no, n_pairs, prec, nb):
+    d = ctypes.create_string_buffer(1 << 12)         # stands in for device memory; never read
+    p = ctypes.cast(d, ctypes.c_void_p)
+    s = Bd.RISystem(N // 10, N, na, no, *[ctypes.cast(d, ctypes.c_void_p).value] * 6)
+    B = None if prec & P.COMPRESSED else p
+    if op == Bd.OP_FOCK:
+        return P.lib().ri_fock_jk(N, na, no, B, prec, p, p, n_pairs, p, p, p, None, p, nb, None)
+    if op == Bd.OP_ENERGY:
+        o, r = Bd.SCFOpts(10, 6, 1e-10, 1e-8, 0, 0), Bd.SCFResult()
+        return P.lib().ri_energy(ctypes.byref(s), B, prec, p, p, n_pairs, ctypes.byref(o), None, p, p, None,
+                                 ctypes.byref(r), p, nb, None)
+    return P.lib().ri_gradient(ctypes.byref(s), p, n_pairs, B, prec, p, p, p, p, p, p, nb, None)
+
+
+@pytest.mark.parametrize("op", [Bd.OP_FOCK, Bd.OP_ENERGY, Bd.OP_GRADIENT])
+@pytest.mark.parametrize("prec", [P.FP64, P.FP32, P.FP64 | P.COMPRESSED, P.FP32 | P.COMPRESSED, P.FP32 | P.FINAL_FP64,
+                                  P.BF16X6, P.BF16X6 | P.FINAL_FP64])
+def test_longer_list_covers_shorter(op, prec):
+    torch = pytest.importorskip("torch")
+    if torch.cuda.is_available():
+        pytest.skip("runs on a host without a GPU")
+    if prec & P.FINAL_FP64 and op != Bd.OP_ENERGY:
+        pytest.skip("a flag of the SCF")
+    for N, na, no in ((40, 100, 4), (400, 1200, 40), (1000, 3000, 100)):
+        full = N * (N + 1) // 2
+        lists = [0, 1, full // 8, full * 3 // 5, full * 2 // 3, full]
+        size = {n: Bd.workspace_bytes(op, N, na, no, n, prec) for n in lists}
+        for longer in lists:
+            for n in lists:
+                if n <= longer:
+                    assert _call(op, N, na, no, n, prec, size[longer]) == HIP, (N, longer, n)
+        assert _call(op, N, na, no, full, prec, size[full] - 1) == WORKSPACE
