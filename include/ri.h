@@ -71,8 +71,11 @@ typedef enum {
  * not resident.  Every call that needs B decompresses the fitted tensor B_c
  * into packed tiles, RI_COMPRESSED_SLAB auxiliary functions at a time, in its
  * workspace (the per-iteration decompression of Algorithm 1), and B is passed
- * as NULL.  Results are identical to the resident form; workspace sizes from
- * ri_workspace_bytes with the same flag. */
+ * as NULL; large builds with at most 60 % of the pairs significant form X^P over
+ * the pairs from B_c instead, as the resident form does (ri_fock_jk).  Results
+ * are identical to the resident form; workspace sizes from ri_workspace_bytes
+ * with the same flag.  That size counts the slab of tiles in any case; where X^P
+ * runs over the pairs the call needs no more than the size without the flag. */
 #define RI_COMPRESSED 0x10
 #define RI_COMPRESSED_SLAB 256
 

@@ -233,6 +233,18 @@ class RIProblem:
             raise RIError(1, "ri_workspace_bytes")
         return self.workspace(nb), nb
 
+    def _call_ws(self, op, prec, call):
+        """call(workspace pointer, bytes) -> status, with the workspace of operation `op`.  A compressed call whose X runs
+        over the significant pairs needs only the size without the flag (no slab of tiles), so that is offered first; a
+        workspace that is too small is refused before anything is launched."""
+        if self.compressed:
+            nb = workspace_bytes(op, self.N, self.n_aux, self.n_occ, max(self.n_pairs or 0, 0), prec)
+            code = call(_ptr(self.workspace(nb)), nb)
+            if code != 4:
+                return code
+        ws, nb = self._ws_for(op, prec)
+        return call(_ptr(ws), nb)
+
     # -- entry points
     def build_3c(self, tau=None):
         torch = self.torch
@@ -290,10 +302,9 @@ class RIProblem:
         J = torch.empty((self.N, self.N), dtype=torch.float64, device=self.device) if J is None else J
         K = torch.empty_like(J) if K is None else K
         gamma = torch.empty(self.n_aux, dtype=torch.float64, device=self.device) if gamma is None else gamma
-        ws, nb = self._ws_for(OP_FOCK)
-        code = lib().ri_fock_jk(self.N, self.n_aux, self.n_occ, _ptr(self.B), self.pflag, _ptr(self.T),
-                                _ptr(self.pairs), self.n_pairs, _ptr(C_occ), _ptr(J), _ptr(K), _ptr(gamma),
-                                _ptr(ws), nb, self.stream())
+        code = self._call_ws(OP_FOCK, self.prec, lambda ws, nb: lib().ri_fock_jk(
+            self.N, self.n_aux, self.n_occ, _ptr(self.B), self.pflag, _ptr(self.T), _ptr(self.pairs), self.n_pairs,
+            _ptr(C_occ), _ptr(J), _ptr(K), _ptr(gamma), ws, nb, self.stream()))
         _check(code, "ri_fock_jk")
         return J, K, gamma
 
@@ -311,11 +322,10 @@ class RIProblem:
         gamma/J = e0..e1 (e2..e1 for the split-BF16 forms, whose gamma/J
         starts after X), X = e0..e2, SYRK = e2..e3 (see fock_phases)."""
         C_occ = C_occ.contiguous()
-        ws, nb = self._ws_for(OP_FOCK)
         arr = (c_void_p * 4)(*[ctypes.c_void_p(e.cuda_event) for e in events])
-        code = lib().ri_fock_jk_timed(self.N, self.n_aux, self.n_occ, _ptr(self.B), self.pflag, _ptr(self.T),
-                                      _ptr(self.pairs), self.n_pairs, _ptr(C_occ), _ptr(J), _ptr(K), _ptr(gamma),
-                                      _ptr(ws), nb, self.stream(), arr)
+        code = self._call_ws(OP_FOCK, self.prec, lambda ws, nb: lib().ri_fock_jk_timed(
+            self.N, self.n_aux, self.n_occ, _ptr(self.B), self.pflag, _ptr(self.T), _ptr(self.pairs), self.n_pairs,
+            _ptr(C_occ), _ptr(J), _ptr(K), _ptr(gamma), ws, nb, self.stream(), arr))
         _check(code, "ri_fock_jk_timed")
 
     @staticmethod
@@ -401,11 +411,10 @@ class RIProblem:
         D = torch.empty_like(F)
         res = SCFResult()
         fin = FINAL_FP64 if final_fp64 else 0
-        ws, nb = self._ws_for(OP_ENERGY, self.prec | fin)
         g = None if guess is None else guess.contiguous()
-        code = lib().ri_energy(ctypes.byref(self.c_sys), _ptr(self.B), self.pflag | fin, _ptr(self.T), _ptr(self.pairs),
-                               self.n_pairs, ctypes.byref(opts), _ptr(g), _ptr(C), _ptr(F), _ptr(D),
-                               ctypes.byref(res), _ptr(ws), nb, self.stream())
+        code = self._call_ws(OP_ENERGY, self.prec | fin, lambda ws, nb: lib().ri_energy(
+            ctypes.byref(self.c_sys), _ptr(self.B), self.pflag | fin, _ptr(self.T), _ptr(self.pairs), self.n_pairs,
+            ctypes.byref(opts), _ptr(g), _ptr(C), _ptr(F), _ptr(D), ctypes.byref(res), ws, nb, self.stream()))
         if code == 3 and not raise_on_noconv:
             return res.as_dict(), C, F, D
         _check(code, "ri_energy")
@@ -427,10 +436,9 @@ class RIProblem:
         C_occ = self.C_occ if C_occ is None else C_occ
         F = self.F if F is None else F
         g = torch.empty((self.system.n_centres, 3), dtype=torch.float64, device=self.device)
-        ws, nb = self._ws_for(OP_GRADIENT)
-        code = lib().ri_gradient(ctypes.byref(self.c_sys), _ptr(self.pairs), self.n_pairs, _ptr(self.B), self.pflag,
-                                 _ptr(self.T), _ptr(self.Linv), _ptr(C_occ), _ptr(F), _ptr(g), _ptr(ws), nb,
-                                 self.stream())
+        code = self._call_ws(OP_GRADIENT, self.prec, lambda ws, nb: lib().ri_gradient(
+            ctypes.byref(self.c_sys), _ptr(self.pairs), self.n_pairs, _ptr(self.B), self.pflag, _ptr(self.T),
+            _ptr(self.Linv), _ptr(C_occ), _ptr(F), _ptr(g), ws, nb, self.stream()))
         _check(code, "ri_gradient")
         return g
 

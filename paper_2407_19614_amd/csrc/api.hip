@@ -111,6 +111,8 @@ MetricWS carve_metric(Arena& a, int N, int n_aux, int64_t n_pairs) {
 }
 
 // Slab buffers of the compressed form: pair map and one slab of packed tiles.
+// A call whose X runs over the partner lists does not take them; the size that
+// ri_workspace_bytes reports (a dry arena) counts them for either form of X.
 struct SlabWS {
     int32_t* map = nullptr;
     void* Bs = nullptr;
@@ -166,8 +168,9 @@ FockWS carve_fock(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_p
                   bool wide = false) {
     FockWS w;
     const int xprec = wide ? (int)RI_FP32 : prec;
-    if (lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, xprec)) w.xs = carve_sparse(a, N, n_aux, n_pairs, xprec == RI_FP32);
-    w.sw = carve_slab(a, N, n_aux, prec, comp);   // the compressed form's size contract holds for either form of X
+    lists = lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, xprec);
+    if (lists) w.xs = carve_sparse(a, N, n_aux, n_pairs, xprec == RI_FP32);
+    w.sw = carve_slab(a, N, n_aux, prec, comp && (!lists || a.dry));
     const int Npad = ri::xt_ld(N);
     w.js = ri::j_split_count(n_aux);
     if (is_bf16(prec)) {
@@ -272,8 +275,9 @@ struct GradWS { double *D, *W, *T1, *dpair, *gamma, *c, *Bij, *Xi, *Zx, *part, *
 GradWS carve_grad(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_pairs, int n_centres, int prec,
                   bool comp = false) {
     GradWS w;
-    if (lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, prec)) w.xs = carve_sparse(a, N, n_aux, n_pairs, prec == RI_FP32);
-    w.sw = carve_slab(a, N, n_aux, prec, comp);   // the compressed form's size contract holds for either form of X
+    lists = lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, prec);
+    if (lists) w.xs = carve_sparse(a, N, n_aux, n_pairs, prec == RI_FP32);
+    w.sw = carve_slab(a, N, n_aux, prec, comp && (!lists || a.dry));
     const int Npad = ri::xt_ld(N);
     const int64_t n2 = (int64_t)N * N, o2 = (int64_t)n_occ * n_occ;
     w.D = a.take<double>(n2);

@@ -97,3 +97,25 @@ def test_scf_and_gradient(prec_name, final):
     torch.cuda.synchronize()
     # sums over all pairs and auxiliaries by atomic adds; Xi carries the metric's condition
     assert float((g0 - g1).abs().max()) < 1e-9 * max(1.0, float(g0.abs().max()))
+
+
+@pytest.mark.parametrize("prec_name", ["FP64", "FP32"])
+def test_compressed_calls_hold_no_slab_beside_the_lists(prec_name):
+    need_gpu()
+    import paper_2407_19614_amd as P
+    from paper_2407_19614_amd import binding as Bd
+    prec = getattr(P, prec_name)
+    print(f"case: compressed over the lists, {prec_name}", flush=True)
+    s = _system(44, 44)
+    out = []
+    for comp in (False, True):
+        pr = P.RIProblem(s, prec=prec, compressed=comp)
+        pr.build_3c()
+        pr.metric_factor(prec)
+        r, C, F, _ = pr.energy(max_iter=60, tol_E=1e-8, tol_err=1e-5)
+        out.append((r["E_total"], C, F, *pr.fock_jk(C), pr.gradient(C, F)))
+    assert out[0][0] == out[1][0] and all(torch.equal(a, b) for a, b in zip(out[0][1:-1], out[1][1:-1]))
+    assert float((out[0][-1] - out[1][-1]).abs().max()) < 1e-9 * max(1.0, float(out[0][-1].abs().max()))
+    most = max(Bd.workspace_bytes(op, s.N, s.n_aux, s.n_occ, pr.n_pairs, prec)
+               for op in (Bd.OP_FOCK, Bd.OP_ENERGY, Bd.OP_GRADIENT))
+    assert pr._ws.numel() <= most

@@ -42,3 +42,20 @@ def test_longer_list_covers_shorter(op, prec):
                 if n <= longer:
                     assert _call(op, N, na, no, n, prec, size[longer]) == HIP, (N, longer, n)
         assert _call(op, N, na, no, full, prec, size[full] - 1) == WORKSPACE
+
+
+@pytest.mark.parametrize("op", [Bd.OP_FOCK, Bd.OP_ENERGY, Bd.OP_GRADIENT])
+@pytest.mark.parametrize("prec", [P.FP64, P.FP32])
+def test_compressed_needs_no_slab_beside_the_lists(op, prec):
+    torch = pytest.importorskip("torch")
+    if torch.cuda.is_available():
+        pytest.skip("runs on a host without a GPU")
+    # X over the significant pairs: the size without the flag is enough
+    for N, na, no, n in ((1000, 3000, 100, 68799), (440, 1320, 44, 24102)):
+        nb = Bd.workspace_bytes(op, N, na, no, n, prec)
+        assert nb < Bd.workspace_bytes(op, N, na, no, n, prec | P.COMPRESSED)
+        assert _call(op, N, na, no, n, prec | P.COMPRESSED, nb) == HIP
+    # a full list, and a small build: X slab by slab, which needs it
+    for N, na, no, n in ((1000, 3000, 100, 500500), (40, 100, 4, 300)):
+        nb = Bd.workspace_bytes(op, N, na, no, n, prec)
+        assert _call(op, N, na, no, n, prec | P.COMPRESSED, nb) == WORKSPACE
