@@ -127,7 +127,8 @@ SlabWS carve_slab(Arena& a, int N, int n_aux, int prec, bool comp) {
     return w;
 }
 
-ri::XSparse carve_sparse(Arena& a, int N, int n_aux, int64_t n_pairs, bool f32 = false) {
+// coulomb: with the scratch of gamma and J from the transposed copy
+ri::XSparse carve_sparse(Arena& a, int N, int n_aux, int64_t n_pairs, bool f32, bool coulomb) {
     ri::XSparse w;
     w.ldp = ri::xs_ldp(n_aux);
     w.lmax = ri::xs_lmax(N);
@@ -137,7 +138,7 @@ ri::XSparse carve_sparse(Arena& a, int N, int n_aux, int64_t n_pairs, bool f32 =
     w.n_pairs = n_pairs;
     if (f32) w.BcT32 = a.take<float>((n_pairs + 1) * w.ldp);
     else w.BcT = a.take<double>((n_pairs + 1) * w.ldp);
-    if (!f32) w.gpart = a.take<double>(ri::xs_gpart(n_aux, n_pairs));
+    if (coulomb && !f32) w.gpart = a.take<double>(ri::xs_gpart(n_aux, n_pairs));
     return w;
 }
 
@@ -169,7 +170,7 @@ FockWS carve_fock(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_p
     FockWS w;
     const int xprec = wide ? (int)RI_FP32 : prec;
     lists = lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, xprec);
-    if (lists) w.xs = carve_sparse(a, N, n_aux, n_pairs, xprec == RI_FP32);
+    if (lists) w.xs = carve_sparse(a, N, n_aux, n_pairs, xprec == RI_FP32, true);
     w.sw = carve_slab(a, N, n_aux, prec, comp && (!lists || a.dry));
     const int Npad = ri::xt_ld(N);
     w.js = ri::j_split_count(n_aux);
@@ -201,15 +202,15 @@ struct DensityWS {
     ri::KDensity k;
     int js;
 };
-DensityWS carve_density(Arena& a, int N, int n_aux, int64_t n_pairs) {
+DensityWS carve_density(Arena& a, int N, int n_aux, int64_t n_pairs, int slab) {
     DensityWS w;
     const int Npad = ri::xt_ld(N);
     w.js = ri::j_split_count(n_aux);
     w.dpair = a.take<double>(std::max<int64_t>(n_pairs, 1));
     w.jpart = a.take<double>((int64_t)w.js * std::max<int64_t>(n_pairs, 1));
     w.gamma = a.take<double>(n_aux);
-    w.k.slab = ri::density_slab(N, n_aux);
-    w.k.xs = carve_sparse(a, N, w.k.slab, n_pairs);
+    w.k.slab = slab;
+    w.k.xs = carve_sparse(a, N, w.k.slab, n_pairs, false, false);
     w.k.ks = ri::k_split_count(N, w.k.slab, N);
     w.k.Dp = a.take<double>(ri::cpad_elems(N, N));
     w.k.Bf = a.take<double>(ri::xt_rows(w.k.slab, N) * Npad);
@@ -234,16 +235,17 @@ struct EnergyWS {
     FockWS fin;   // final FP64 exchange build of the split-BF16 forms: FP64 Xt and slabs of B_c
     DensityWS dens;
 };
+// Room for a density start beside the iterations' buffers.  Its Fock build with a
+// workspace of its own takes up to 1.2 GiB; N = 170 with 32, 64, 128, 256 MiB of
+// room and all of it: start and first iteration 2.25, 2.24, 1.74, 1.66, 1.59 ms;
+// N = 400: 7.88, 7.87, 7.87, 7.44, 7.15; no difference from N = 600 on.
+constexpr size_t DENSITY_ROOM = size_t(256) << 20;
 EnergyWS carve_energy(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, int diis_n,
                       bool comp = false, bool fin_slab = false, bool wide = false) {
     EnergyWS w;
     const int64_t n2 = (int64_t)N * N;
     double** mats[] = {&w.S, &w.H, &w.Ls, &w.LinvS, &w.J, &w.K, &w.F, &w.D, &w.T1, &w.T2, &w.Fx, &w.X, &w.X2};
     for (double** m : mats) *m = a.take<double>(n2);
-    for (int i = 0; i < 8; ++i) {
-        w.dF[i] = i < diis_n ? a.take<double>(n2) : nullptr;
-        w.dE[i] = i < diis_n ? a.take<double>(n2) : nullptr;
-    }
     w.Bfull = a.take<double>(64);
     w.coef = a.take<double>(8);
     w.Y = a.take<double>((int64_t)N * n_occ);
@@ -258,9 +260,28 @@ EnergyWS carve_energy(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t
     w.tpart = a.take<double>(4 * (int64_t)ri::tc2f_tiles(N));   // purification partial sums, two parities
     w.bad = a.take<int>(2);
     w.tst = a.take<int>(16);                                    // purification state, two parities
+    const size_t loop = a.off;   // used by the SCF iterations only, from here
+    for (int i = 0; i < 8; ++i) {
+        w.dF[i] = i < diis_n ? a.take<double>(n2) : nullptr;
+        w.dE[i] = i < diis_n ? a.take<double>(n2) : nullptr;
+    }
     w.fock = carve_fock(a, lists, N, n_aux, n_occ, n_pairs, prec, comp, wide);
     w.fin = fin_slab ? carve_fock(a, lists, N, n_aux, n_occ, n_pairs, RI_FP64, true) : FockWS{};
-    w.dens = carve_density(a, N, n_aux, n_pairs);
+    // The Fock build of a density start is over before the first iteration, so it
+    // takes the iterations' space and at most DENSITY_ROOM more, with the largest
+    // slab that fits there.
+    auto density_bytes = [&](int slab) {
+        Arena d{nullptr, 0, 0, true};
+        carve_density(d, N, n_aux, n_pairs, slab);
+        return d.off;
+    };
+    int slab = ri::density_slab(N, n_aux);
+    a.take<char>((int64_t)std::min(DENSITY_ROOM, density_bytes(slab)));
+    const size_t end = a.off;
+    while (slab > ri::DENSITY_SLAB_MIN && density_bytes(slab) > end - loop) slab = ri::density_slab_below(slab);
+    a.off = loop;
+    w.dens = carve_density(a, N, n_aux, n_pairs, slab);
+    a.off = std::max(a.off, end);
     return w;
 }
 
@@ -276,7 +297,7 @@ GradWS carve_grad(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_p
                   bool comp = false) {
     GradWS w;
     lists = lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, prec);
-    if (lists) w.xs = carve_sparse(a, N, n_aux, n_pairs, prec == RI_FP32);
+    if (lists) w.xs = carve_sparse(a, N, n_aux, n_pairs, prec == RI_FP32, false);
     w.sw = carve_slab(a, N, n_aux, prec, comp && (!lists || a.dry));
     const int Npad = ri::xt_ld(N);
     const int64_t n2 = (int64_t)N * N, o2 = (int64_t)n_occ * n_occ;
@@ -531,7 +552,7 @@ size_t ri_workspace_bytes(int32_t op, int32_t N, int32_t n_aux, int32_t n_occ, i
                 carve_grad(b, lists, N, n_aux, n_occ, n_pairs, 2048, is_bf16(prec) ? RI_FP64 : prec,
                            pp.comp || is_bf16(prec));
             });
-        case RI_OP_FOCK_DENSITY: carve_density(a, N, n_aux, n_pairs); break;
+        case RI_OP_FOCK_DENSITY: carve_density(a, N, n_aux, n_pairs, ri::density_slab(N, n_aux)); break;
         case RI_OP_MLP: {
             size_t off = 0;
             ri::carve_mlp(nullptr, 0, off, std::max<int64_t>(n_pairs, 1));
@@ -710,7 +731,7 @@ int32_t ri_fock_jk_density(int32_t N, int32_t n_aux, const double* Bc, const int
     if (N <= 0 || n_aux <= 0 || n_pairs < 0 || !D || !J || !K || !ws || (n_pairs > 0 && (!Bc || !pairs)))
         return RI_E_ARG;
     Arena a{(char*)ws, ws_bytes, 0, false};
-    DensityWS w = carve_density(a, N, n_aux, n_pairs);
+    DensityWS w = carve_density(a, N, n_aux, n_pairs, ri::density_slab(N, n_aux));
     if (!a.ok()) return RI_E_WORKSPACE;
     HIPC(jk_density(Bc, pairs, n_pairs, N, n_aux, D, J, K, gamma, w, st));
     return RI_OK;

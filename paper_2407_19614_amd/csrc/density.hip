@@ -38,14 +38,18 @@ __global__ void pad_symmetric_kernel(const double* __restrict__ D, int N, int ro
 namespace ri {
 
 // Auxiliaries a slab: whole blocks of 64, as many as keep the slab's B^P and
-// D B^P at 512 MiB each, so that a slab's launches fill the chip at small N; a
-// quarter of a block where 64 would take more than 16 GiB (N over 5700).
+// D B^P at 512 MiB each, so that a slab's launches fill the chip at small N; above
+// N = 1024 a block of 64, halved while it takes more than 1 GiB (32 from N =
+// 1450 on, 8 from N = 2890 on).
 int density_slab(int N, int n_aux) {
-    const int64_t per = (int64_t)64 * N * xt_ld(N) * 8;
-    if (per > (int64_t(1) << 34)) return std::min(16, n_aux);
-    const int64_t want = std::max<int64_t>(1, (int64_t(1) << 29) / per) * 64;
+    const int64_t per = (int64_t)N * xt_ld(N) * 8;
+    int64_t want = (int64_t(1) << 29) / (64 * per) * 64;
+    if (want == 0)
+        for (want = 64; want > DENSITY_SLAB_MIN && want * per > (int64_t(1) << 30);) want /= 2;
     return (int)std::min<int64_t>({want, n_aux, 32768});   // a grid dimension takes 65535
 }
+
+int density_slab_below(int slab) { return slab > 64 ? (slab - 1) / 64 * 64 : slab / 2; }
 
 hipError_t k_density(const double* Bc, const int32_t* pairs, int64_t n_pairs, int N, int n_aux, const double* D,
                      const KDensity& w, double* K, hipStream_t st) {

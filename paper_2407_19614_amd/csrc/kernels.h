@@ -126,7 +126,9 @@ struct KDensity {
     double *Dp, *Bf, *Y, *part;       // padded D; one slab of full B^P and of D B^P, rows (P, sigma); K partials
     int slab, ks;
 };
+constexpr int DENSITY_SLAB_MIN = 8;
 int density_slab(int N, int n_aux);
+int density_slab_below(int slab);     // the next smaller one to try, for slab > DENSITY_SLAB_MIN
 hipError_t k_density(const double* Bc, const int32_t* pairs, int64_t n_pairs, int N, int n_aux, const double* D,
                      const KDensity& w, double* K, hipStream_t st);
 int j_split_count(int n_aux);

@@ -59,3 +59,19 @@ def test_compressed_needs_no_slab_beside_the_lists(op, prec):
     for N, na, no, n in ((1000, 3000, 100, 500500), (40, 100, 4, 300)):
         nb = Bd.workspace_bytes(op, N, na, no, n, prec)
         assert _call(op, N, na, no, n, prec | P.COMPRESSED, nb) == WORKSPACE
+
+
+def test_scf_holds_no_space_of_its_own_for_the_density_start():
+    # the SCF's N x N matrices (13 and 16 of the DIIS ring), reduction scratch and N x n_occ blocks beside its Fock build,
+    # and 256 MiB of room for the Fock build of a density start, which is over before the iterations begin
+    for N, np_ in ((170, 11000), (400, 21000), (1000, 67325), (2000, 200000), (4000, 480000)):
+        na, no = 3 * N, N // 10
+        for prec in (P.FP64, P.FP32):
+            extra = Bd.workspace_bytes(Bd.OP_ENERGY, N, na, no, np_, prec) - Bd.workspace_bytes(Bd.OP_FOCK, N, na, no, np_, prec)
+            assert extra <= 30 * N * N * 8 + 6 * N * no * 8 + 4 * (N // 32 + 64) * 4096 * 8 + (256 << 20), (N, prec)
+    # the build of a density itself: B^P and D B^P of a slab, at most 1 GiB each, the transposed copy of 64 auxiliaries
+    for N, np_ in ((1000, 67325), (2000, 200000), (4000, 480000), (8000, 1200000)):
+        nb = Bd.workspace_bytes(Bd.OP_FOCK_DENSITY, N, 3 * N, 1, np_, P.FP64)
+        pad = (N + 127) // 128 * 128
+        one = max(1 << 30, 8 * N * pad * 8)
+        assert nb <= 2 * one + np_ * (64 + 17) * 8 + 4 * pad * pad * 8 + (N * (N + 256) * 8 + (1 << 25)), N
