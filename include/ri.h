@@ -454,7 +454,8 @@ typedef struct {
 
 /* Workspace bytes for ri_energy_batched (0 on invalid input).  Supported:
  * prec RI_FP64, RI_FP32 or RI_FP32 | RI_FINAL_FP64, n_occ <= 64 for every
- * molecule. */
+ * molecule.  Not smaller for longer pair lists: sized for the longest lists it
+ * is enough for any. */
 size_t ri_energy_batched_workspace(int32_t n_mol, const ri_system* sys, const ri_batch_mol* mol, int32_t prec);
 
 /* Launch shapes of the batched SCF per size bucket.  Molecule m belongs to

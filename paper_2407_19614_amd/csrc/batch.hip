@@ -693,10 +693,13 @@ static int32_t batch_layout(int32_t n_mol, const ri_system* sys, const ri_batch_
         // enough that a row's list fills whole steps
         m.sp = N >= BATCH_SP_MIN && ri::xs_sparse(N, na, m.n_pairs);
         m.lmax = ri::xs_lmax(N);
-        if (m.sp) {
+        if (N >= BATCH_SP_MIN) {
+            // room for as many pairs as may take this form, so that a workspace sized for
+            // longer lists is enough for shorter ones
+            const int64_t most = std::min(m.n_pairs, ri::xs_most_pairs(N, na));
             m.plist = cv.take<int2>((int64_t)N * m.lmax);
             m.pcnt = cv.take<int>(N);
-            m.BcT = cv.take<char>((m.n_pairs + 1) * ri::xs_ldp(na) * (prec == RI_FP64 ? 8 : 4));
+            m.BcT = cv.take<char>((most + 1) * ri::xs_ldp(na) * (prec == RI_FP64 ? 8 : 4));
         }
         m.Y = cv.take<double>((int64_t)N * no);
         m.Cp = cv.take<double>((int64_t)N * no);

@@ -70,6 +70,7 @@ struct XSparse {
 // the dense form and its workspace, which need no partner lists or copy).
 bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs, int prec);
 bool xs_sparse(int N, int n_aux, int64_t n_pairs);   // the first two conditions
+int64_t xs_most_pairs(int N, int n_aux);             // the most pairs that meet them
 int xs_ldp(int n_aux);
 int xs_lmax(int N);
 int64_t xs_gpart(int n_aux, int64_t n_pairs);

@@ -503,6 +503,12 @@ bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs, int prec) {
            xt_rows(n_aux, n_occ) * xt_ld(N) * (prec == RI_FP64 ? 8 : 4) > (int64_t)RI_NOALLOC_SCRATCH_BYTES;
 }
 
+int64_t xs_most_pairs(int N, int n_aux) {
+    int64_t n = std::min<int64_t>((int64_t)((0.6 * N * N + N) / 2), ((int64_t)1 << 33) / xs_ldp(n_aux) - 1) + 1;
+    while (n > 0 && !xs_sparse(N, n_aux, n)) --n;
+    return n;
+}
+
 int xs_ldp(int n_aux) { return (n_aux + 63) / 64 * 64; }
 int xs_lmax(int N) { return (N + 63) / 64 * 64 + 128; }
 

@@ -75,3 +75,28 @@ def test_scf_holds_no_space_of_its_own_for_the_density_start():
         pad = (N + 127) // 128 * 128
         one = max(1 << 30, 8 * N * pad * 8)
         assert nb <= 2 * one + np_ * (64 + 17) * 8 + 4 * pad * pad * 8 + (N * (N + 256) * 8 + (1 << 25)), N
+
+
+@pytest.mark.parametrize("prec", [P.FP64, P.FP32, P.FP32 | P.FINAL_FP64])
+def test_batch_longer_lists_cover_shorter(prec):
+    torch = pytest.importorskip("torch")
+    if torch.cuda.is_available():
+        pytest.skip("runs on a host without a GPU")
+    d = ctypes.create_string_buffer(1 << 12)
+    a = ctypes.cast(d, ctypes.c_void_p).value
+    sizes = [(100, 300, 10), (149, 450, 14), (150, 450, 15), (333, 999, 33), (600, 1800, 60)]
+    n = len(sizes)
+    sys_ = (Bd.RISystem * n)(*[Bd.RISystem(N // 10, N, na, no, a, a, a, a, a, a) for N, na, no in sizes])
+
+    def mols(f):
+        return (Bd.BatchMol * n)(*[Bd.BatchMol(a, a, a, int(f * N * (N + 1) / 2), a, None) for N, _, _ in sizes])
+
+    fills = [0.0, 0.01, 0.3, 0.59, 0.6, 0.61, 1.0]
+    need = [P.lib().ri_energy_batched_workspace(n, ctypes.byref(sys_), ctypes.byref(mols(f)), prec) for f in fills]
+    assert need == sorted(need)
+    opts, res = Bd.SCFOpts(10, 6, 1e-10, 1e-8, 0, 0), (Bd.SCFResult * n)()
+    for f, nb in zip(fills, need):
+        args = [n, ctypes.byref(sys_), ctypes.byref(mols(f)), prec, ctypes.byref(opts), 0, None, ctypes.byref(res),
+                ctypes.c_void_p(a)]
+        assert P.lib().ri_energy_batched(*args, nb - 1, None) == WORKSPACE
+        assert P.lib().ri_energy_batched(*args, need[-1], None) == HIP
