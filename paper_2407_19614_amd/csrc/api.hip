@@ -312,7 +312,7 @@ GradWS carve_grad(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_p
     w.Zx = a.take<double>((int64_t)n_aux * n_aux);
     w.part = a.take<double>((int64_t)(3 * ri::GRAD_BLOCKS + 1) * 3 * std::max(n_centres, 1));
     w.Cp = a.take<double>(ri::cpad_elems(N, n_occ));
-    w.WY = a.take<double>((int64_t)ri::grad_slab(N, n_aux) * N * N);   // U^P C^T, one slab of P
+    w.WY = a.take<double>(ri::grad_wy_elems(N, n_aux, n_pairs));   // U^P C^T, one slab of P
     w.rows = a.take<int32_t>(N + 2);
     w.pscr = a.take<double>(ri::grad_pair_elems(n_pairs));
     // X^T for B_ij, reused afterwards for U^P = C Xi^P ([n_aux][N][n_occ])

@@ -796,8 +796,8 @@ hipError_t grad_three_centre(const ri_system* s, const int32_t* pairs, int64_t n
     pair_consts_kernel<<<(unsigned)((n_pairs + 255) / 256 + 2), 256, 0, st>>>(s->xyz, s->fn_centre, s->fn_exp, pairs,
                                                                               n_pairs, D, N, pc, ctr, bt);
     RI_TRY(hipGetLastError());
-    // auxiliaries at a time that WY holds (at least twice grad_slab: a pair counts once)
-    const int ns = (int)std::min<int64_t>(na, (int64_t)grad_slab(N, na) * N * N / n_pairs);
+    // auxiliaries at a time that WY holds (nearly twice grad_slab where every pair is listed once)
+    const int ns = (int)std::min<int64_t>(na, grad_wy_elems(N, na, n_pairs) / n_pairs);
     for (int P0 = 0; P0 < na; P0 += ns) {
         const int np = std::min(ns, na - P0);
         for (int k0 = 0; k0 < n_occ; k0 += 128) {
@@ -821,6 +821,9 @@ hipError_t grad_three_centre(const ri_system* s, const int32_t* pairs, int64_t n
         RI_TRY(hipGetLastError());
     }
     return hipSuccess;
+}
+int64_t grad_wy_elems(int N, int n_aux, int64_t n_pairs) {
+    return std::max((int64_t)grad_slab(N, n_aux) * N * N, n_pairs);
 }
 int64_t grad_pair_elems(int64_t n_pairs) { return (PC_N + 2) * n_pairs + BT_N * BT_M; }
 hipError_t grad_nuclear(const ri_system* s, double* part, hipStream_t st) {

@@ -193,9 +193,11 @@ hipError_t grad_metric_z(const double* Xi, int n_aux, int64_t K, double* tmp, in
                          hipStream_t st);
 // Three-centre term, U^P = C Xi^P, [n_aux][N][n_occ].  (U^P C^T)_mu_nu is formed
 // on MFMA at the significant pairs, for as many auxiliary indices at a time as
-// WY holds (workspace of grad_slab * N * N doubles), and the derivative kernel
+// WY holds (workspace of grad_wy_elems doubles: grad_slab * N * N, and at least one
+// auxiliary of a list that names pairs repeatedly), and the derivative kernel
 // reads it there.  The pairs may be in any order.  rows: N + 2 ints of scratch; pscratch: grad_pair_elems doubles.
 int grad_slab(int N, int n_aux);
+int64_t grad_wy_elems(int N, int n_aux, int64_t n_pairs);
 // U[p] = C Xi^p for p < np: C [N][K], Xi [np][K][K] with symmetric blocks,
 // U [np][N][K].
 hipError_t u_products(const double* C, const double* Xi, int N, int K, int np, double* U, hipStream_t st);
