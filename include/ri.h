@@ -71,10 +71,9 @@ typedef enum {
  * not resident.  Every call that needs B decompresses the fitted tensor B_c
  * into packed tiles, RI_COMPRESSED_SLAB auxiliary functions at a time, in its
  * workspace (the per-iteration decompression of Algorithm 1), and B is passed
- * as NULL; large builds with at most 60 % of the pairs significant form X^P over
- * the pairs from B_c instead, as the resident form does (ri_fock_jk).  Results
- * are identical to the resident form; workspace sizes from ri_workspace_bytes
- * with the same flag.  That size counts the slab of tiles in any case; where X^P
+ * as NULL; large builds with few of the pairs significant form X^P over the pairs
+ * from B_c instead (ri_fock_jk).  Results are identical to the resident form;
+ * workspace sizes from ri_workspace_bytes with the same flag.  That size counts the slab of tiles in any case; where X^P
  * runs over the pairs the call needs no more than the size without the flag. */
 #define RI_COMPRESSED 0x10
 #define RI_COMPRESSED_SLAB 256
@@ -190,9 +189,10 @@ int32_t ri_pack_b(int32_t N, int32_t n_aux, const double* Bc, const int32_t* pai
  *   B       packed B in precision `prec` (from ri_metric_factor), or NULL
  *           with prec | RI_COMPRESSED: X^P is then formed slab by slab from
  *           Bc (Algorithm 1's per-iteration decompression).  In FP64 and FP32,
- *           large builds with at most 60 % of the pairs significant form X^P
- *           over those pairs, from Bc, and do not read B (where the workspace
- *           has room for it, see ri_workspace_bytes).
+ *           large builds with few of the pairs significant (at most 60 %, or,
+ *           while X^P is under 512 MiB, 42 % in FP64 and with a resident B 34 %
+ *           in FP32) form X^P over those pairs, from Bc, and do not read B
+ *           (where the workspace has room for it, see ri_workspace_bytes).
  *   Bc      [n_aux][n_pairs] FP64 fitted tensor on compressed pairs, and
  *   pairs   [n_pairs][2]: gamma and J are formed from these in FP64 for
  *           every precision.
@@ -530,7 +530,7 @@ enum { RI_OP_BUILD_3C = 0, RI_OP_METRIC = 1, RI_OP_FOCK = 2, RI_OP_ENERGY = 3,
 
 /* Bytes of workspace an operation needs (0 on invalid arguments).  The Fock
  * build, the SCF and the gradient run X^P over the significant pairs of large
- * builds with at most 60 % of them (ri_fock_jk), for which the size holds a
+ * builds with few enough of them (ri_fock_jk), for which the size holds a
  * second, transposed copy of B_c; it is therefore not monotone in n_pairs, but
  * a workspace sized for a longer list is always enough for a shorter one: where
  * it has no room for the copy, X^P is formed from packed tiles (the same bits in

@@ -165,11 +165,17 @@ hipError_t x_any(const void* B, int prec, int N, int n_aux, int n_occ, const dou
 
 struct FockWS { void* Xt; double* part; double* dpair; double* jpart; double* gamma; double* Cp; int ks, js; SlabWS sw; ri::XSparse xs; };
 // wide: FP32-stored B in the FP64 layout (FP32 iterations and an FP64 build at the end)
-FockWS carve_fock(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, bool comp = false,
+// One build (as against an SCF's) over the lists pays up to a lower fill where it
+// could read resident tiles (ri::xs_wanted).  The compressed form would gain in any
+// case; in FP64, where the two forms sum in different orders, it follows the
+// resident form all the same, whose results it promises.
+bool lists_once(int prec, bool comp) { return !comp || prec == RI_FP64; }
+
+FockWS carve_fock(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_pairs, int prec, bool comp, bool once,
                   bool wide = false) {
     FockWS w;
     const int xprec = wide ? (int)RI_FP32 : prec;
-    lists = lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, xprec);
+    lists = lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, xprec, once && lists_once(xprec, comp));
     if (lists) w.xs = carve_sparse(a, N, n_aux, n_pairs, xprec == RI_FP32, true);
     w.sw = carve_slab(a, N, n_aux, prec, comp && (!lists || a.dry));
     const int Npad = ri::xt_ld(N);
@@ -265,8 +271,8 @@ EnergyWS carve_energy(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t
         w.dF[i] = i < diis_n ? a.take<double>(n2) : nullptr;
         w.dE[i] = i < diis_n ? a.take<double>(n2) : nullptr;
     }
-    w.fock = carve_fock(a, lists, N, n_aux, n_occ, n_pairs, prec, comp, wide);
-    w.fin = fin_slab ? carve_fock(a, lists, N, n_aux, n_occ, n_pairs, RI_FP64, true) : FockWS{};
+    w.fock = carve_fock(a, lists, N, n_aux, n_occ, n_pairs, prec, comp, false, wide);
+    w.fin = fin_slab ? carve_fock(a, lists, N, n_aux, n_occ, n_pairs, RI_FP64, true, false) : FockWS{};
     // The Fock build of a density start is over before the first iteration, so it
     // takes the iterations' space and at most DENSITY_ROOM more, with the largest
     // slab that fits there.
@@ -296,7 +302,7 @@ struct GradWS { double *D, *W, *T1, *dpair, *gamma, *c, *Bij, *Xi, *Zx, *part, *
 GradWS carve_grad(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_pairs, int n_centres, int prec,
                   bool comp = false) {
     GradWS w;
-    lists = lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, prec);
+    lists = lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, prec, lists_once(prec, comp));
     if (lists) w.xs = carve_sparse(a, N, n_aux, n_pairs, prec == RI_FP32, false);
     w.sw = carve_slab(a, N, n_aux, prec, comp && (!lists || a.dry));
     const int Npad = ri::xt_ld(N);
@@ -541,7 +547,9 @@ size_t ri_workspace_bytes(int32_t op, int32_t N, int32_t n_aux, int32_t n_occ, i
         case RI_OP_BUILD_3C: carve_build(a, N); break;
         case RI_OP_METRIC: carve_metric(a, N, n_aux, n_pairs); break;
         case RI_OP_FOCK:
-            return carve_bytes([&](Arena& b, bool lists) { carve_fock(b, lists, N, n_aux, n_occ, n_pairs, prec, pp.comp); });
+            return carve_bytes([&](Arena& b, bool lists) {
+                carve_fock(b, lists, N, n_aux, n_occ, n_pairs, prec, pp.comp, true);
+            });
         case RI_OP_ENERGY:
             return carve_bytes([&](Arena& b, bool lists) {
                 carve_energy(b, lists, N, n_aux, n_occ, n_pairs, energy_layout(pp), 8, pp.comp, energy_fin_slab(pp),
@@ -682,7 +690,9 @@ int32_t ri_fock_jk(int32_t N, int32_t n_aux, int32_t n_occ, const void* B, int32
     if (!pp.ok || (is_bf16(prec) && n_occ > 128)) return RI_E_UNSUPPORTED;
     if (pp.comp) B = nullptr;
     FockWS w;
-    if (!carve_fit(ws, ws_bytes, [&](Arena& a, bool lists) { w = carve_fock(a, lists, N, n_aux, n_occ, n_pairs, prec, pp.comp); }))
+    if (!carve_fit(ws, ws_bytes, [&](Arena& a, bool lists) {
+            w = carve_fock(a, lists, N, n_aux, n_occ, n_pairs, prec, pp.comp, true);
+        }))
         return RI_E_WORKSPACE;
     return fock_impl(N, n_aux, n_occ, B, prec, Bc, pairs, n_pairs, C, J, K, gamma, w, st);
 }
@@ -698,13 +708,13 @@ int32_t ri_fock_jk_noalloc(int32_t N, int32_t n_aux, int32_t n_occ, const void* 
     if (!pp.ok || (is_bf16(prec) && n_occ > 128)) return RI_E_UNSUPPORTED;
     if (pp.comp) B = nullptr;
     Arena dry{nullptr, 0, 0, true};
-    carve_fock(dry, false, N, n_aux, n_occ, n_pairs, prec, pp.comp);
+    carve_fock(dry, false, N, n_aux, n_occ, n_pairs, prec, pp.comp, true);
     if (dry.off + 256 > RI_NOALLOC_SCRATCH_BYTES) return RI_E_WORKSPACE;
     void* ws = nullptr;
     const int32_t rc = noalloc_scratch(&ws);
     if (rc != RI_OK) return rc;
     Arena a{(char*)ws, RI_NOALLOC_SCRATCH_BYTES, 0, false};
-    FockWS w = carve_fock(a, false, N, n_aux, n_occ, n_pairs, prec, pp.comp);
+    FockWS w = carve_fock(a, false, N, n_aux, n_occ, n_pairs, prec, pp.comp, true);
     return fock_impl(N, n_aux, n_occ, B, prec, Bc, pairs, n_pairs, C, J, K, gamma, w, st, nullptr, false);
 }
 
@@ -720,7 +730,9 @@ int32_t ri_fock_jk_timed(int32_t N, int32_t n_aux, int32_t n_occ, const void* B,
     if (!pp.ok || (is_bf16(prec) && n_occ > 128)) return RI_E_UNSUPPORTED;
     if (pp.comp) B = nullptr;
     FockWS w;
-    if (!carve_fit(ws, ws_bytes, [&](Arena& a, bool lists) { w = carve_fock(a, lists, N, n_aux, n_occ, n_pairs, prec, pp.comp); }))
+    if (!carve_fit(ws, ws_bytes, [&](Arena& a, bool lists) {
+            w = carve_fock(a, lists, N, n_aux, n_occ, n_pairs, prec, pp.comp, true);
+        }))
         return RI_E_WORKSPACE;
     return fock_impl(N, n_aux, n_occ, B, prec, Bc, pairs, n_pairs, C, J, K, gamma, w, st, events);
 }

@@ -67,8 +67,19 @@ struct XSparse {
 // (its multiplications are those of the pairs; above, the dense kernel's whole
 // tiles cost no more than the gathers), the copy is at most 64 GiB, and X^T is
 // over 64 MiB (builds that fit the static scratch of ri_fock_jk_noalloc keep
-// the dense form and its workspace, which need no partner lists or copy).
-bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs, int prec);
+// the dense form and its workspace, which need no partner lists or copy).  once:
+// the lists and the copy, prepared in the call, serve one build that could read
+// resident tiles; up to 512 MiB of X^T that pays up to 42 % (FP32: 34 %) only.
+// Measured, time on tiles over time on lists with their preparation:
+//   one Fock build, FP64: N = 300 1.11, 1.02, 0.86 at 29, 39, 50 % fill; N = 400
+//     1.22, 1.05, 0.98 at 26, 40, 47; N = 500 1.27, 1.05, 0.94 at 23, 37, 49; N =
+//     600 1.36, 1.08, 1.05 at 21, 51, 79; N = 1000 1.76, 1.25, 1.02 at 14, 44, 74;
+//   FP32: N = 400 1.09, 1.00, 0.85 at 26, 36, 52; N = 600 1.19, 1.06, 0.96 at 21,
+//     35, 47; N = 800 1.32, 1.02, 1.07 at 17, 38, 47; N = 1000 1.56, 1.10 at 14, 44;
+//   six SCF iterations (one preparation): N = 300 1.11 to 1.09, N = 600 1.39 to
+//     1.21 in FP64 up to 60 %, 0.99 or more in FP32;
+//   compressed (tiles unpacked each time): 1.3 or more everywhere.
+bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs, int prec, bool once);
 bool xs_sparse(int N, int n_aux, int64_t n_pairs);   // the first two conditions
 int64_t xs_most_pairs(int N, int n_aux);             // the most pairs that meet them
 int xs_ldp(int n_aux);

@@ -498,9 +498,12 @@ bool xs_sparse(int N, int n_aux, int64_t n_pairs) {
            (double)(2 * n_pairs - N) <= 0.6 * (double)N * N;
 }
 
-bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs, int prec) {
-    return (prec == RI_FP64 || prec == RI_FP32) && xs_sparse(N, n_aux, n_pairs) &&
-           xt_rows(n_aux, n_occ) * xt_ld(N) * (prec == RI_FP64 ? 8 : 4) > (int64_t)RI_NOALLOC_SCRATCH_BYTES;
+bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs, int prec, bool once) {
+    if ((prec != RI_FP64 && prec != RI_FP32) || !xs_sparse(N, n_aux, n_pairs)) return false;
+    const int64_t xt = xt_rows(n_aux, n_occ) * xt_ld(N) * (prec == RI_FP64 ? 8 : 4);
+    const double most = prec == RI_FP64 ? 0.42 : 0.34;
+    return xt > (int64_t)RI_NOALLOC_SCRATCH_BYTES &&
+           (!once || xt > ((int64_t)512 << 20) || (double)(2 * n_pairs - N) <= most * (double)N * N);
 }
 
 int64_t xs_most_pairs(int N, int n_aux) {

@@ -100,3 +100,21 @@ def test_batch_longer_lists_cover_shorter(prec):
                 ctypes.c_void_p(a)]
         assert P.lib().ri_energy_batched(*args, nb - 1, None) == WORKSPACE
         assert P.lib().ri_energy_batched(*args, need[-1], None) == HIP
+
+
+@pytest.mark.parametrize("prec", [P.FP64, P.FP32])
+def test_single_builds_of_dense_lists_stay_on_tiles(prec):
+    # the copy of B_c for the partner lists is in the size where that form runs: one build with half of the pairs
+    # significant is faster on resident tiles (and in FP64 the compressed form gives the same bits), the SCF over the lists
+    W, size = Bd.workspace_bytes, 8 if prec == P.FP64 else 4
+    for N in (400, 450, 500):
+        na, no, half, few = 3 * N, N // 10, N * N // 4, N * N // 8
+        copy = na * half * size
+        jparts = 17 * 8 * (half + 1)
+        full = N * (N + 1) // 2
+        for op in (Bd.OP_FOCK, Bd.OP_GRADIENT):
+            assert W(op, N, na, no, half, prec) <= W(op, N, na, no, full, prec)
+            assert W(op, N, na, no, few, prec) > W(op, N, na, no, full, prec) - 17 * 8 * full + na * few * size
+        comp = W(Bd.OP_FOCK, N, na, no, half, prec | P.COMPRESSED) - W(Bd.OP_FOCK, N, na, no, half, prec)
+        assert comp < copy if prec == P.FP64 else comp > copy
+        assert W(Bd.OP_ENERGY, N, na, no, half, prec) > W(Bd.OP_ENERGY, N, na, no, full, prec) - (256 << 20) - 17 * 8 * full + copy - jparts
