@@ -333,7 +333,7 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec, const doubl
  *   B, prec, Bc, pairs, Linv as returned by ri_metric_factor (B may be NULL
  *            with prec | RI_COMPRESSED).  With RI_FP64 or RI_FP32 the
  *            half-transform X^P = B^P C for B_ij is in that precision, and
- *            reads B or Bc as ri_fock_jk does.
+ *            reads B or Bc as ri_fock_jk does (Bc up to 60 % of the pairs).
  *            With RI_BF16X3 or RI_BF16X6, B is not read (it may be NULL):
  *            B_ij, Xi and every sum are formed in FP64 from Bc, unpacked
  *            RI_COMPRESSED_SLAB auxiliaries at a time as for RI_COMPRESSED,

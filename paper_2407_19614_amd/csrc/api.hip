@@ -165,9 +165,9 @@ hipError_t x_any(const void* B, int prec, int N, int n_aux, int n_occ, const dou
 
 struct FockWS { void* Xt; double* part; double* dpair; double* jpart; double* gamma; double* Cp; int ks, js; SlabWS sw; ri::XSparse xs; };
 // wide: FP32-stored B in the FP64 layout (FP32 iterations and an FP64 build at the end)
-// One build (as against an SCF's) over the lists pays up to a lower fill where it
-// could read resident tiles (ri::xs_wanted).  The compressed form would gain in any
-// case; in FP64, where the two forms sum in different orders, it follows the
+// One Fock build (as against an SCF's) over the lists pays up to a lower fill where
+// it could read resident tiles (ri::xs_wanted).  The compressed form would gain in
+// any case; in FP64, where the two forms sum in different orders, it follows the
 // resident form all the same, whose results it promises.
 bool lists_once(int prec, bool comp) { return !comp || prec == RI_FP64; }
 
@@ -302,7 +302,7 @@ struct GradWS { double *D, *W, *T1, *dpair, *gamma, *c, *Bij, *Xi, *Zx, *part, *
 GradWS carve_grad(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t n_pairs, int n_centres, int prec,
                   bool comp = false) {
     GradWS w;
-    lists = lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, prec, lists_once(prec, comp));
+    lists = lists && ri::xs_wanted(N, n_aux, n_occ, n_pairs, prec, false);
     if (lists) w.xs = carve_sparse(a, N, n_aux, n_pairs, prec == RI_FP32, false);
     w.sw = carve_slab(a, N, n_aux, prec, comp && (!lists || a.dry));
     const int Npad = ri::xt_ld(N);

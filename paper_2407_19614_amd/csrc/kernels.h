@@ -68,7 +68,7 @@ struct XSparse {
 // tiles cost no more than the gathers), the copy is at most 64 GiB, and X^T is
 // over 64 MiB (builds that fit the static scratch of ri_fock_jk_noalloc keep
 // the dense form and its workspace, which need no partner lists or copy).  once:
-// the lists and the copy, prepared in the call, serve one build that could read
+// the lists and the copy, prepared in the call, serve one Fock build that could read
 // resident tiles; up to 512 MiB of X^T that pays up to 42 % (FP32: 34 %) only.
 // Measured, time on tiles over time on lists with their preparation:
 //   one Fock build, FP64: N = 300 1.11, 1.02, 0.86 at 29, 39, 50 % fill; N = 400
@@ -78,6 +78,8 @@ struct XSparse {
 //     35, 47; N = 800 1.32, 1.02, 1.07 at 17, 38, 47; N = 1000 1.56, 1.10 at 14, 44;
 //   six SCF iterations (one preparation): N = 300 1.11 to 1.09, N = 600 1.39 to
 //     1.21 in FP64 up to 60 %, 0.99 or more in FP32;
+//   the gradient, FP64: N = 300 0.99, 0.93 at 29, 50 %; N = 400 1.05, 1.01, 0.97 at
+//     26, 47, 59; N = 600 1.20, 1.01 at 21, 51; FP32 0.93 (N = 370) to 1.18;
 //   compressed (tiles unpacked each time): 1.3 or more everywhere.
 bool xs_wanted(int N, int n_aux, int n_occ, int64_t n_pairs, int prec, bool once);
 bool xs_sparse(int N, int n_aux, int64_t n_pairs);   // the first two conditions
