@@ -897,6 +897,12 @@ int32_t ri_energy(const ri_system* sys, const void* B, int32_t prec_arg, const d
     return converged ? RI_OK : RI_E_NO_CONV;
 }
 
+// n_aux^2 n_occ^2 from which half of the ij columns save the gradient more than the
+// two launches that pack and unpack them take: N = 90, 33 occupied (79 M) 219 us
+// without, 232 with; N = 130 (26 M) 230, 233; N = 240 (299 M) 480, 482; N = 270
+// (478 M) 571, 564; N = 350 (1351 M) 954, 907.
+static constexpr int64_t PACK_IJ_MIN = 400000000;
+
 int32_t ri_gradient(const ri_system* sys, const int32_t* pairs, int64_t n_pairs, const void* B, int32_t prec_arg,
                     const double* Bc, const double* Linv, const double* C, const double* F, double* grad, void* ws,
                     size_t ws_bytes, hipStream_t st) {
@@ -925,10 +931,12 @@ int32_t ri_gradient(const ri_system* sys, const int32_t* pairs, int64_t n_pairs,
     const int GB = ri::GRAD_BLOCKS;
     const int64_t rowlen = 3 * (int64_t)nc;
     // On the side stream, beside X and the exchange products (they share no
-    // buffers): gamma = L^{-1} d, c = L^{-T} gamma = A^{-1} d and the
-    // one-electron term.  Without a side stream they run here in turn.
+    // buffers): the pairs' part of the three-centre term, gamma = L^{-1} d, c =
+    // L^{-T} gamma = A^{-1} d and the one-electron and nuclear terms.  Without a
+    // side stream they run here in turn.
     Fork fk;
     hipStream_t ss = fk.open(st) ? fk.side : st;
+    HIPC(ri::grad_pairs(sys, pairs, n_pairs, w.D, w.rows, w.pscr, w.part + 3 * GB * rowlen, ss));
     HIPC(ri::gamma_only(Bc, pairs, n_pairs, na, no, C, w.dpair, w.gamma, ss));
     HIPC(ri::gemm_f64(true, false, na, 1, na, 1.0, Linv, na, 0, w.gamma, 1, 0, 0.0, w.c, 1, 0, 1, 2, 0, ss));
     HIPC(ri::grad_one_electron(sys, w.D, w.W, w.part, ss));
@@ -943,23 +951,29 @@ int32_t ri_gradient(const ri_system* sys, const int32_t* pairs, int64_t n_pairs,
     // one GEMM over all (P, i) rows: the rows of X^T are stacked P-major, as B_ij's
     HIPC(ri::gemm_f64(false, false, na * no, no, N, 1.0, (const double*)w.Xt, Npad, 0, C, no, 0, 0.0, w.Bij, no, 0,
                       1, 0, 0, st, 128));
-    // B_ij (in FP32 the mean of its halves) and Xi are symmetric in ij: half the
-    // columns (i >= j, sqrt 2 off the diagonal) carry Xi = L^{-T} B_ij and Zx = -2 sum_ij Xi_ij Xi_ij^T.  Packed B_ij goes
-    // where X was, packed Xi over B_ij, and Xi is unpacked for the products with C.
-    const int64_t oh = (int64_t)no * (no + 1) / 2;
-    double* Bp = (double*)w.Xt;
-    HIPC(ri::pack_ij(w.Bij, no, na, prec == RI_FP32, Bp, st));
-    HIPC(ri::gemm_f64(true, false, na, (int)oh, na, 1.0, Linv, na, 0, Bp, oh, 0, 0.0, w.Bij, oh, 0, 1, 2, 0, st));
-    // lower tiles; Z = c c^T + Zx inside the contraction
-    HIPC(ri::grad_metric_z(w.Bij, na, oh, w.WY, (int64_t)ri::grad_slab(N, na) * N * N, w.Zx, st));
-    HIPC(ri::unpack_ij(w.Bij, no, na, w.Xi, st));
+    // lower tiles of Zx; Z = c c^T + Zx inside the contraction
+    if ((int64_t)na * na * o2 < PACK_IJ_MIN) {
+        // Xi = L^{-T} B_ij and Zx = -2 sum_ij Xi_ij Xi_ij^T over all ij
+        if (prec == RI_FP32) HIPC(ri::mean_ij(w.Bij, no, na, st));
+        HIPC(ri::gemm_f64(true, false, na, (int)o2, na, 1.0, Linv, na, 0, w.Bij, o2, 0, 0.0, w.Xi, o2, 0, 1, 2, 0, st));
+        HIPC(ri::grad_metric_z(w.Xi, na, o2, w.WY, (int64_t)ri::grad_slab(N, na) * N * N, w.Zx, st));
+    } else {
+        // B_ij (in FP32 the mean of its halves) and Xi are symmetric in ij: half the
+        // columns (i >= j, sqrt 2 off the diagonal) carry the same sums.  Packed B_ij goes
+        // where X was, packed Xi over B_ij, and Xi is unpacked for the products with C.
+        const int64_t oh = (int64_t)no * (no + 1) / 2;
+        double* Bp = (double*)w.Xt;
+        HIPC(ri::pack_ij(w.Bij, no, na, prec == RI_FP32, Bp, st));
+        HIPC(ri::gemm_f64(true, false, na, (int)oh, na, 1.0, Linv, na, 0, Bp, oh, 0, 0.0, w.Bij, oh, 0, 1, 2, 0, st));
+        HIPC(ri::grad_metric_z(w.Bij, na, oh, w.WY, (int64_t)ri::grad_slab(N, na) * N * N, w.Zx, st));
+        HIPC(ri::unpack_ij(w.Bij, no, na, w.Xi, st));
+    }
     // U^P = C Xi^P  (stored over the X buffer)
     double* U = (double*)w.Xt;
     HIPC(ri::u_products(C, w.Xi, N, no, na, U, st));
-    HIPC(fk.close());   // c and the one-electron rows are ready on st from here
+    HIPC(fk.close());   // the side stream's results are ready on st from here
     HIPC(ri::grad_metric(sys, w.Zx, w.c, w.part + GB * rowlen, st));
-    HIPC(ri::grad_three_centre(sys, pairs, n_pairs, U, C, no, w.D, w.c, w.WY, w.rows, w.pscr, w.part + 2 * GB * rowlen, st));
-    HIPC(ri::grad_nuclear(sys, w.part + 3 * GB * rowlen, st));
+    HIPC(ri::grad_three_centre(sys, n_pairs, U, C, no, w.c, w.WY, w.rows, w.pscr, w.part + 2 * GB * rowlen, st));
     HIPC(ri::grad_reduce(w.part, 3 * GB + 1, nc, grad, st));
     return RI_OK;
 }

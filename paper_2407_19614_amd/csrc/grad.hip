@@ -271,21 +271,15 @@ __global__ __launch_bounds__(256) void g2c_kernel(const double* xyz, const int32
     flush(g, 3 * nc, part);
 }
 
-// Constants of each pair for the derivative integrals, as PC_N arrays over the
-// pairs, and its two centres; the first two blocks make the table T.
+// Constants of pair q for the derivative integrals, as PC_N arrays over the pairs,
+// and its two centres.
 constexpr int PC_P = 0, PC_K = 1, PC_X = 2, PC_M = 5, PC_A = 6, PC_B = 7, PC_D = 8, PC_W = 11, PC_N = 12;
 
-__global__ __launch_bounds__(256) void pair_consts_kernel(const double* __restrict__ xyz,
-                                                          const int32_t* __restrict__ fc,
-                                                          const double* __restrict__ fe,
-                                                          const int32_t* __restrict__ pairs, int64_t n_pairs,
-                                                          const double* __restrict__ D, int N,
-                                                          double* __restrict__ pc, int2* __restrict__ ctr,
-                                                          double* __restrict__ T) {
-    const int64_t q = (blockIdx.x - 2ll) * 256 + threadIdx.x;
-    if (q < 0 && q + 512 < BT_N) boys_row((int)(q + 512), T + (q + 512) * BT_M);
-    if (q < 0 || q >= n_pairs) return;
-    const int mu = pairs[2 * q], nu = pairs[2 * q + 1], ca = fc[mu], cb = fc[nu];
+__device__ __forceinline__ void pair_consts(int64_t q, int mu, int nu, const double* __restrict__ xyz,
+                                            const int32_t* __restrict__ fc, const double* __restrict__ fe,
+                                            int64_t n_pairs, const double* __restrict__ D, int N,
+                                            double* __restrict__ pc, int2* __restrict__ ctr) {
+    const int ca = fc[mu], cb = fc[nu];
     const double a = fe[mu], b = fe[nu], p = a + b, ip = 1.0 / p, m = a * b * ip;
     const double* A = xyz + 3 * ca;
     const double* B = xyz + 3 * cb;
@@ -306,9 +300,23 @@ __global__ __launch_bounds__(256) void pair_consts_kernel(const double* __restri
     ctr[q] = make_int2(mu == nu ? ~ca : ca, cb);   // the diagonal's weight is 1, the others' 2
 }
 
+// The first two blocks make the table T, the others a pair per thread.
+__global__ __launch_bounds__(256) void pair_consts_kernel(const double* __restrict__ xyz,
+                                                          const int32_t* __restrict__ fc,
+                                                          const double* __restrict__ fe,
+                                                          const int32_t* __restrict__ pairs, int64_t n_pairs,
+                                                          const double* __restrict__ D, int N,
+                                                          double* __restrict__ pc, int2* __restrict__ ctr,
+                                                          double* __restrict__ T) {
+    const int64_t q = (blockIdx.x - 2ll) * 256 + threadIdx.x;
+    if (q < 0 && q + 512 < BT_N) boys_row((int)(q + 512), T + (q + 512) * BT_M);
+    if (q < 0 || q >= n_pairs) return;
+    pair_consts(q, pairs[2 * q], pairs[2 * q + 1], xyz, fc, fe, n_pairs, D, N, pc, ctr);
+}
+
 // sum_P sum_pairs w Y^P_mu_nu (mu nu|P)',  Y = c_P D_mu_nu - 2 (U^P C^T)_mu_nu, for
 // auxiliary indices P0 .. P0 + np - 1 (WY[P - P0][q] = (U^P C^T)_mu_nu of pair q),
-// added to the block's partial row.  Work items are (bpi blocks of 256 pairs,
+// into the block's partial row, or (P0 > 0) added to it.  Work items are (bpi blocks of 256 pairs,
 // chunk of G3_PC auxiliaries), a pair per thread, the chunk's auxiliaries in
 // turn (their constants staged in LDS).  With e = P - R_aux and g = 2 w c0 F1, an
 // entry adds I y to s and g y e to G: the pair's centres take -2 m s (A - B) -
@@ -399,7 +407,8 @@ __global__ __launch_bounds__(256, 2) void g3c_kernel(const double* __restrict__ 
             if (lane == 0) lds_add3(g, sc[k], sx, sy, sz);
         }
     }
-    flush_add(g, 3 * nc, part);
+    if (P0 == 0) flush(g, 3 * nc, part);
+    else flush_add(g, 3 * nc, part);
 }
 
 // The pairs by rows: sp, a copy of the pairs, and rows, the first of each mu in it
@@ -426,20 +435,16 @@ __global__ __launch_bounds__(256) void pair_rows_kernel(const Pair* __restrict__
     rows[t] = (int32_t)lo;
 }
 
-// Pairs in another order, by rows: a workgroup per row mu (mu = N: the end) counts
-// the pairs of the rows before it and its own, a quarter of the list per wave, then
-// places its own in the order that they have.  Bound by the reads of the list
-// through L2, N times.  Measured, gradient of shuffled pairs: N = 200 0.41 ms, N =
-// 400 1.24, N = 1000 13.0 (on one workgroup, a row a thread: 1.23, 3.5, 21.1;
-// sorted: 0.40, 1.21, 12.8).
-__global__ __launch_bounds__(256) void pair_sort_kernel(const Pair* __restrict__ pairs, int64_t n_pairs, int N,
-                                                        int32_t* rows, Pair* __restrict__ sp) {
-    if (rows[N + 1] == 0) return;
+// Row mu of the pairs in any order, by one workgroup: counts the pairs of the rows
+// before it (rows[mu]) and its own, a quarter of the list per wave, then places its
+// own in the order that they have.  Returns their first place and count.
+__device__ __forceinline__ int2 sort_row(const Pair* __restrict__ pairs, int64_t n_pairs, int mu, int32_t* rows,
+                                         Pair* __restrict__ sp) {
     constexpr int D = 8;                           // steps of 64 pairs in flight
     __shared__ int32_t before[4], own[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, mu = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t per = (n_pairs + 255) / 256 * 64, a = wave * per, z = min(n_pairs, a + per);
-    int32_t less = 0, mine = 0, at = 0;
+    int32_t less = 0, mine = 0, at = 0, first = 0, all = 0;
     for (int pass = 0; pass < 2; ++pass) {         // count, then place
         for (int64_t q0 = a; q0 < z; q0 += 64 * D) {
             Pair v[D];
@@ -464,11 +469,69 @@ __global__ __launch_bounds__(256) void pair_sort_kernel(const Pair* __restrict__
                 own[wave] = mine;
             }
             __syncthreads();
-            const int32_t first = before[0] + before[1] + before[2] + before[3];
+            first = before[0] + before[1] + before[2] + before[3];
+            all = own[0] + own[1] + own[2] + own[3];
             if (threadIdx.x == 0) rows[mu] = first;
             at = first;
             for (int w = 0; w < wave; ++w) at += own[w];
         }
+    }
+    return make_int2(first, all);
+}
+
+// Pairs that pair_rows_kernel found in another order, a workgroup per row (the last:
+// the end).  Bound by the reads of the list through L2, N times.  Measured, gradient
+// of shuffled pairs: N = 400 1.24 ms, N = 1000 13.0 (on one workgroup, a row a thread:
+// 3.5, 21.1; sorted: 1.21, 12.8).
+__global__ __launch_bounds__(256) void pair_sort_kernel(const Pair* __restrict__ pairs, int64_t n_pairs, int N,
+                                                        int32_t* rows, Pair* __restrict__ sp) {
+    if (rows[N + 1] != 0) sort_row(pairs, n_pairs, blockIdx.x, rows, sp);
+}
+
+// The nuclear repulsion's row of partial sums, by one workgroup.
+__device__ void nuclear_row(const double* xyz, const double* Z, int nc, double* part) {
+    for (int A = threadIdx.x; A < nc; A += 256) {
+        double gx = 0, gy = 0, gz = 0;
+        for (int B = 0; B < nc; ++B) {
+            if (B == A || Z[A] * Z[B] == 0.0) continue;
+            double dx = xyz[3 * A] - xyz[3 * B], dy = xyz[3 * A + 1] - xyz[3 * B + 1], dz = xyz[3 * A + 2] - xyz[3 * B + 2];
+            double r = sqrt(dx * dx + dy * dy + dz * dz);
+            double f = -Z[A] * Z[B] / (r * r * r);
+            gx += f * dx; gy += f * dy; gz += f * dz;
+        }
+        part[3 * A] = gx; part[3 * A + 1] = gy; part[3 * A + 2] = gz;
+    }
+}
+
+__global__ __launch_bounds__(256) void gnuc_kernel(const double* xyz, const double* Z, int nc, double* part) {
+    nuclear_row(xyz, Z, nc, part);
+}
+
+// All of the above in one launch for short lists, in any order: the first two blocks
+// make the table T, the third the nuclear row, the others a row of pairs each.
+// Bound by the table's chain of double-double operations (15 us), beside the work
+// of the caller's stream.
+__global__ __launch_bounds__(256) void pair_setup_kernel(const Pair* __restrict__ pairs, int64_t n_pairs, int N,
+                                                         int32_t* rows, Pair* __restrict__ sp,
+                                                         const double* __restrict__ xyz, const double* __restrict__ Z,
+                                                         int nc, const int32_t* __restrict__ fc,
+                                                         const double* __restrict__ fe, const double* __restrict__ D,
+                                                         double* __restrict__ pc, int2* __restrict__ ctr,
+                                                         double* __restrict__ T, double* __restrict__ nuc) {
+    if (blockIdx.x < 2) {
+        const int j = blockIdx.x * 256 + threadIdx.x;
+        if (j < BT_N) boys_row(j, T + j * BT_M);
+        return;
+    }
+    if (blockIdx.x == 2) {
+        nuclear_row(xyz, Z, nc, nuc);
+        return;
+    }
+    const int2 own = sort_row(pairs, n_pairs, blockIdx.x - 3, rows, sp);
+    __syncthreads();                               // the row's pairs are placed
+    for (int k = threadIdx.x; k < own.y; k += 256) {
+        const int q = own.x + k;
+        pair_consts(q, sp[q].x, sp[q].y, xyz, fc, fe, n_pairs, D, N, pc, ctr);
     }
 }
 
@@ -622,20 +685,6 @@ __global__ __launch_bounds__(256, 2) void u_kernel(const double* __restrict__ C,
     }
 }
 
-__global__ __launch_bounds__(256) void gnuc_kernel(const double* xyz, const double* Z, int nc, double* part) {
-    for (int A = threadIdx.x; A < nc; A += 256) {
-        double gx = 0, gy = 0, gz = 0;
-        for (int B = 0; B < nc; ++B) {
-            if (B == A || Z[A] * Z[B] == 0.0) continue;
-            double dx = xyz[3 * A] - xyz[3 * B], dy = xyz[3 * A + 1] - xyz[3 * B + 1], dz = xyz[3 * A + 2] - xyz[3 * B + 2];
-            double r = sqrt(dx * dx + dy * dy + dz * dz);
-            double f = -Z[A] * Z[B] / (r * r * r);
-            gx += f * dx; gy += f * dy; gz += f * dz;
-        }
-        part[3 * A] = gx; part[3 * A + 1] = gy; part[3 * A + 2] = gz;
-    }
-}
-
 // grad[i] = sum over rows of part[row][i]: one block per component, the rows
 // strided over the threads, then a fixed-order tree (deterministic).
 __global__ __launch_bounds__(256) void greduce_kernel(const double* part, int rows, int nc3, double* grad) {
@@ -683,6 +732,18 @@ __global__ __launch_bounds__(256) void unpack_ij_kernel(const double* __restrict
     }
 }
 
+// The same mean in place, for blocks that are not packed.
+__global__ __launch_bounds__(256) void mean_ij_kernel(double* __restrict__ B, int o, int64_t n) {
+    const int64_t e = blockIdx.x * 256ll + threadIdx.x;
+    if (e >= n) return;
+    const int j = (int)(e % o), i = (int)(e / o % o);
+    if (j >= i) return;
+    double* t = B + e / o / o * o * o + (int64_t)j * o + i;
+    const double v = 0.5 * (B[e] + *t);
+    B[e] = v;
+    *t = v;
+}
+
 // out[r][c] = sum_z part[z][r][c] for c <= r, z in order.
 __global__ void sum_lower_kernel(const double* part, int S, int64_t stride, int n, double* out) {
     const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -722,6 +783,11 @@ hipError_t pack_ij(const double* B, int o, int np, bool mean, double* Bp, hipStr
     const unsigned blocks = (unsigned)np * (unsigned)o, threads = o > 64 ? 128 : 64;
     if (mean) pack_ij_kernel<true><<<blocks, threads, 0, st>>>(B, o, Bp);
     else pack_ij_kernel<false><<<blocks, threads, 0, st>>>(B, o, Bp);
+    return hipGetLastError();
+}
+hipError_t mean_ij(double* B, int o, int np, hipStream_t st) {
+    const int64_t n = (int64_t)np * o * o;
+    mean_ij_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(B, o, n);
     return hipGetLastError();
 }
 hipError_t unpack_ij(const double* Xp, int o, int np, double* Xi, hipStream_t st) {
@@ -783,29 +849,51 @@ hipError_t u_products(const double* C, const double* Xi, int N, int K, int np, d
     }
     return hipGetLastError();
 }
-hipError_t grad_three_centre(const ri_system* s, const int32_t* pairs, int64_t n_pairs, const double* U,
-                             const double* C, int n_occ, const double* D, const double* c, double* WY, int32_t* rows,
-                             double* pscratch, double* part, hipStream_t st) {
+// Pairs times functions up to which pair_setup_kernel, which reads the list 2 N
+// times, takes the place of five launches: the gradient of N = 130 in 230 us for
+// 240, N = 240 480 for 492, N = 350 903 for 909, N = 500 (14.5 M) 1947 for 1943.
+constexpr int64_t PAIR_SETUP_MAX = 1 << 23;
+// Where the parts of the three-centre term's scratch lie.
+struct PairScratch {
+    double* pc;      // [PC_N][n_pairs]
+    int2* ctr;       // [n_pairs]
+    Pair* sp;        // [n_pairs] pairs by rows
+    double* bt;      // table of the Boys function
+    PairScratch(double* p, int64_t n_pairs)
+        : pc(p), ctr((int2*)(p + PC_N * n_pairs)), sp((Pair*)(ctr + n_pairs)), bt((double*)(sp + n_pairs)) {}
+};
+hipError_t grad_pairs(const ri_system* s, const int32_t* pairs, int64_t n_pairs, const double* D, int32_t* rows,
+                      double* pscratch, double* nuclear, hipStream_t st) {
+    const int N = s->n_fn;
+    const PairScratch w(pscratch, n_pairs);
+    const Pair* given = (const Pair*)pairs;
+    if (n_pairs > 0 && N * n_pairs <= PAIR_SETUP_MAX) {
+        pair_setup_kernel<<<(unsigned)N + 4, 256, 0, st>>>(given, n_pairs, N, rows, w.sp, s->xyz, s->Z, s->n_centres,
+                                                           s->fn_centre, s->fn_exp, D, w.pc, w.ctr, w.bt, nuclear);
+        return hipGetLastError();
+    }
+    gnuc_kernel<<<1, 256, 0, st>>>(s->xyz, s->Z, s->n_centres, nuclear);
+    RI_TRY(hipGetLastError());
+    if (n_pairs == 0) return hipSuccess;
+    RI_TRY(fill_i32(rows + N + 1, 0, 1, st));
+    pair_rows_kernel<<<(unsigned)((std::max<int64_t>(n_pairs, N + 1) + 255) / 256), 256, 0, st>>>(given, n_pairs, N, rows,
+                                                                                                  w.sp);
+    pair_sort_kernel<<<(unsigned)N + 1, 256, 0, st>>>(given, n_pairs, N, rows, w.sp);
+    RI_TRY(hipGetLastError());
+    pair_consts_kernel<<<(unsigned)((n_pairs + 255) / 256 + 2), 256, 0, st>>>(s->xyz, s->fn_centre, s->fn_exp,
+                                                                              (const int32_t*)w.sp, n_pairs, D, N, w.pc,
+                                                                              w.ctr, w.bt);
+    return hipGetLastError();
+}
+hipError_t grad_three_centre(const ri_system* s, int64_t n_pairs, const double* U, const double* C, int n_occ,
+                             const double* c, double* WY, const int32_t* rows, double* pscratch, double* part,
+                             hipStream_t st) {
     if (s->n_centres > MAXC) return hipErrorInvalidValue;
     const int N = s->n_fn, na = s->n_aux;
     const size_t lds = 3 * s->n_centres * sizeof(double);
-    RI_TRY(fill(part, 0.0, (int64_t)GRAD_BLOCKS * 3 * s->n_centres, st));
-    if (n_pairs == 0) return hipSuccess;
-    double* pc = pscratch;
-    int2* ctr = (int2*)(pc + PC_N * n_pairs);
-    Pair* sp = (Pair*)(ctr + n_pairs);
-    double* bt = (double*)(sp + n_pairs);
-    // nothing below needs the given order, so rows of it are made where it has none
-    const Pair* given = (const Pair*)pairs;
-    RI_TRY(fill_i32(rows + N + 1, 0, 1, st));
-    pair_rows_kernel<<<(unsigned)((std::max<int64_t>(n_pairs, N + 1) + 255) / 256), 256, 0, st>>>(given, n_pairs, N, rows,
-                                                                                                  sp);
-    pair_sort_kernel<<<(unsigned)N + 1, 256, 0, st>>>(given, n_pairs, N, rows, sp);
-    RI_TRY(hipGetLastError());
-    pairs = (const int32_t*)sp;
-    pair_consts_kernel<<<(unsigned)((n_pairs + 255) / 256 + 2), 256, 0, st>>>(s->xyz, s->fn_centre, s->fn_exp, pairs,
-                                                                              n_pairs, D, N, pc, ctr, bt);
-    RI_TRY(hipGetLastError());
+    if (n_pairs == 0) return fill(part, 0.0, (int64_t)GRAD_BLOCKS * 3 * s->n_centres, st);
+    const PairScratch w(pscratch, n_pairs);
+    const int32_t* pairs = (const int32_t*)w.sp;
     // auxiliaries at a time that WY holds (nearly twice grad_slab where every pair is listed once)
     const int ns = (int)std::min<int64_t>(na, grad_wy_elems(N, na, n_pairs) / n_pairs);
     for (int P0 = 0; P0 < na; P0 += ns) {
@@ -826,8 +914,8 @@ hipError_t grad_three_centre(const ri_system* s, const int32_t* pairs, int64_t n
         // blocks of pairs per item: as many as leave every workgroup two items
         const int64_t one = (n_pairs + 255) / 256 * ((np + G3_PC - 1) / G3_PC);
         const int bpi = (int)std::max<int64_t>(1, std::min<int64_t>(8, one / (2 * GRAD_BLOCKS)));
-        g3c_kernel<<<GRAD_BLOCKS, 256, lds, st>>>(s->xyz, s->aux_centre, s->aux_exp, P0, np, s->n_centres, n_pairs, bpi, pc,
-                                                  ctr, WY, c, bt, part);
+        g3c_kernel<<<GRAD_BLOCKS, 256, lds, st>>>(s->xyz, s->aux_centre, s->aux_exp, P0, np, s->n_centres, n_pairs, bpi,
+                                                  w.pc, w.ctr, WY, c, w.bt, part);
         RI_TRY(hipGetLastError());
     }
     return hipSuccess;
@@ -836,10 +924,6 @@ int64_t grad_wy_elems(int N, int n_aux, int64_t n_pairs) {
     return std::max((int64_t)grad_slab(N, n_aux) * N * N, n_pairs);
 }
 int64_t grad_pair_elems(int64_t n_pairs) { return (PC_N + 2) * n_pairs + BT_N * BT_M; }
-hipError_t grad_nuclear(const ri_system* s, double* part, hipStream_t st) {
-    gnuc_kernel<<<1, 256, 0, st>>>(s->xyz, s->Z, s->n_centres, part);
-    return hipGetLastError();
-}
 hipError_t grad_reduce(const double* part, int rows, int n_centres, double* grad, hipStream_t st) {
     greduce_kernel<<<3 * n_centres, 256, 0, st>>>(part, rows, 3 * n_centres, grad);
     return hipGetLastError();

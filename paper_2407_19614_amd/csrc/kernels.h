@@ -199,26 +199,31 @@ hipError_t grad_metric(const ri_system* s, const double* Z, const double* c, dou
 // [np][o][o] blocks, symmetric up to rounding: entries j <= i (mean: of both halves) times sqrt 2 off the
 // diagonal ([np][o (o + 1) / 2]), and back
 hipError_t pack_ij(const double* B, int o, int np, bool mean, double* Bp, hipStream_t st);
+hipError_t mean_ij(double* B, int o, int np, hipStream_t st);   // B = the mean of both halves
 hipError_t unpack_ij(const double* Xp, int o, int np, double* Xi, hipStream_t st);
 // Zx = -2 Xi Xi^T (lower 128-tiles) for Xi [n_aux][K], split over K through
 // tmp (tmp_elems doubles of scratch).
 hipError_t grad_metric_z(const double* Xi, int n_aux, int64_t K, double* tmp, int64_t tmp_elems, double* Zx,
                          hipStream_t st);
-// Three-centre term, U^P = C Xi^P, [n_aux][N][n_occ].  (U^P C^T)_mu_nu is formed
+// What the three-centre term needs of the pairs, and the nuclear repulsion's row of partial sums: the pairs by
+// rows, their constants and the table of the Boys function, into rows (N + 2 ints) and pscratch
+// (grad_pair_elems doubles).  The pairs may be in any order.
+hipError_t grad_pairs(const ri_system* s, const int32_t* pairs, int64_t n_pairs, const double* D, int32_t* rows,
+                      double* pscratch, double* nuclear, hipStream_t st);
+// Three-centre term after grad_pairs, U^P = C Xi^P, [n_aux][N][n_occ].  (U^P C^T)_mu_nu is formed
 // on MFMA at the significant pairs, for as many auxiliary indices at a time as
 // WY holds (workspace of grad_wy_elems doubles: grad_slab * N * N, and at least one
 // auxiliary of a list that names pairs repeatedly), and the derivative kernel
-// reads it there.  The pairs may be in any order.  rows: N + 2 ints of scratch; pscratch: grad_pair_elems doubles.
+// reads it there.
 int grad_slab(int N, int n_aux);
 int64_t grad_wy_elems(int N, int n_aux, int64_t n_pairs);
 // U[p] = C Xi^p for p < np: C [N][K], Xi [np][K][K] with symmetric blocks,
 // U [np][N][K].
 hipError_t u_products(const double* C, const double* Xi, int N, int K, int np, double* U, hipStream_t st);
-hipError_t grad_three_centre(const ri_system* s, const int32_t* pairs, int64_t n_pairs, const double* U,
-                             const double* C, int n_occ, const double* D, const double* c, double* WY, int32_t* rows,
-                             double* pscratch, double* part, hipStream_t st);
+hipError_t grad_three_centre(const ri_system* s, int64_t n_pairs, const double* U, const double* C, int n_occ,
+                             const double* c, double* WY, const int32_t* rows, double* pscratch, double* part,
+                             hipStream_t st);
 int64_t grad_pair_elems(int64_t n_pairs);
-hipError_t grad_nuclear(const ri_system* s, double* part, hipStream_t st);
 hipError_t grad_reduce(const double* part, int rows, int n_centres, double* grad, hipStream_t st);
 hipError_t gamma_only(const double* Bc, const int32_t* pairs, int64_t n_pairs, int n_aux, int n_occ,
                       const double* C, double* dpair, double* gamma, hipStream_t st);
