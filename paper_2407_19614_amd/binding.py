@@ -207,6 +207,7 @@ class RIProblem:
                               self.xyz.data_ptr(), self.Z.data_ptr(), self.fn_centre.data_ptr(),
                               self.fn_exp.data_ptr(), self.aux_centre.data_ptr(), self.aux_exp.data_ptr())
         self._ws = None
+        self._ws_plain = {}           # compressed: whether the size without the flag is enough, by (operation, precision, pairs)
         self.pairs = self.T = self.L = self.Linv = self.B = None
         self.n_pairs = None
 
@@ -237,11 +238,13 @@ class RIProblem:
         """call(workspace pointer, bytes) -> status, with the workspace of operation `op`.  A compressed call whose X runs
         over the significant pairs needs only the size without the flag (no slab of tiles), so that is offered first; a
         workspace that is too small is refused before anything is launched."""
-        if self.compressed:
+        key = (op, prec, self.n_pairs)
+        if self.compressed and self._ws_plain.get(key, True):
             nb = workspace_bytes(op, self.N, self.n_aux, self.n_occ, max(self.n_pairs or 0, 0), prec)
             code = call(_ptr(self.workspace(nb)), nb)
             if code != 4:
                 return code
+            self._ws_plain[key] = False
         ws, nb = self._ws_for(op, prec)
         return call(_ptr(ws), nb)
 
