@@ -16,11 +16,18 @@
 
 namespace {
 
-// Bf[p][mu][nu] = B_c[p][pair(mu, nu)] or 0, rows of ld
+// Bf[p][mu][nu] = B_c[p][pair(mu, nu)] or 0, rows of ld; and `tail` rows of zeros
+// after the last one of Bf and of Y, which k_product reads
 __global__ void unpack_full_kernel(const double* __restrict__ Bc, int64_t n_pairs, const int32_t* __restrict__ map,
-                                   int N, int ld, double* __restrict__ Bf) {
+                                   int N, int ld, int tail, double* __restrict__ Bf, double* __restrict__ Y) {
     const int nu = blockIdx.x * blockDim.x + threadIdx.x, mu = blockIdx.y, p = blockIdx.z;
     if (nu >= ld) return;
+    if (p == 0)
+        for (int64_t t = mu; t < tail; t += N) {
+            const int64_t e = ((int64_t)gridDim.z * N + t) * ld + nu;
+            Bf[e] = 0.0;
+            Y[e] = 0.0;
+        }
     const int32_t q = nu < N ? map[(int64_t)mu * N + nu] : -1;
     Bf[((int64_t)p * N + mu) * ld + nu] = q >= 0 ? Bc[(int64_t)p * n_pairs + q] : 0.0;
 }
@@ -64,11 +71,13 @@ hipError_t k_density(const double* Bc, const int32_t* pairs, int64_t n_pairs, in
         const double* b = Bc + (int64_t)P0 * n_pairs;
         RI_TRY(xs_rows(w.xs, b, n_pairs, s, st));
         RI_TRY(xs_run(w.xs, N, s, N, w.Dp, w.Y, st));
-        unpack_full_kernel<<<dim3((ld + 255) / 256, N, s), 256, 0, st>>>(b, n_pairs, w.xs.map, N, ld, w.Bf);
+        const int64_t rows_s = (int64_t)s * N;
+        unpack_full_kernel<<<dim3((ld + 255) / 256, N, s), 256, 0, st>>>(b, n_pairs, w.xs.map, N, ld,
+                                                                         (int)(xt_rows(s, N) - rows_s), w.Bf, w.Y);
         RI_TRY(hipGetLastError());
         // every slab has the same number of splits, so that each adds to what the first wrote
         int u = 0;
-        RI_TRY(k_product(w.Bf, w.Y, (int64_t)s * N, N, w.part, P0 == 0 ? w.ks : used, P0 > 0, &u, st));
+        RI_TRY(k_product(w.Bf, w.Y, rows_s, N, w.part, P0 == 0 ? w.ks : used, P0 > 0, &u, st));
         used = std::max(used, u);
     }
     return kreduce(w.part, used, N, 0.5, K, st);

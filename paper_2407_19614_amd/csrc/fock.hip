@@ -972,14 +972,12 @@ hipError_t kreduce(const double* part, int n_split, int N, double scale, double*
     return hipGetLastError();
 }
 
-hipError_t k_product(double* X, double* Y, int64_t rows, int N, double* part, int n_split, bool add, int* used,
+hipError_t k_product(const double* X, const double* Y, int64_t rows, int N, double* part, int n_split, bool add, int* used,
                      hipStream_t st) {
     const int Npad = xt_ld(N), t128 = Npad / 128;
     const int64_t rows_pad = (rows + 15) / 16 * 16;
     const int64_t chunk = ((rows_pad + n_split - 1) / n_split + 15) / 16 * 16;
     *used = (int)((rows_pad + chunk - 1) / chunk);
-    RI_TRY(fill(X + rows * Npad, 0.0, (rows_pad + 16 - rows) * Npad, st));
-    RI_TRY(fill(Y + rows * Npad, 0.0, (rows_pad + 16 - rows) * Npad, st));
     const unsigned blocks = (unsigned)(t128 * (t128 + 1) / 2 * *used);
     if (add) product_lds_kernel<true><<<blocks, 256, 0, st>>>(X, Y, N, Npad, rows_pad, chunk, t128, part);
     else product_lds_kernel<false><<<blocks, 256, 0, st>>>(X, Y, N, Npad, rows_pad, chunk, t128, part);

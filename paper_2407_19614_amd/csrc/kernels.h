@@ -112,8 +112,9 @@ int k_split_count(int N, int n_aux, int n_occ);
 // K[m][n] = K[n][m] = scale * sum over splits of part, m >= n
 hipError_t kreduce(const double* part, int n_split, int N, double scale, double* K, hipStream_t st);
 // Lower 128-tiles of sum_r X[r][m] Y[r][n] (a product known to be symmetric) over `rows` rows of
-// stride xt_ld(N), in n_split parts (*used of them written, or added to); X and Y hold 32 rows more.
-hipError_t k_product(double* X, double* Y, int64_t rows, int N, double* part, int n_split, bool add, int* used,
+// stride xt_ld(N), in n_split parts (*used of them written, or added to); X and Y hold zero rows after them, up
+// to the next multiple of 16 and 16 more.
+hipError_t k_product(const double* X, const double* Y, int64_t rows, int N, double* part, int n_split, bool add, int* used,
                      hipStream_t st);
 int64_t xt_rows(int n_aux, int n_occ);
 int xt_ld(int N);
