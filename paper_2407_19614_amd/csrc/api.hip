@@ -235,7 +235,7 @@ hipError_t jk_density(const double* Bc, const int32_t* pairs, int64_t n_pairs, i
 struct EnergyWS {
     double *S, *H, *Ls, *LinvS, *J, *K, *F, *D, *T1, *T2, *Fx, *X, *X2;
     double *dF[8], *dE[8];
-    double *Bfull, *coef, *Y, *Cp, *R, *Mo, *LinvM, *dinvS, *dinvM, *scal, *red, *tpart;
+    double *Bfull, *coef, *Y, *Cp, *Mo, *LinvM, *dinvS, *dinvM, *scal, *red, *tpart;
     int *bad, *tst;
     FockWS fock;
     FockWS fin;   // final FP64 exchange build of the split-BF16 forms: FP64 Xt and slabs of B_c
@@ -256,7 +256,6 @@ EnergyWS carve_energy(Arena& a, bool lists, int N, int n_aux, int n_occ, int64_t
     w.coef = a.take<double>(8);
     w.Y = a.take<double>((int64_t)N * n_occ);
     w.Cp = a.take<double>((int64_t)N * n_occ);
-    w.R = a.take<double>((int64_t)N * n_occ);
     w.Mo = a.take<double>((int64_t)n_occ * n_occ);
     w.LinvM = a.take<double>((int64_t)n_occ * n_occ);
     w.dinvS = a.take<double>((int64_t)((N + 63) / 64) * 4096);

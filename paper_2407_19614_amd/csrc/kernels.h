@@ -99,7 +99,7 @@ hipError_t xs_run(const XSparse& w, int N, int n_aux, int n_occ, const double* C
 // FP32 arithmetic (BcT32): the dense FP32 kernel's result bit for bit
 hipError_t xs_transform32(const XSparse& w, int N, int n_aux, int n_occ, const double* C, float* Cf, float* Xt,
                           hipStream_t st);
-// gamma and (J != nullptr) J from the pair weights dpair (FP64 copy only)
+// gamma and J from the pair weights dpair (FP64 copy only)
 hipError_t xs_gamma_j(const XSparse& w, int N, int n_aux, const double* dpair, const int32_t* pairs, double* gamma,
                       double* J, hipStream_t st);
 // pair weights of D = 2 C C^T

@@ -70,8 +70,8 @@ __global__ __launch_bounds__(256) void fock_energy_kernel(const double* __restri
 // One upper 32 x 32 tile of e = M - M^T with its mirror -e^T, both written to the
 // ring with the same entries of F, and the tile pair's sums.
 __global__ __launch_bounds__(256) void error_push_kernel(const double* __restrict__ M, const double* __restrict__ F,
-                                                         MutPtrs dE, double* __restrict__ dFnew, Slots sl, int m,
-                                                         int N, double* __restrict__ red) {
+                                                         MutPtrs dE, double* __restrict__ dFnew, int m, int N,
+                                                         double* __restrict__ red) {
     __shared__ double t1[32][33], t2[32][33], sh[4];
     const int nt = (N + 31) / 32;
     int I = 0, rem = blockIdx.x;
@@ -297,12 +297,8 @@ hipError_t error_push(const double* M, const double* F, double* const* dE, doubl
                       int N, double* red, hipStream_t st) {
     if (m < 1 || m > 8) return hipErrorInvalidValue;
     MutPtrs e{};
-    Slots sl{};
-    for (int k = 0; k < m; ++k) {
-        e.p[k] = dE[slots[k]];
-        sl.s[k] = slots[k];
-    }
-    error_push_kernel<<<err_tiles(N), 256, 0, st>>>(M, F, e, dFnew, sl, m, N, red);
+    for (int k = 0; k < m; ++k) e.p[k] = dE[slots[k]];
+    error_push_kernel<<<err_tiles(N), 256, 0, st>>>(M, F, e, dFnew, m, N, red);
     return hipGetLastError();
 }
 hipError_t step_finish(double* red, const double* enuc, double* scal, double* Bfull, const int* slots, int m, int N,

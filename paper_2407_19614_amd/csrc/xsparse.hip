@@ -548,7 +548,6 @@ hipError_t xs_gamma_j(const XSparse& w, int N, int n_aux, const double* dpair, c
     RI_TRY(hipGetLastError());
     gamma_sum_kernel<<<w.ldp / 16, 256, 0, st>>>(w.gpart, strips, w.ldp, n_aux, gamma, gpad);
     RI_TRY(hipGetLastError());
-    if (!J) return hipSuccess;
     RI_TRY(fill(J, 0.0, (int64_t)N * N, st));
     j_rows_kernel<<<(unsigned)((w.n_pairs + 4 * JQ - 1) / (4 * JQ)), 256, 0, st>>>(w.BcT, w.n_pairs, nblk, gpad, pairs,
                                                                                   N, J);
