@@ -71,6 +71,8 @@ struct XSparse {
 // the lists and the copy, prepared in the call, serve one Fock build that could read
 // resident tiles; up to 512 MiB of X^T that pays up to 42 % (FP32: 34 %) only.
 // Measured, time on tiles over time on lists with their preparation:
+//   under 64 MiB, FP64: N = 150 0.79, N = 200 0.94, N = 250 0.97, N = 260 1.06; FP32:
+//     N = 150 0.79, N = 260 0.88, N = 300 0.99, N = 370 1.04;
 //   one Fock build, FP64: N = 300 1.11, 1.02, 0.86 at 29, 39, 50 % fill; N = 400
 //     1.22, 1.05, 0.98 at 26, 40, 47; N = 500 1.27, 1.05, 0.94 at 23, 37, 49; N =
 //     600 1.36, 1.08, 1.05 at 21, 51, 79; N = 1000 1.76, 1.25, 1.02 at 14, 44, 74;
