@@ -153,7 +153,7 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f64", "data": "synthetic",
         "config": {"workload": "n1000: 100 He-like centres, N=1000, N_aux=3000, n_occ=100, tau=1e-12, "
-                               "FP64, X over the significant pairs of the fitted tensor",
+                               "decompressed packed-tile FP64 B, X over the significant pairs of the fitted tensor",
                    "n_pairs": int(npairs), "parallelism": "single GPU"},
         "roofline": {"bound": "mfma", "kernel": "syrk_lds_kernel (K = sum_P X^P X^P^T)",
                      "achieved": round(achieved, 2), "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",

@@ -16,7 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libri.so")
 
 FP64, FP32, BF16X3, BF16X6 = 0, 1, 2, 3
-COMPRESSED = 0x10          # flag: B not resident, decompressed per auxiliary slab each call
+COMPRESSED = 0x10          # flag: B not resident (where X runs on tiles, decompressed per auxiliary slab each call)
 COMPRESSED_SLAB = 256
 FINAL_FP64 = 0x20          # SCF flag (FP32, BF16X3, BF16X6): one FP64 exchange build after the SCF
 OP_BUILD_3C, OP_METRIC, OP_FOCK, OP_ENERGY, OP_GRADIENT = range(5)
