@@ -704,21 +704,41 @@ __global__ __launch_bounds__(256) void greduce_kernel(const double* part, int ro
 // The blocks B_ij^P and Xi^P are symmetric in ij up to rounding.  pack: Bp[P][e] =
 // B[P][i][j] for the entries e = i (i + 1) / 2 + j, j <= i, times sqrt 2 off the
 // diagonal, so that sums over all ij are sums over e; unpack: both halves of
-// Xi[P] from Xp[P].  MEAN takes the mean of the two halves: after an FP32
-// half-transform they are rounded independently at 2^-24 (j's column of C in
-// FP32, i's in FP64), and one of them alone would carry sqrt 2 times the error
-// of both.  A workgroup per row (P, i); the mean's column reads stay within P's
-// block, which the rows beside it read too.
-template <bool MEAN>
+// Xi[P] from Xp[P].  A workgroup per row (P, i).
 __global__ __launch_bounds__(256) void pack_ij_kernel(const double* __restrict__ B, int o, double* __restrict__ Bp) {
     const int64_t P = blockIdx.x / o;
     const int i = (int)(blockIdx.x % o);
     const double* row = B + (P * o + i) * o;
-    const double* col = B + P * o * o + i;
     double* out = Bp + P * ((int64_t)o * (o + 1) / 2) + (int64_t)i * (i + 1) / 2;
-    for (int j = threadIdx.x; j <= i; j += blockDim.x) {
-        const double v = MEAN ? 0.5 * (row[j] + col[(int64_t)j * o]) : row[j];
-        out[j] = j == i ? v : 1.41421356237309504880 * v;
+    for (int j = threadIdx.x; j <= i; j += blockDim.x) out[j] = j == i ? row[j] : 1.41421356237309504880 * row[j];
+}
+// pack of the mean of the two halves: after an FP32 half-transform they are rounded
+// independently at 2^-24 (j's column of C in FP32, i's in FP64), and one of them
+// alone would carry sqrt 2 times the error of both.  A workgroup per lower 32 x 32
+// tile of a block, its mirror tile through LDS (gradient of N = 1000 in FP32 13.17
+// ms, 13.23 with the mirror read down its columns, 13.08 without the mean).
+__global__ __launch_bounds__(256) void pack_mean_ij_kernel(const double* __restrict__ B, int o, int tiles,
+                                                           double* __restrict__ Bp) {
+    __shared__ double m[32][33];
+    const int64_t P = blockIdx.x / tiles;
+    const int t = (int)(blockIdx.x % tiles), c = threadIdx.x & 31, r0 = threadIdx.x >> 5;
+    int I = 0;
+    while ((I + 1) * (I + 2) / 2 <= t) ++I;
+    const int J = t - I * (I + 1) / 2;
+    const double* blk = B + P * o * o;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {                  // mirror: rows of J, columns of I
+        const int r = 32 * J + r0 + 8 * k, q = 32 * I + c;
+        m[r0 + 8 * k][c] = (r < o && q < o) ? blk[(int64_t)r * o + q] : 0.0;
+    }
+    __syncthreads();
+    double* out = Bp + P * ((int64_t)o * (o + 1) / 2);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int i = 32 * I + r0 + 8 * k, j = 32 * J + c;
+        if (i >= o || j > i) continue;
+        const double v = 0.5 * (blk[(int64_t)i * o + j] + m[c][r0 + 8 * k]);
+        out[(int64_t)i * (i + 1) / 2 + j] = j == i ? v : 1.41421356237309504880 * v;
     }
 }
 __global__ __launch_bounds__(256) void unpack_ij_kernel(const double* __restrict__ Xp, int o, double* __restrict__ Xi) {
@@ -780,9 +800,9 @@ __global__ __launch_bounds__(256) void gamma_row_kernel(const double* Bc, int64_
 namespace ri {
 
 hipError_t pack_ij(const double* B, int o, int np, bool mean, double* Bp, hipStream_t st) {
-    const unsigned blocks = (unsigned)np * (unsigned)o, threads = o > 64 ? 128 : 64;
-    if (mean) pack_ij_kernel<true><<<blocks, threads, 0, st>>>(B, o, Bp);
-    else pack_ij_kernel<false><<<blocks, threads, 0, st>>>(B, o, Bp);
+    const int t = (o + 31) / 32, tiles = t * (t + 1) / 2;
+    if (mean) pack_mean_ij_kernel<<<(unsigned)np * (unsigned)tiles, 256, 0, st>>>(B, o, tiles, Bp);
+    else pack_ij_kernel<<<(unsigned)np * (unsigned)o, o > 64 ? 128 : 64, 0, st>>>(B, o, Bp);
     return hipGetLastError();
 }
 hipError_t mean_ij(double* B, int o, int np, hipStream_t st) {

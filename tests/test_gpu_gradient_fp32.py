@@ -72,3 +72,24 @@ def test_both_halves_enter(nc, n_occ):
     tol = 1e-13 * size
     assert np.abs(one_half - want).max() > 20 * tol               # the input tells the two apart
     assert np.abs(got - want).max() < tol
+
+
+# packed halves: occupied counts around the 32-wide tiles, sizes past the switch from whole blocks
+@pytest.mark.parametrize("nc,n_occ", [(21, 33), (20, 64), (20, 97), (13, 130)])
+def test_packed_halves_match_fp64(nc, n_occ):
+    need_gpu()
+    import paper_2407_19614_amd as P
+    print(f"case: FP32 gradient with packed halves, {nc} centres, {n_occ} occupied", flush=True)
+    s = synth.config_system("n400", n_centres=nc, seed=nc)
+    s.n_occ = n_occ
+    assert s.n_aux ** 2 * n_occ ** 2 >= 4e8
+    C, F = dev(synth.random_coeffs(s.N, n_occ, 3)), dev(synth.random_coeffs(s.N, s.N, 4))
+    g = []
+    for prec in (P.FP64, P.FP32):
+        pr = P.RIProblem(s, prec=prec)
+        pr.build_3c()
+        pr.metric_factor(prec)
+        g.append(pr.gradient(C, F + F.T))
+    # B and one C rounded to FP32, X to FP32 after sums of at most N products: 3 + log2 N roundings of 2^-24 on terms
+    # that cancel by up to 1e3 in the components' sums
+    assert float((g[0] - g[1]).norm() / g[0].norm()) < 11 * 2.0 ** -24 * 1e3
